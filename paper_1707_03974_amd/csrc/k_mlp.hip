@@ -4,9 +4,9 @@
 // Parameters live in one vector (W1 128x32, b1, W2 128x128, b2, W3 2x128, b3;
 // 20,994 values): FP32 master copy for Adam, BF16 copy for the kernels.
 // Dense products run on the BF16 matrix cores (16x16x32, FP32 accumulation):
-// one wave multiplies a tile of 16 states by the weights; a tile's first
-// hidden layer goes through LDS to change from the accumulator layout to the
-// operand layout of the second product.  Stored activations are BF16.
+// one wave multiplies the weights by tiles of 16 states, the rows of weights
+// dealt so that a layer's accumulators are the next layer's operands in
+// place.  Stored activations are BF16.
 //
 // Training samples states with probability proportional to |psi|^2 using
 // integer weights w_r = floor(2^32 psi_r^2 / max psi^2), an exact prefix sum
@@ -58,7 +58,8 @@ __device__ __forceinline__ f32x4 mma(bf16x8 a, bf16x8 b, f32x4 c) {
 }
 // tanh(x) = 1 - 2 / (exp(2x) + 1); saturates to +-1 for large |x|
 __device__ __forceinline__ float tanh_fast(float x) {
-    return 1.0f - 2.0f * __builtin_amdgcn_rcpf(__expf(2.0f * x) + 1.0f);
+    constexpr float k = 2.0f * 1.44269504088896340736f;   // exp(2x) = 2^(2x log2(e))
+    return fmaf(-2.0f, __builtin_amdgcn_rcpf(__builtin_amdgcn_exp2f(k * x) + 1.0f), 1.0f);
 }
 // 8 features (+-1 in BF16) of one operand slot: bits [off, off + 8) of `bits`
 __device__ __forceinline__ bf16x8 feature8(uint32_t bits) {
@@ -67,10 +68,6 @@ __device__ __forceinline__ bf16x8 feature8(uint32_t bits) {
     for (int t = 0; t < 8; ++t) v[t] = ((bits >> t) & 1u) ? (uint16_t)0x3F80 : (uint16_t)0xBF80;
     return pack8(v);
 }
-__device__ __forceinline__ float pick4(const float* p, int i) {
-    return i == 0 ? p[0] : (i == 1 ? p[1] : (i == 2 ? p[2] : p[3]));
-}
-
 // Source of the states of a forward pass.
 struct StateSrc {
     const uint32_t* occ;        // list mode: occ[2s] up bits, occ[2s+1] down bits
@@ -80,10 +77,10 @@ struct StateSrc {
 };
 template <bool BASIS>
 __device__ __forceinline__ void state_of(const StateSrc& S, uint64_t s, uint32_t* up, uint32_t* dn) {
-    if (BASIS) {
-        const uint64_t iu = s / S.D_dn;
+    if (BASIS) {   // at most 16 sites: the basis has fewer than 2^32 states
+        const uint32_t iu = (uint32_t)s / (uint32_t)S.D_dn;
         *up = S.up_states[iu];
-        *dn = S.dn_states[s - iu * S.D_dn];
+        *dn = S.dn_states[(uint32_t)s - iu * (uint32_t)S.D_dn];
     } else {
         *up = S.occ[2 * s];
         *dn = S.occ[2 * s + 1];
@@ -96,16 +93,149 @@ struct Act {                 // saved activations of a training forward pass (BF
     uint16_t* h2;            // n x 128
 };
 
+// Weights as a wave's matrix operands read them, staged in LDS (padded rows)
+// or held in registers.  Row r of the last layer's operand is row r mod 4 of
+// W3 with two rows of zeros below it.
+struct WLds {
+    const uint16_t *w1, *w2, *w3;
+    __device__ __forceinline__ bf16x8 l3(int q, int g, int c) const { return ld8(w3 + (c & 3) * kLd2 + 32 * q + 8 * g); }
+    __device__ __forceinline__ bf16x8 l1(int, int u, int g) const { return ld8(w1 + u * kLd1 + 8 * g); }
+    __device__ __forceinline__ bf16x8 l2(int, int k, int u, int g) const { return ld8(w2 + u * kLd2 + 32 * k + 8 * g); }
+};
+struct WReg {
+    bf16x8 w1[8], w2[8][4], w3[4];
+    __device__ __forceinline__ bf16x8 l3(int q, int, int) const { return w3[q]; }
+    __device__ __forceinline__ bf16x8 l1(int i, int, int) const { return w1[i]; }
+    __device__ __forceinline__ bf16x8 l2(int i, int k, int, int) const { return w2[i][k]; }
+};
+
+// Unit of row r in tile i of a hidden layer's operand order: tiles 2q and
+// 2q + 1 give the lane group g of the accumulators the units 32q + 8g .. + 3
+// and 32q + 8g + 4 .. + 7, that is the eight features 8g .. 8g + 7 of block q
+// that the same lane has to bring to the next product.
+__device__ __forceinline__ int tile_unit(int i, int r) { return 32 * (i >> 1) + 8 * (r >> 2) + 4 * (i & 1) + (r & 3); }
+
+// tanh of eight pre-activations (two accumulators plus biases), BF16
+__device__ __forceinline__ bf16x8 tanh8(f32x4 a, f32x4 b, f32x4 ba, f32x4 bb) {
+    typedef float f32x8 __attribute__((ext_vector_type(8)));
+    f32x8 v;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        v[t] = tanh_fast(a[t] + ba[t]);
+        v[4 + t] = tanh_fast(b[t] + bb[t]);
+    }
+    return __builtin_convertvector(v, bf16x8);   // round to nearest even, two per instruction
+}
+
+// One wave, 16 S states from s0: the three layers.  Products are weights
+// (rows: units) times states (columns), so a lane's accumulators hold four
+// units of one state; the rows are dealt (tile_unit) so that two tiles leave
+// a lane exactly the operand slot it feeds to the next layer, in the plain
+// feature order: no exchange between lanes, no LDS round trip and no barrier
+// between layers.  The last layer's two rows sit in rows 4s, 4s + 1 of the
+// operand of state tile s, so one accumulator collects all S tiles: with
+// S = 4 lane l holds (o_0, o_1) of state s0 + l in o[0], o[1] (S = 1: lanes
+// 0..15, state s0 + l).
+template <bool ACT, int S, typename W>
+__device__ __forceinline__ f32x4 mlp_layers(const W& w, const bf16x8 (&x)[S], const float* b1, const float* b2,
+                                            int g, int c, uint64_t s0, uint64_t n, const Act& act,
+                                            bool act_wide) {
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    bf16x8 h[S][4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const bf16x8 wa = w.l1(2 * q, tile_unit(2 * q, c), g), wb = w.l1(2 * q + 1, tile_unit(2 * q + 1, c), g);
+        const f32x4 ba = *reinterpret_cast<const f32x4*>(b1 + 32 * q + 8 * g);
+        const f32x4 bb = *reinterpret_cast<const f32x4*>(b1 + 32 * q + 8 * g + 4);
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            h[s][q] = tanh8(mma(wa, x[s], zero), mma(wb, x[s], zero), ba, bb);
+            const uint64_t st = s0 + 16 * s + c;
+            if (ACT && act.h1 && st < n) {
+                const u32x4 hv = __builtin_bit_cast(u32x4, h[s][q]);
+                uint16_t* row = act.h1 + st * kHid + 32 * q + 8 * g;
+                if (act_wide) *reinterpret_cast<u32x4*>(row) = hv;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const uint16_t hb = (uint16_t)((e & 1) ? (hv[e >> 1] >> 16) : (hv[e >> 1] & 0xFFFFu));
+                    if (!act_wide) row[e] = hb;
+                    act.h1t[(uint64_t)(32 * q + 8 * g + e) * n + st] = hb;
+                }
+            }
+        }
+    }
+    f32x4 o = zero;
+    int mine = c >> 2;
+    asm volatile("" : "+v"(mine));   // the masked rows below are formed when used, not kept over the caller's loop
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        if (S > 1) asm volatile("" ::: "memory");   // the next block's weights are not read before this one is done
+        f32x4 a[S], b[S];
+#pragma unroll
+        for (int s = 0; s < S; ++s) a[s] = b[s] = zero;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const bf16x8 wa = w.l2(2 * q, k, tile_unit(2 * q, c), g), wb = w.l2(2 * q + 1, k, tile_unit(2 * q + 1, c), g);
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                a[s] = mma(wa, h[s][k], a[s]);
+                b[s] = mma(wb, h[s][k], b[s]);
+            }
+        }
+        const f32x4 ba = *reinterpret_cast<const f32x4*>(b2 + 32 * q + 8 * g);
+        const f32x4 bb = *reinterpret_cast<const f32x4*>(b2 + 32 * q + 8 * g + 4);
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const bf16x8 h2 = tanh8(a[s], b[s], ba, bb);
+            const uint64_t st = s0 + 16 * s + c;
+            if (ACT && act.h2 && st < n) {
+                const u32x4 hv = __builtin_bit_cast(u32x4, h2);
+                uint16_t* row = act.h2 + st * kHid + 32 * q + 8 * g;
+                if (act_wide) *reinterpret_cast<u32x4*>(row) = hv;
+                else
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        row[e] = (uint16_t)((e & 1) ? (hv[e >> 1] >> 16) : (hv[e >> 1] & 0xFFFFu));
+            }
+            u32x4 m = __builtin_bit_cast(u32x4, w.l3(q, g, c));
+            if (S > 1 && mine != s) m = u32x4{0u, 0u, 0u, 0u};
+            o = mma(__builtin_bit_cast(bf16x8, m), h2, o);
+        }
+    }
+    return o;
+}
+
+// Features of a state whose up and down strings are packed as up | dn << 16:
+// operand slot g holds sites 8g .. 8g + 7 of the 32.
+__device__ __forceinline__ uint32_t pack_state(uint32_t up, uint32_t dn) { return (up & 0xFFFFu) | (dn << 16); }
+
+__device__ __forceinline__ void write_out(float* out, uint64_t s, float o0, float o1) {
+    out[2 * s] = o0;
+    out[2 * s + 1] = o1;
+}
+
 // Forward pass over n states.  BASIS = false: outputs (n x 2) and, when
-// act.h1 != NULL, the activations; BASIS = true: the start vector
+// act.h1 != NULL, the activations; BASIS = true (n < 2^32): the start vector
 // v0[s] = sign * exp(min(o_0, 60)), sign = + for o_1 >= 0.
+//
+// Bound by the vector ALUs: 256 tanh a state, each five vector instructions,
+// an exponential and a reciprocal.  A wave takes 64 states, so an operand of
+// weights is read from LDS once for four products (40 KB of LDS reads per 64
+// states; with 16 states a wave they would cost half as much as the ALU work).
+// 1.31e8 states (4x4, 7 + 7): 19.2 ms with 16 states a wave, the hidden layer
+// through LDS, scalar rounding to BF16 and the last layer on the vector ALUs;
+// 9.6 ms so (565 TFLOP/s).
+constexpr int kFwdTiles = 4;             // state tiles of 16 per wave
+constexpr int kFwdStates = 4 * 16 * kFwdTiles;   // states per work group and turn
 template <typename T, bool BASIS>
-__global__ __launch_bounds__(256) void k_mlp_fwd(const uint16_t* __restrict__ prm, StateSrc src, uint64_t n,
-                                                 float* __restrict__ out, Act act, T* __restrict__ v0) {
+__global__ __launch_bounds__(256, BASIS ? 3 : 2) void k_mlp_fwd(const uint16_t* __restrict__ prm, StateSrc src, uint64_t n,
+                                                    float* __restrict__ out, Act act, int act_wide,
+                                                    T* __restrict__ v0) {
     __shared__ __align__(16) uint16_t sW1[kHid * kLd1];
     __shared__ __align__(16) uint16_t sW2[kHid * kLd2];
-    __shared__ __align__(16) uint16_t sH[4][16 * kLd2];
-    __shared__ float sb1[kHid], sb2[kHid], sW3[kOut * kHid], sb3[kOut];
+    __shared__ __align__(16) uint16_t sW3[4 * kLd2];
+    __shared__ __align__(16) uint16_t sF[256 * 8];   // the eight features of every byte of occupations
+    __shared__ __align__(16) float sb1[kHid], sb2[kHid];
     const int tid = threadIdx.x;
     for (int i = tid; i < kHid * kIn; i += 256) sW1[(i / kIn) * kLd1 + (i % kIn)] = prm[oW1 + i];
     for (int i = tid; i < kHid * kHid; i += 256) sW2[(i / kHid) * kLd2 + (i % kHid)] = prm[oW2 + i];
@@ -113,83 +243,71 @@ __global__ __launch_bounds__(256) void k_mlp_fwd(const uint16_t* __restrict__ pr
         sb1[i] = bf2f(prm[oB1 + i]);
         sb2[i] = bf2f(prm[oB2 + i]);
     }
-    for (int i = tid; i < kOut * kHid; i += 256) sW3[i] = bf2f(prm[oW3 + i]);
-    if (tid < kOut) sb3[tid] = bf2f(prm[oB3 + tid]);
-    __syncthreads();
+    for (int i = tid; i < 4 * kHid; i += 256) sW3[(i / kHid) * kLd2 + (i % kHid)] = i < kOut * kHid ? prm[oW3 + i] : 0;
+    *reinterpret_cast<bf16x8*>(sF + 8 * tid) = feature8((uint32_t)tid);
     const int wave = tid >> 6, lane = tid & 63, g = lane >> 4, c = lane & 15;
-    uint16_t* h = sH[wave];
-    const uint64_t ngroups = (n + 63) / 64;
-    for (uint64_t grp = blockIdx.x; grp < ngroups; grp += gridDim.x) {   // block-uniform trip count
-        const uint64_t s0 = grp * 64 + (uint64_t)wave * 16;
-        // ---- layer 1: operand A holds state s0 + c, features 8g .. 8g+7
-        uint32_t up = 0, dn = 0;
-        {
-            const uint64_t sa = s0 + c;
-            state_of<BASIS>(src, sa < n ? sa : n - 1, &up, &dn);
-        }
-        const bf16x8 A1 = feature8(((g < 2) ? up : dn) >> (8 * (g & 1)));
+    const float b30 = bf2f(prm[oB3]), b31 = bf2f(prm[oB3 + 1]);
+    const WLds w{sW1, sW2, sW3};
+    __syncthreads();
+    for (uint64_t s0 = blockIdx.x * (uint64_t)kFwdStates + wave * (16 * kFwdTiles); s0 < n;
+         s0 += (uint64_t)gridDim.x * kFwdStates) {
+        const uint64_t own = s0 + lane, sa = own < n ? own : n - 1;
+        uint32_t up, dn;
+        state_of<BASIS>(src, sa, &up, &dn);
+        const uint32_t occ = pack_state(up, dn);
+        bf16x8 x[kFwdTiles];
 #pragma unroll
-        for (int ct = 0; ct < 8; ++ct) {
-            const int j = 16 * ct + c;
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-            acc = mma(A1, ld8(sW1 + j * kLd1 + 8 * g), acc);
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const uint16_t hb = f2bf(tanh_fast(acc[t] + sb1[j]));
-                h[(4 * g + t) * kLd2 + j] = hb;
-                const uint64_t s = s0 + 4 * g + t;
-                if (!BASIS && act.h1 && s < n) {
-                    act.h1[s * kHid + j] = hb;
-                    act.h1t[(uint64_t)j * n + s] = hb;
-                }
+        for (int s = 0; s < kFwdTiles; ++s)
+            x[s] = ld8(sF + 8 * (((uint32_t)__shfl((int)occ, 16 * s + c) >> (8 * g)) & 255u));
+        asm volatile("" ::: "memory");   // read the weights anew each turn: kept, they would not fit the registers
+        const f32x4 o = mlp_layers<!BASIS, kFwdTiles>(w, x, sb1, sb2, g, c, s0, n, act, act_wide != 0);
+        if (own < n) {
+            const float o0 = o[0] + b30, o1 = o[1] + b31;
+            if (BASIS) {
+                const double a = exp((double)fminf(o0, 60.0f));
+                v0[own] = (T)(o1 >= 0.0f ? a : -a);
+            } else {
+                write_out(out, own, o0, o1);
             }
         }
-        __syncthreads();
-        // ---- layer 2: operand A = row c of the tile, features 32kc + 8g ..
-        bf16x8 A2[4];
-#pragma unroll
-        for (int kc = 0; kc < 4; ++kc) A2[kc] = ld8(h + c * kLd2 + 32 * kc + 8 * g);
-        float p0[4] = {0.f, 0.f, 0.f, 0.f}, p1[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ct = 0; ct < 8; ++ct) {
-            const int j = 16 * ct + c;
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int kc = 0; kc < 4; ++kc) acc = mma(A2[kc], ld8(sW2 + j * kLd2 + 32 * kc + 8 * g), acc);
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const uint16_t hb = f2bf(tanh_fast(acc[t] + sb2[j]));
-                const float hq = bf2f(hb);
-                const uint64_t s = s0 + 4 * g + t;
-                if (!BASIS && act.h2 && s < n) act.h2[s * kHid + j] = hb;
-                p0[t] += hq * sW3[j];
-                p1[t] += hq * sW3[kHid + j];
-            }
-        }
-        // ---- layer 3: sum the 16 lanes of each state group
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int m = 1; m < 16; m <<= 1) {
-                p0[t] += __shfl_xor(p0[t], m);
-                p1[t] += __shfl_xor(p1[t], m);
-            }
-        if (c < 4) {
-            const uint64_t s = s0 + 4 * g + c;
-            if (s < n) {
-                const float o0 = pick4(p0, c) + sb3[0];
-                const float o1 = pick4(p1, c) + sb3[1];
-                if (BASIS) {
-                    const double a = exp((double)fminf(o0, 60.0f));
-                    v0[s] = (T)(o1 >= 0.0f ? a : -a);
-                } else {
-                    out[2 * s] = o0;
-                    out[2 * s + 1] = o1;
-                }
-            }
-        }
-        __syncthreads();   // the tile buffer is rewritten by the next group
     }
+}
+
+// The same for a list of at most kFwdFew states, one wave per 16: at these
+// sizes the time is latency, so a work group is one wave that holds the
+// weights in registers (40 loads of 16 bytes a lane, all in flight at once,
+// instead of staging them through LDS behind a barrier).  A training gradient
+// of 4096 states took 74 us with the kernel above at 16 states a wave, 66 us
+// with this one (nothing else changed).  prm 16-byte aligned.
+constexpr uint64_t kFwdFew = 16384;
+__global__ __launch_bounds__(64) void k_mlp_fwd_few(const uint16_t* __restrict__ prm,
+                                                    const uint32_t* __restrict__ occ, uint64_t n,
+                                                    float* __restrict__ out, Act act, int act_wide) {
+    __shared__ __align__(16) float sb1[kHid], sb2[kHid];
+    const int lane = threadIdx.x, g = lane >> 4, c = lane & 15;
+    const uint64_t s0 = blockIdx.x * 16ull, own = s0 + c, sa = own < n ? own : n - 1;
+    const uint32_t st = pack_state(occ[2 * sa], occ[2 * sa + 1]);
+    for (int i = lane; i < kHid; i += 64) {
+        sb1[i] = bf2f(prm[oB1 + i]);
+        sb2[i] = bf2f(prm[oB2 + i]);
+    }
+    WReg w;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int u = tile_unit(i, c);
+        w.w1[i] = ld8(prm + oW1 + u * kIn + 8 * g);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) w.w2[i][k] = ld8(prm + oW2 + u * kHid + 32 * k + 8 * g);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {   // rows of other tiles than the one there is stay zero
+        const uint16_t none[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+        w.w3[q] = c < kOut ? ld8(prm + oW3 + c * kHid + 32 * q + 8 * g) : pack8(none);
+    }
+    const bf16x8 x[1] = {feature8(st >> (8 * g))};
+    __syncthreads();
+    const f32x4 o = mlp_layers<true, 1>(w, x, sb1, sb2, g, c, s0, n, act, act_wide != 0);
+    if (g == 0 && own < n) write_out(out, own, o[0] + bf2f(prm[oB3]), o[1] + bf2f(prm[oB3 + 1]));
 }
 
 // dout and the per-block loss partial sums.
@@ -614,8 +732,8 @@ SampWs samp_ws(uint64_t D) {
 int fwd_grid(uint64_t n) {
     DeviceCtx* ctx = nullptr;
     const int cu = (device_ctx(&ctx) == PDZ_OK && ctx) ? ctx->cu_count : 256;
-    const uint64_t groups = (n + 63) / 64;
-    const uint64_t g = (uint64_t)cu * 2;
+    const uint64_t groups = (n + kFwdStates - 1) / kFwdStates;
+    const uint64_t g = (uint64_t)cu * 3;   // three work groups fit a CU (50 KB of LDS, 168 registers)
     return (int)(groups < g ? groups : g);
 }
 
@@ -704,8 +822,13 @@ pdz_status pdz_mlp_forward(const uint16_t* params_bf16, const uint32_t* occ, uin
     if (n > (1ull << 32)) return fail(PDZ_ERANGE, "at most 2^32 states per call");
     StateSrc src{occ, nullptr, nullptr, 1};
     const Act a = act_views(act, n);
-    hipLaunchKernelGGL((k_mlp_fwd<float, false>), dim3(fwd_grid(n)), dim3(256), 0, (hipStream_t)stream, params_bf16,
-                       src, n, out, a, (float*)nullptr);
+    const int act_wide = reinterpret_cast<uintptr_t>(act) % 16 == 0;   // 16-byte stores of the activations
+    if (n <= kFwdFew && reinterpret_cast<uintptr_t>(params_bf16) % 16 == 0)
+        hipLaunchKernelGGL(k_mlp_fwd_few, dim3((unsigned)((n + 15) / 16)), dim3(64), 0, (hipStream_t)stream,
+                           params_bf16, occ, n, out, a, act_wide);
+    else
+        hipLaunchKernelGGL((k_mlp_fwd<float, false>), dim3(fwd_grid(n)), dim3(256), 0, (hipStream_t)stream,
+                           params_bf16, src, n, out, a, act_wide, (float*)nullptr);
     PDZ_HIP(hipGetLastError());
     return ok();
 }
@@ -820,10 +943,10 @@ pdz_status pdz_start_vector(pdz_problem p, const uint16_t* params_bf16, pdz_dtyp
     hipStream_t s = (hipStream_t)stream;
     if (dt == PDZ_F64)
         hipLaunchKernelGGL((k_mlp_fwd<double, true>), dim3(fwd_grid(p->D)), dim3(256), 0, s, params_bf16, src, p->D,
-                           (float*)nullptr, none, static_cast<double*>(v0));
+                           (float*)nullptr, none, 0, static_cast<double*>(v0));
     else
         hipLaunchKernelGGL((k_mlp_fwd<float, true>), dim3(fwd_grid(p->D)), dim3(256), 0, s, params_bf16, src, p->D,
-                           (float*)nullptr, none, static_cast<float*>(v0));
+                           (float*)nullptr, none, 0, static_cast<float*>(v0));
     PDZ_HIP(hipGetLastError());
     return ok();
 }
