@@ -28,7 +28,6 @@ constexpr int oW1 = 0, oB1 = kHid * kIn, oW2 = oB1 + kHid, oB2 = oW2 + kHid * kH
 static_assert(oB3 + kOut == kParams, "parameter layout");
 constexpr int kLd1 = kIn + 8;    // padded LDS row of W1 (bf16 elements)
 constexpr int kLd2 = kHid + 8;   // padded LDS row of W2 / W2^T / hidden tiles
-constexpr int kSlice = 512;      // states per partial weight gradient
 constexpr int kLossBlocks = 64;
 constexpr int kScanChunk = 8192;   // elements per block of the sampler prefix sum (32 per thread)
 
@@ -310,13 +309,17 @@ __global__ __launch_bounds__(64) void k_mlp_fwd_few(const uint16_t* __restrict__
     if (g == 0 && own < n) write_out(out, own, o[0] + bf2f(prm[oB3]), o[1] + bf2f(prm[oB3 + 1]));
 }
 
-// dout and the per-block loss partial sums.
-__global__ __launch_bounds__(256) void k_mlp_loss(const float* __restrict__ out, const float* __restrict__ target,
-                                                  uint64_t n, float* __restrict__ dout, double* partial) {
-    __shared__ double red[256];
+// dout and the loss partial sums of one work group of BLOCK threads; with
+// one work group (at most kLossOne states) partial is the loss itself.
+constexpr uint64_t kLossOne = 8192;
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK) void k_mlp_loss(const float* __restrict__ out, const float* __restrict__ target,
+                                                    uint64_t n, float* __restrict__ dout, double* partial,
+                                                    double scale) {
+    __shared__ double red[BLOCK / 64];
     double acc = 0.0;
     const float inv_n = 1.0f / (float)n;
-    for (uint64_t s = blockIdx.x * 256ull + threadIdx.x; s < n; s += (uint64_t)gridDim.x * 256) {
+    for (uint64_t s = blockIdx.x * (uint64_t)BLOCK + threadIdx.x; s < n; s += (uint64_t)gridDim.x * BLOCK) {
         const float a = out[2 * s], z = out[2 * s + 1];
         const float la = target[2 * s];
         const float y = target[2 * s + 1] > 0.0f ? 1.0f : 0.0f;
@@ -326,13 +329,15 @@ __global__ __launch_bounds__(256) void k_mlp_loss(const float* __restrict__ out,
         dout[2 * s] = 2.0f * d * inv_n;
         dout[2 * s + 1] = (1.0f / (1.0f + expf(-z)) - y) * inv_n;
     }
-    red[threadIdx.x] = acc;
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1) acc += __shfl_xor(acc, m);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
     __syncthreads();
-    for (int st = 128; st > 0; st >>= 1) {
-        if (threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
-        __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = red[0];
+        for (int i = 1; i < BLOCK / 64; ++i) t += red[i];
+        partial[blockIdx.x] = t * scale;
     }
-    if (threadIdx.x == 0) partial[blockIdx.x] = red[0];
 }
 
 __global__ void k_sum_partials(const double* partial, int np, double scale, double* result) {
@@ -343,49 +348,118 @@ __global__ void k_sum_partials(const double* partial, int np, double scale, doub
     }
 }
 
-// Backward, per state: dz2 = (dout W3) (1 - h2^2) and dz1 = (dz2 W2) (1 - h1^2),
-// both stored transposed (BF16).  One wave per tile of 16 states; n % 16 == 0.
-__global__ __launch_bounds__(256) void k_mlp_bwd_act(const uint16_t* __restrict__ prm, uint64_t n, Act act,
-                                                     const float* __restrict__ dout, uint16_t* __restrict__ dz2t,
-                                                     uint16_t* __restrict__ dz1t) {
+// Backward over one slice of states per work group, in chunks of 64 states:
+//   dz2 = (dout W3) (1 - h2^2), dz1 = (dz2 W2) (1 - h1^2)   (BF16, in LDS)
+//   dW2 += dz2^T h1, dW1 += dz1^T x, b2 += dz2^T 1, b1 += dz1^T 1 on the matrix cores,
+//   dW3 += dout^T h2, b3 += dout^T 1 in FP32.
+// Wave w: states 16 (w & 3) .. + 15 of the chunk and half w >> 2 of the units
+// for dz1; then the unit rows 16 w .. + 15 of the weight gradients, whose
+// accumulators stay in registers over the chunks.  The slice's sums go to
+// part[slice * kParams + k] (to grad itself when there is one slice).
+//
+// Bound by latency: at 4096 states a work group has one chunk, and its time is
+// one round of loads, 16 + 40 products a wave and the stores of its partial
+// gradient.  dz2 and dz1 never leave LDS; as kernels of their own (dz1, dz2
+// through memory, then 16x16 gradient tiles with 16 dependent load rounds of
+// 32 states each) these took 11 + 37 us at 4096 states; the whole gradient of
+// 4096 states 66 us then, 30 us with this kernel and a one-launch loss.
+constexpr int kBwdBlock = 512;
+constexpr int kChunk = 64;             // states per chunk
+constexpr int kMaxSlices = 256;        // one work group per CU
+constexpr int kLdS = kChunk + 8;       // padded LDS row of a [unit][state] tile
+__global__ __launch_bounds__(kBwdBlock) void k_mlp_bwd(const uint16_t* __restrict__ prm, int prm_wide,
+                                                       const uint32_t* __restrict__ occ, uint64_t n, uint64_t slice_len,
+                                                       Act act, const float* __restrict__ dout,
+                                                       float* __restrict__ part) {
     __shared__ __align__(16) uint16_t sW2t[kHid * kLd2];   // sW2t[j][o] = W2[o][j]
+    __shared__ __align__(16) uint16_t sZ2[kHid * kLdS], sZ1[kHid * kLdS], sH1[kHid * kLdS];
     __shared__ float sW3[kOut * kHid];
+    __shared__ float sD[kChunk * kOut];
+    __shared__ __align__(16) uint32_t sOcc[kChunk];
+    __shared__ float sR[3][kHid * kOut];
     const int tid = threadIdx.x;
-    for (int i = tid; i < kHid * kHid; i += 256) sW2t[(i % kHid) * kLd2 + (i / kHid)] = prm[oW2 + i];
-    for (int i = tid; i < kOut * kHid; i += 256) sW3[i] = bf2f(prm[oW3 + i]);
-    __syncthreads();
     const int wave = tid >> 6, lane = tid & 63, g = lane >> 4, c = lane & 15;
-    const uint64_t ntiles = n / 16;
-    for (uint64_t tile = (uint64_t)blockIdx.x * 4 + wave; tile < ntiles; tile += (uint64_t)gridDim.x * 4) {
-        const uint64_t s0 = tile * 16;
-        // dz2 of state s0 + c, units 32kc + 8g + t, in operand layout
-        const uint64_t sa = s0 + c;
-        const float d0 = dout[2 * sa], d1 = dout[2 * sa + 1];
+    const uint64_t b0 = blockIdx.x * slice_len;
+    const uint64_t b1 = b0 + slice_len < n ? b0 + slice_len : n;
+    // W2 transposed: a wave reads eight columns of 64 rows at a time
+    for (int i = tid; i < kHid * kHid / 8; i += kBwdBlock) {
+        const int o = i & (kHid - 1), j0 = 8 * (i >> 7);
+        uint16_t v[8];
+        if (prm_wide) {
+            const u32x4 u = *reinterpret_cast<const u32x4*>(prm + oW2 + o * kHid + j0);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = (uint16_t)((e & 1) ? (u[e >> 1] >> 16) : (u[e >> 1] & 0xFFFFu));
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = prm[oW2 + o * kHid + j0 + e];
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sW2t[(j0 + e) * kLd2 + o] = v[e];
+    }
+    if (tid < kOut * kHid) sW3[tid] = bf2f(prm[oW3 + tid]);
+    const uint16_t one8[8] = {0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80};   // BF16 1.0
+    const bf16x8 ones = pack8(one8);
+    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    f32x4 g2[8], g1[2], gb2 = zero, gb1 = zero;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) g2[t] = zero;
+    g1[0] = g1[1] = zero;
+    float w30 = 0.f, w31 = 0.f, e0 = 0.f, e1 = 0.f;
+    const int tile = wave & 3, half = wave >> 2;
+    for (uint64_t s0 = b0; s0 < b1; s0 += kChunk) {   // b0, b1, n: multiples of 32
+        if (s0 != b0) __syncthreads();   // the tiles of the chunk before are read
+        // h1^T of the chunk: eight states per 16-byte load; states past the slice are zeros
+        for (int i = tid; i < kHid * kChunk / 8; i += kBwdBlock) {
+            const int j = i >> 3, sl = 8 * (i & 7);
+            u32x4 v = {0u, 0u, 0u, 0u};
+            if (s0 + sl < b1) v = *reinterpret_cast<const u32x4*>(act.h1t + (uint64_t)j * n + s0 + sl);
+            *reinterpret_cast<u32x4*>(sH1 + j * kLdS + sl) = v;
+        }
+        if (tid < kChunk) {
+            const uint64_t s = s0 + tid;
+            const bool in = s < b1;
+            sOcc[tid] = in ? pack_state(occ[2 * s], occ[2 * s + 1]) : 0u;
+            const float d0 = in ? dout[2 * s] : 0.f, d1 = in ? dout[2 * s + 1] : 0.f;
+            sD[2 * tid] = d0;
+            sD[2 * tid + 1] = d1;
+            e0 += d0;
+            e1 += d1;
+        }
+        u32x4 hv[4];
+        {
+            const uint64_t s = s0 + 16 * tile + c;
+#pragma unroll
+            for (int kc = 0; kc < 4; ++kc)
+                hv[kc] = s < b1 ? *reinterpret_cast<const u32x4*>(act.h2 + s * kHid + 32 * kc + 8 * g)
+                                : u32x4{0u, 0u, 0u, 0u};
+        }
+        __syncthreads();
+        // dz2 of state 16 tile + c, units 32kc + 8g + t, in operand layout
         bf16x8 A[4];
+        const float d0 = sD[2 * (16 * tile + c)], d1 = sD[2 * (16 * tile + c) + 1];
 #pragma unroll
         for (int kc = 0; kc < 4; ++kc) {
             const int o0 = 32 * kc + 8 * g;
-            const u32x4 hv = *reinterpret_cast<const u32x4*>(act.h2 + sa * kHid + o0);
             uint16_t v[8];
 #pragma unroll
             for (int t = 0; t < 8; ++t) {
-                const uint32_t w = hv[t >> 1];
+                const uint32_t w = hv[kc][t >> 1];
                 const float h2 = bf2f((uint16_t)((t & 1) ? (w >> 16) : (w & 0xFFFFu)));
-                const float dz = (d0 * sW3[o0 + t] + d1 * sW3[kHid + o0 + t]) * (1.0f - h2 * h2);
-                v[t] = f2bf(dz);
-                dz2t[(uint64_t)(o0 + t) * n + sa] = v[t];
+                v[t] = f2bf((d0 * sW3[o0 + t] + d1 * sW3[kHid + o0 + t]) * (1.0f - h2 * h2));
             }
+            if ((kc >> 1) == half)   // the two waves of a tile store one half each
+#pragma unroll
+                for (int t = 0; t < 8; ++t) sZ2[(o0 + t) * kLdS + 16 * tile + c] = v[t];
             A[kc] = pack8(v);
         }
-        // dh1 = dz2 W2 on the matrix cores; accumulator rows 4g + t, column j
+        // dh1 = dz2 W2; accumulator rows: states 16 tile + 4g + t, column: unit j
 #pragma unroll
-        for (int ct = 0; ct < 8; ++ct) {
-            const int j = 16 * ct + c;
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int ct = 0; ct < 4; ++ct) {
+            const int j = 64 * half + 16 * ct + c;
+            f32x4 acc = zero;
 #pragma unroll
             for (int kc = 0; kc < 4; ++kc) acc = mma(A[kc], ld8(sW2t + j * kLd2 + 32 * kc + 8 * g), acc);
-            const uint64_t s = s0 + 4 * g;
-            const uint2 h1w = *reinterpret_cast<const uint2*>(act.h1t + (uint64_t)j * n + s);
+            const uint2 h1w = *reinterpret_cast<const uint2*>(sH1 + j * kLdS + 16 * tile + 4 * g);
             uint16_t o[4];
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
@@ -396,124 +470,97 @@ __global__ __launch_bounds__(256) void k_mlp_bwd_act(const uint16_t* __restrict_
             uint2 st;
             st.x = o[0] | ((uint32_t)o[1] << 16);
             st.y = o[2] | ((uint32_t)o[3] << 16);
-            *reinterpret_cast<uint2*>(dz1t + (uint64_t)j * n + s) = st;
+            *reinterpret_cast<uint2*>(sZ1 + j * kLdS + 16 * tile + 4 * g) = st;
         }
-    }
-}
-
-// Weight-gradient partials over one slice of states (one wave per job):
-// jobs 0..63: 16x16 tiles of dW2 = dz2^T h1 (tiles of column block 0 also
-// b2 = dz2^T 1, a second product with an all-ones operand); jobs 64..71:
-// 16-unit rows of dW1 = dz1^T x (and b1 = dz1^T 1); jobs 72..79: 16 columns
-// of W3 = dout^T h2 each, the 64 lanes as 16 columns x 4 interleaved sample
-// streams (job 72 also b3 = dout^T 1).  part[slice * kParams + k].
-constexpr int kGradJobs = 80;
-__global__ __launch_bounds__(64) void k_mlp_bwd_grad(const uint32_t* __restrict__ occ, uint64_t n, Act act,
-                                                     const float* __restrict__ dout,
-                                                     const uint16_t* __restrict__ dz2t,
-                                                     const uint16_t* __restrict__ dz1t, float* __restrict__ part) {
-    const int job = blockIdx.x;
-    const int slice = blockIdx.y;
-    const uint64_t b0 = (uint64_t)slice * kSlice;
-    const uint64_t b1 = (b0 + kSlice < n) ? b0 + kSlice : n;
-    const int lane = threadIdx.x, g = lane >> 4, c = lane & 15;
-    float* P = part + (size_t)slice * kParams;
-    const uint16_t one8[8] = {0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80, 0x3F80};   // BF16 1.0
-    const bf16x8 ones = pack8(one8);
-    if (job < 64) {
-        const int ot = job >> 3, jt = job & 7;
-        const int o = 16 * ot + c, j = 16 * jt + c;
-        const bool bias = jt == 0;   // wave-uniform
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f}, accb = {0.f, 0.f, 0.f, 0.f};
-        for (uint64_t s = b0; s < b1; s += 32) {
-            const bf16x8 a = ld8(dz2t + (uint64_t)o * n + s + 8 * g);
-            acc = mma(a, ld8(act.h1t + (uint64_t)j * n + s + 8 * g), acc);
-            if (bias) accb = mma(a, ones, accb);
+        // W3: unit tid mod 128, the chunk's states 16 (tid / 128) .. + 15
+        {
+            const int j = tid & (kHid - 1), q = tid >> 7;
+            float h[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                const uint64_t s = s0 + 16 * q + u;
+                h[u] = s < b1 ? bf2f(act.h2[s * kHid + j]) : 0.f;
+            }
+#pragma unroll
+            for (int u = 0; u < 16; ++u) {
+                w30 += sD[2 * (16 * q + u)] * h[u];
+                w31 += sD[2 * (16 * q + u) + 1] * h[u];
+            }
         }
+        __syncthreads();
+        // weight gradients of unit rows 16 wave + c over the chunk's states
 #pragma unroll
-        for (int t = 0; t < 4; ++t) P[oW2 + (16 * ot + 4 * g + t) * kHid + j] = acc[t];
-        if (bias && c == 0)   // every column of accb holds the row sums
+        for (int k = 0; k < kChunk; k += 32) {
+            const bf16x8 a2 = ld8(sZ2 + (16 * wave + c) * kLdS + k + 8 * g);
 #pragma unroll
-            for (int t = 0; t < 4; ++t) P[oB2 + 16 * ot + 4 * g + t] = accb[t];
-    } else if (job < 72) {
-        const int ot = job - 64;
-        const int o = 16 * ot + c;
-        f32x4 accb = {0.f, 0.f, 0.f, 0.f};
+            for (int jt = 0; jt < 8; ++jt) g2[jt] = mma(a2, ld8(sH1 + (16 * jt + c) * kLdS + k + 8 * g), g2[jt]);
+            gb2 = mma(a2, ones, gb2);
+            const bf16x8 a1 = ld8(sZ1 + (16 * wave + c) * kLdS + k + 8 * g);
+            const u32x4 oa = *reinterpret_cast<const u32x4*>(sOcc + k + 8 * g);
+            const u32x4 ob = *reinterpret_cast<const u32x4*>(sOcc + k + 8 * g + 4);
 #pragma unroll
-        for (int it = 0; it < 2; ++it) {
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-            const int i = 16 * it + c;   // feature i: up site i (i < 16) or down site i - 16
-            for (uint64_t s = b0; s < b1; s += 32) {
-                uint16_t v[8];
+            for (int it = 0; it < 2; ++it) {   // feature i = 16 it + c of states k + 8g + e: +1 where its bit is set
+                u32x4 f;
 #pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    const uint32_t bits = occ[2 * (s + 8 * g + t) + (i >> 4)];
-                    v[t] = ((bits >> (i & 15)) & 1u) ? (uint16_t)0x3F80 : (uint16_t)0xBF80;
+                for (int e = 0; e < 4; ++e) {
+                    const uint32_t lo = e < 2 ? oa[2 * e] : ob[2 * e - 4], hi = e < 2 ? oa[2 * e + 1] : ob[2 * e - 3];
+                    f[e] = 0xBF80BF80u ^ (((lo >> (16 * it + c)) & 1u) << 15) ^ (((hi >> (16 * it + c)) & 1u) << 31);
                 }
-                const bf16x8 a = ld8(dz1t + (uint64_t)o * n + s + 8 * g);
-                acc = mma(a, pack8(v), acc);
-                if (it == 0) accb = mma(a, ones, accb);
+                g1[it] = mma(a1, __builtin_bit_cast(bf16x8, f), g1[it]);
             }
-#pragma unroll
-            for (int t = 0; t < 4; ++t) P[oW1 + (16 * ot + 4 * g + t) * kIn + i] = acc[t];
+            gb1 = mma(a1, ones, gb1);
         }
-        if (c == 0)
+    }
+    float* P = part + (size_t)blockIdx.x * kParams;
 #pragma unroll
-            for (int t = 0; t < 4; ++t) P[oB1 + 16 * ot + 4 * g + t] = accb[t];
-    } else {
-        const int jt = job - 72;
-        const int j = 16 * jt + c;
-        float a0 = 0.f, a1 = 0.f;
-        constexpr int U = 8;   // loads in flight per lane
-        for (uint64_t s0 = b0 + (uint64_t)g; s0 < b1; s0 += 4 * U) {
-            float h[U], d0[U], d1[U];
+    for (int t = 0; t < 4; ++t) {
+        const int o = 16 * wave + 4 * g + t;
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint64_t s = s0 + 4 * (uint64_t)u;
-                const bool in = s < b1;
-                h[u] = in ? bf2f(act.h2[s * kHid + j]) : 0.f;
-                d0[u] = in ? dout[2 * s] : 0.f;
-                d1[u] = in ? dout[2 * s + 1] : 0.f;
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                a0 += d0[u] * h[u];
-                a1 += d1[u] * h[u];
-            }
+        for (int jt = 0; jt < 8; ++jt) P[oW2 + o * kHid + 16 * jt + c] = g2[jt][t];
+        P[oW1 + o * kIn + c] = g1[0][t];
+        P[oW1 + o * kIn + 16 + c] = g1[1][t];
+        if (c == 0) {   // every column of gb holds the row sums
+            P[oB2 + o] = gb2[t];
+            P[oB1 + o] = gb1[t];
         }
-        a0 += __shfl_xor(a0, 16);
-        a0 += __shfl_xor(a0, 32);
-        a1 += __shfl_xor(a1, 16);
-        a1 += __shfl_xor(a1, 32);
-        if (g == 0) {
-            P[oW3 + j] = a0;
-            P[oW3 + kHid + j] = a1;
+    }
+    if (tid >= kHid) {
+        sR[(tid >> 7) - 1][tid & (kHid - 1)] = w30;
+        sR[(tid >> 7) - 1][kHid + (tid & (kHid - 1))] = w31;
+    }
+    __syncthreads();
+    if (tid < kHid) {
+        P[oW3 + tid] = ((w30 + sR[0][tid]) + sR[1][tid]) + sR[2][tid];
+        P[oW3 + kHid + tid] = ((w31 + sR[0][kHid + tid]) + sR[1][kHid + tid]) + sR[2][kHid + tid];
+    }
+    if (wave == 0) {
+#pragma unroll
+        for (int m = 32; m > 0; m >>= 1) {
+            e0 += __shfl_xor(e0, m);
+            e1 += __shfl_xor(e1, m);
         }
-        if (jt == 0) {
-            float e0 = 0.f, e1 = 0.f;
-            for (uint64_t s = b0 + (uint64_t)lane; s < b1; s += 64) {
-                e0 += dout[2 * s];
-                e1 += dout[2 * s + 1];
-            }
-            for (int m = 32; m > 0; m >>= 1) {
-                e0 += __shfl_xor(e0, m);
-                e1 += __shfl_xor(e1, m);
-            }
-            if (lane == 0) {
-                P[oB3] = e0;
-                P[oB3 + 1] = e1;
-            }
+        if (lane == 0) {
+            P[oB3] = e0;
+            P[oB3 + 1] = e1;
         }
     }
 }
 
+// Sum of the slices, one wave per 64 parameters and every fourth slice, the
+// four sums combined in a fixed order.
 __global__ __launch_bounds__(256) void k_mlp_grad_reduce(const float* __restrict__ part, int slices,
                                                          float* __restrict__ grad) {
-    const int k = blockIdx.x * 256 + threadIdx.x;
-    if (k >= kParams) return;
+    __shared__ float red[3][64];
+    const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
+    const int k = blockIdx.x * 64 + lane;
     float s = 0.f;
-    for (int i = 0; i < slices; ++i) s += part[(size_t)i * kParams + k];
-    grad[k] = s;
+    if (k < kParams) {
+#pragma unroll 16
+        for (int i = q; i < slices; i += 4) s += part[(size_t)i * kParams + k];
+    }
+    if (q > 0) red[q - 1][lane] = s;
+    __syncthreads();
+    if (q == 0 && k < kParams) grad[k] = ((s + red[0][lane]) + red[1][lane]) + red[2][lane];
 }
 
 __global__ __launch_bounds__(256) void k_adam(float* __restrict__ w, uint16_t* __restrict__ wb,
@@ -692,17 +739,17 @@ __global__ __launch_bounds__(256) void k_vdot(const T* __restrict__ a, const T* 
 size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 struct MlpWs {
-    size_t dz2t = 0, dz1t = 0, part = 0, loss = 0, total = 0;
+    size_t part = 0, loss = 0, total = 0;
     int slices = 0;
+    uint64_t slice_len = 0;   // states per slice, a multiple of kChunk
 };
 MlpWs mlp_ws(uint64_t n) {
     MlpWs w;
-    w.slices = (int)((n + kSlice - 1) / kSlice);
+    const uint64_t chunks = (n + kChunk - 1) / kChunk;
+    const uint64_t per = (chunks + kMaxSlices - 1) / kMaxSlices;   // chunks per slice
+    w.slice_len = per * kChunk;
+    w.slices = per ? (int)((chunks + per - 1) / per) : 0;
     size_t off = 0;
-    w.dz2t = off;
-    off += al256((size_t)n * kHid * 2);
-    w.dz1t = off;
-    off += al256((size_t)n * kHid * 2);
     w.part = off;
     off += al256((size_t)w.slices * kParams * 4);
     w.loss = off;
@@ -847,8 +894,13 @@ pdz_status pdz_mlp_loss(const float* out, const float* target, uint64_t n, float
     if (ws_bytes < w.total) return fail(PDZ_EINVAL, "workspace smaller than pdz_mlp_workspace_size");
     double* part = reinterpret_cast<double*>(static_cast<char*>(ws) + w.loss);
     hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(k_mlp_loss, dim3(kLossBlocks), dim3(256), 0, s, out, target, n, dout, part);
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(64), 0, s, part, kLossBlocks, 1.0 / (double)n, loss);
+    // one launch while a work group has at most eight states a thread (the sum over work groups is a launch of its own)
+    if (n <= kLossOne) {
+        hipLaunchKernelGGL(k_mlp_loss<1024>, dim3(1), dim3(1024), 0, s, out, target, n, dout, loss, 1.0 / (double)n);
+    } else {
+        hipLaunchKernelGGL(k_mlp_loss<256>, dim3(kLossBlocks), dim3(256), 0, s, out, target, n, dout, part, 1.0);
+        hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(64), 0, s, part, kLossBlocks, 1.0 / (double)n, loss);
+    }
     PDZ_HIP(hipGetLastError());
     return ok();
 }
@@ -863,17 +915,15 @@ pdz_status pdz_mlp_backward(const uint16_t* params_bf16, const uint32_t* occ, ui
     if (reinterpret_cast<uintptr_t>(ws) % 256 || reinterpret_cast<uintptr_t>(act) % 16)
         return fail(PDZ_EINVAL, "workspace must be 256-byte aligned and activations 16-byte aligned");
     char* base = static_cast<char*>(ws);
-    uint16_t* dz2t = reinterpret_cast<uint16_t*>(base + w.dz2t);
-    uint16_t* dz1t = reinterpret_cast<uint16_t*>(base + w.dz1t);
     float* part = reinterpret_cast<float*>(base + w.part);
     const Act a = act_views(const_cast<void*>(act), n);
     hipStream_t s = (hipStream_t)stream;
-    const uint64_t tiles = n / 16;
-    uint64_t grid = (tiles + 3) / 4;
-    if (grid > 1024) grid = 1024;
-    hipLaunchKernelGGL(k_mlp_bwd_act, dim3((unsigned)grid), dim3(256), 0, s, params_bf16, n, a, dout, dz2t, dz1t);
-    hipLaunchKernelGGL(k_mlp_bwd_grad, dim3(kGradJobs, w.slices), dim3(64), 0, s, occ, n, a, dout, dz2t, dz1t, part);
-    hipLaunchKernelGGL(k_mlp_grad_reduce, dim3((kParams + 255) / 256), dim3(256), 0, s, part, w.slices, grad);
+    const int prm_wide = reinterpret_cast<uintptr_t>(params_bf16) % 16 == 0;
+    float* sums = w.slices == 1 ? grad : part;
+    hipLaunchKernelGGL(k_mlp_bwd, dim3((unsigned)w.slices), dim3(kBwdBlock), 0, s, params_bf16, prm_wide, occ, n,
+                       w.slice_len, a, dout, sums);
+    if (w.slices > 1)
+        hipLaunchKernelGGL(k_mlp_grad_reduce, dim3((kParams + 63) / 64), dim3(256), 0, s, part, w.slices, grad);
     PDZ_HIP(hipGetLastError());
     return ok();
 }
