@@ -289,37 +289,22 @@ __global__ void k_binit(BCtl* ctl, double* beta, int ld, uint32_t n) {
 
 // One block per cluster: lowest eigenpair of its T_k, convergence test, step
 // counter.  Row p of svec receives the eigenvector.
-__global__ __launch_bounds__(kRed) void k_btridiag(BCtl* ctl, const double* alpha, const double* beta, double* svec,
+__global__ __launch_bounds__(kTriBlock) void k_btridiag(BCtl* ctl, const double* alpha, const double* beta, double* svec,
                                                    int ld, double tol, int max_iter, uint32_t* err) {
     const uint32_t p = blockIdx.x;
     BCtl* st = ctl + p;
     if (st->done) return;
-    __shared__ double a[kBatchMaxIter];
-    __shared__ double e[kBatchMaxIter];
-    __shared__ double zs[kBatchMaxIter];
-    __shared__ double rp[kBatchMaxIter];
-    __shared__ double lo_s[kRed], hi_s[kRed];
-    __shared__ int found;
-    __shared__ double bounds[2];
+    __shared__ TriShared<kBatchMaxIter> S;
     const int k = st->k + 1;
-    const double* al = alpha + (size_t)p * ld;
     const double* be = beta + (size_t)p * ld;
-    for (int i = threadIdx.x; i < k; i += blockDim.x) {
-        a[i] = al[i];
-        e[i] = (i == 0) ? 0.0 : be[i];
-    }
-    __syncthreads();
     double hint_lo = 0.0, hint_hi = 0.0;
     if (k >= 3) ritz_hint(st->theta, st->theta_prev, &hint_lo, &hint_hi);
-    tridiag_bracket_min(a, e, k, lo_s, hi_s, &found, bounds, hint_lo, hint_hi);
-    if (threadIdx.x == 0) tridiag_min_vector(a, e, k, bounds[0], zs, rp);
-    __syncthreads();
+    const double theta = tridiag_min_pair(S, alpha + (size_t)p * ld, be, k, hint_lo, hint_hi);
     double* z = svec + (size_t)p * ld;
-    for (int i = threadIdx.x; i < k; i += blockDim.x) z[i] = zs[i];
+    for (int i = threadIdx.x; i < k; i += blockDim.x) z[i] = S.z[i];
     if (threadIdx.x == 0) {
-        const double theta = 0.5 * (bounds[0] + bounds[1]);
         const double bk1 = be[k];
-        const double resid = fabs(bk1 * zs[k - 1]);
+        const double resid = fabs(bk1 * S.z[k - 1]);
         st->theta_prev = st->theta;
         st->theta = theta;
         st->resid = resid;
@@ -650,7 +635,7 @@ pdz_status batch_lanczos_run(pdz_batch_s* b, const pdz_lanczos_opts* o, char* ws
         hipLaunchKernelGGL(k_bupdate<T>, nch, blk, 0, s, b->d_chunks, b->d_probs, ctl, alpha, beta, ld, w, v, vp,
                            partial);
         hipLaunchKernelGGL(k_bfinal, np, blk, 0, s, b->d_chunk_begin, partial, ctl, alpha, beta, ld, 1, err);
-        hipLaunchKernelGGL(k_btridiag, np, blk, 0, s, ctl, alpha, beta, svec, ld, o->tol, o->max_iter, err);
+        hipLaunchKernelGGL(k_btridiag, np, dim3(kTriBlock), 0, s, ctl, alpha, beta, svec, ld, o->tol, o->max_iter, err);
         hipLaunchKernelGGL(k_bscale<T>, nch, blk, 0, s, b->d_chunks, b->d_probs, ctl, beta, ld, 0, 0, w);
         PDZ_HIP(hipGetLastError());
         return ok();

@@ -202,6 +202,18 @@ __device__ __forceinline__ T update_one(T wi, T zi, T qi, T qpi, double a, doubl
 // elements in a fixed order.
 constexpr int kUpdBlock = 512;   // 32 waves per CU at kRedGrid work groups: more loads in flight
 
+// Partial sums of q_k . H q_k of which every work group of the update forms
+// alpha_k itself (p1 = NULL: alpha[k] is read).  Up to kAlphaInUpdate of them:
+// four loads a thread, against a launch of 4.7 us for one work group.
+constexpr uint64_t kAlphaInUpdate = 2048;
+struct AlphaSums {
+    const double* p1 = nullptr;
+    const double* p2 = nullptr;
+    int n1 = 0, n2 = 0;
+    double* alpha = nullptr;
+    uint32_t* err = nullptr;
+};
+
 // Sum over a work group of BLOCK threads (fixed order), valid in thread 0.
 template <int BLOCK>
 __device__ __forceinline__ double block_sum_waves(double v) {
@@ -216,6 +228,29 @@ __device__ __forceinline__ double block_sum_waves(double v) {
     return t;
 }
 
+// Sum over a work group of BLOCK threads (fixed order), valid in every thread.
+template <int BLOCK>
+__device__ __forceinline__ double block_sum_all(double v) {
+    __shared__ double ws[BLOCK / 64];
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1) v += __shfl_xor(v, m);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = v;
+    __syncthreads();
+    double t = ws[0];
+    for (int i = 1; i < BLOCK / 64; ++i) t += ws[i];
+    return t;
+}
+
+// Whole work group: sum of p1[0..n1) and p2[0..n2).
+template <int BLOCK>
+__device__ __forceinline__ double sum_two(const double* p1, int n1, const double* p2, int n2) {
+    double acc = 0.0;
+    for (int i = threadIdx.x; i < n1; i += BLOCK) acc += p1[i];
+    for (int i = threadIdx.x; i < n2; i += BLOCK) acc += p2[i];
+    return block_sum_all<BLOCK>(acc);
+}
+
 // KEEP: the new vector is also stored as slot k + 1 of the kept basis (slots
 // of keep_ld elements, keep_cap of them), the copy the refinement combines.
 template <typename T, bool HZ, bool KEEP>
@@ -224,11 +259,21 @@ __global__ __launch_bounds__(kUpdBlock) void k_update_scaled(T* __restrict__ w, 
                                                              uint64_t D, const double* alpha, const double* beta,
                                                              const double* sc, const int* kidx, double* partial,
                                                              const int* skip, int vec, T* __restrict__ keep,
-                                                             uint64_t keep_ld, int keep_cap) {
+                                                             uint64_t keep_ld, int keep_cap, const AlphaSums as) {
     if (skip && *skip) return;
     const int k = *kidx;
     const double a = sc[k];
-    const double b = alpha[k] * sc[k];
+    double ak;
+    if (as.p1) {
+        ak = a * a * sum_two<kUpdBlock>(as.p1, as.n1, as.p2, as.n2);
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            as.alpha[k] = ak;
+            if (!isfinite(ak)) atomicOr(as.err, kErrNonFinite);
+        }
+    } else {
+        ak = alpha[k];
+    }
+    const double b = ak * a;
     const double c = k > 0 ? beta[k] * sc[k - 1] : 0.0;
     const uint64_t tid = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
@@ -289,27 +334,29 @@ __global__ __launch_bounds__(kUpdBlock) void k_update_scaled(T* __restrict__ w, 
 template <typename T, bool KEEP>
 void launch_update_scaled_k(T* w, const T* z, const T* q, const T* qp, uint64_t D, const double* alpha,
                             const double* beta, const double* sc, const int* kidx, double* partial, const int* skip,
-                            hipStream_t s, int vec, T* keep, uint64_t keep_ld, int keep_cap) {
+                            hipStream_t s, int vec, T* keep, uint64_t keep_ld, int keep_cap, const AlphaSums& as) {
     if (z)
         hipLaunchKernelGGL((k_update_scaled<T, true, KEEP>), dim3(kRedGrid), dim3(kUpdBlock), 0, s, w, z, q, qp, D,
-                           alpha, beta, sc, kidx, partial, skip, vec, keep, keep_ld, keep_cap);
+                           alpha, beta, sc, kidx, partial, skip, vec, keep, keep_ld, keep_cap, as);
     else
         hipLaunchKernelGGL((k_update_scaled<T, false, KEEP>), dim3(kRedGrid), dim3(kUpdBlock), 0, s, w, z, q, qp, D,
-                           alpha, beta, sc, kidx, partial, skip, vec, keep, keep_ld, keep_cap);
+                           alpha, beta, sc, kidx, partial, skip, vec, keep, keep_ld, keep_cap, as);
 }
 
 // keep: NULL, or the kept basis (keep_cap slots of keep_ld elements)
 template <typename T>
 void launch_update_scaled(T* w, const T* z, const T* q, const T* qp, uint64_t D, const double* alpha,
                           const double* beta, const double* sc, const int* kidx, double* partial, const int* skip,
-                          hipStream_t s, T* keep = nullptr, uint64_t keep_ld = 0, int keep_cap = 0) {
+                          hipStream_t s, T* keep = nullptr, uint64_t keep_ld = 0, int keep_cap = 0,
+                          const AlphaSums& as = AlphaSums()) {
     auto al = [](const void* x) { return ((uintptr_t)x & 15) == 0; };
     const int vec = al(w) && al(q) && al(qp) && (!z || al(z)) && (!keep || (al(keep) && keep_ld % 4 == 0));
     if (keep)
         launch_update_scaled_k<T, true>(w, z, q, qp, D, alpha, beta, sc, kidx, partial, skip, s, vec, keep, keep_ld,
-                                        keep_cap);
+                                        keep_cap, as);
     else
-        launch_update_scaled_k<T, false>(w, z, q, qp, D, alpha, beta, sc, kidx, partial, skip, s, vec, nullptr, 0, 0);
+        launch_update_scaled_k<T, false>(w, z, q, qp, D, alpha, beta, sc, kidx, partial, skip, s, vec, nullptr, 0, 0,
+                                         as);
 }
 
 // y = sum_{j < m} (s_j sc_j) Q_j over kept unnormalised vectors, in j order
@@ -328,15 +375,13 @@ __global__ __launch_bounds__(kRedBlock) void k_combine_kept(double* __restrict__
 
 // alpha[k] = sc[k]^2 * (sum(p1[0..n1)) + sum(p2[0..n2))): <v_k, H v_k> from
 // partial sums of q_k . H q_k.
-__global__ __launch_bounds__(kRedBlock) void k_finalize_alpha(const double* p1, int n1, const double* p2, int n2,
-                                                              double* alpha, const double* sc, const int* kidx,
-                                                              const int* skip, uint32_t* err) {
+constexpr int kAlphaBlock = 1024;
+constexpr uint64_t kAlphaOne = 16384;   // partial sums one work group adds; more go through k_sum_strided first
+__global__ __launch_bounds__(kAlphaBlock) void k_finalize_alpha(const double* p1, int n1, const double* p2, int n2,
+                                                                double* alpha, const double* sc, const int* kidx,
+                                                                const int* skip, uint32_t* err) {
     if (skip && *skip) return;
-    __shared__ double red[kRedBlock];
-    double acc = 0.0;
-    for (int i = threadIdx.x; i < n1; i += blockDim.x) acc += p1[i];
-    for (int i = threadIdx.x; i < n2; i += blockDim.x) acc += p2[i];
-    acc = block_sum(acc, red);
+    const double acc = sum_two<kAlphaBlock>(p1, n1, p2, n2);
     if (threadIdx.x == 0) {
         const int k = *kidx;
         const double v = sc[k] * sc[k] * acc;
@@ -355,11 +400,6 @@ __global__ __launch_bounds__(kRedBlock) void k_sum_strided(const double* in, uin
         acc += in[i];
     acc = block_sum(acc, red);
     if (threadIdx.x == 0) out[blockIdx.x] = acc;
-}
-
-// sc[k] = 1 / beta[k] for the step counter k just advanced by k_tridiag.
-__global__ void k_next_scale(const double* beta, double* sc, const Ctl* ctl) {
-    if (threadIdx.x == 0 && blockIdx.x == 0 && !ctl->done) sc[ctl->k] = 1.0 / beta[ctl->k];
 }
 
 // sc[0] = 1 / norm0
@@ -441,36 +481,29 @@ __global__ __launch_bounds__(kRedBlock) void k_resid_partial(const double* __res
     if (threadIdx.x == 0) partial[blockIdx.x] = acc;
 }
 
-// One block: theta = lambda_min(T_k), s = its normalised eigenvector, the
-// convergence test, and the step counter.  alpha[0..k-1] is the diagonal,
-// beta[1..k-1] the off-diagonal, beta[k] = beta_{k+1}.
-__global__ __launch_bounds__(kRedBlock) void k_tridiag(const double* alpha, const double* beta, double* s_out,
-                                                       double* theta_hist, Ctl* ctl, double tol, int max_iter,
-                                                       uint32_t* err) {
+// One block ends step k: beta_{k+1} = sqrt(sum of the n partials of |q_{k+1}|^2),
+// theta = lambda_min(T_k), s = its normalised eigenvector, the convergence
+// test, the step counter and (sc != NULL) the scale sc[k] = 1 / beta_{k+1} of
+// the next vector.  alpha[0..k-1] is the diagonal, beta[1..k-1] the
+// off-diagonal, beta[k] = beta_{k+1}.  One launch: as three (sum, solve,
+// scale) each of the two small ones cost 4.6 us of a step.
+__global__ __launch_bounds__(kTriBlock) void k_ritz(const double* partial, int n, const double* alpha, double* beta,
+                                                    double* sc, double* s_out, double* theta_hist, Ctl* ctl, double tol,
+                                                    int max_iter, uint32_t* err) {
     if (ctl->done) return;
-    __shared__ double a[kMaxIter];
-    __shared__ double e[kMaxIter];
-    __shared__ double zs[kMaxIter];
-    __shared__ double rp[kMaxIter];
-    __shared__ double lo_s[kRedBlock], hi_s[kRedBlock];
-    __shared__ int found;
-    __shared__ double bounds[2];
+    __shared__ TriShared<kMaxIter> S;
+    __shared__ double red[kRedBlock];
     const int k = ctl->k + 1;
-    for (int i = threadIdx.x; i < k; i += blockDim.x) {
-        a[i] = alpha[i];
-        e[i] = (i == 0) ? 0.0 : beta[i];
-    }
-    __syncthreads();
+    double acc = 0.0;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) acc += partial[i];
+    const double bk1 = sqrt(block_sum(acc, red));
     double hint_lo = 0.0, hint_hi = 0.0;
     if (k >= 3) ritz_hint(theta_hist[k - 2], theta_hist[k - 3], &hint_lo, &hint_hi);
-    tridiag_bracket_min(a, e, k, lo_s, hi_s, &found, bounds, hint_lo, hint_hi);
-    if (threadIdx.x == 0) tridiag_min_vector(a, e, k, bounds[0], zs, rp);
-    __syncthreads();
-    for (int i = threadIdx.x; i < k; i += blockDim.x) s_out[i] = zs[i];
+    const double theta = tridiag_min_pair(S, alpha, beta, k, hint_lo, hint_hi);
+    for (int i = threadIdx.x; i < k; i += blockDim.x) s_out[i] = S.z[i];
     if (threadIdx.x == 0) {
-        const double theta = 0.5 * (bounds[0] + bounds[1]);
-        const double bk1 = beta[k];
-        const double resid = fabs(bk1 * zs[k - 1]);
+        const double resid = fabs(bk1 * S.z[k - 1]);
+        beta[k] = bk1;
         theta_hist[k - 1] = theta;
         ctl->theta = theta;
         ctl->resid = resid;
@@ -478,16 +511,20 @@ __global__ __launch_bounds__(kRedBlock) void k_tridiag(const double* alpha, cons
         const double scale = fmax(fabs(theta), 1e-300);
         const bool breakdown = !(bk1 > 1e-14 * fmax(1.0, fabs(theta)));
         const bool conv = breakdown || resid <= tol * scale;
+        bool done = k >= max_iter;
         if (!isfinite(theta) || !isfinite(bk1)) {
             atomicOr(err, kErrNonFinite);
-            ctl->done = 1;
+            done = true;
         }
         if (conv) {
             ctl->converged = 1;
             ctl->breakdown = breakdown ? 1 : 0;
-            ctl->done = 1;
+            done = true;
         }
-        if (k >= max_iter) ctl->done = 1;
+        if (done)
+            ctl->done = 1;
+        else if (sc)
+            sc[k] = 1.0 / bk1;
     }
 }
 
@@ -764,6 +801,23 @@ struct Run {
         return c;
     }
 
+    // beta_{k+1} from its partial sums, the Ritz pair of T_k, the next scale.
+    void end_step(const double* norms, int n, double* scale) {
+        hipLaunchKernelGGL(k_ritz, dim3(1), dim3(kTriBlock), 0, s, norms, n, alpha(), beta(), scale, svec(), theta(),
+                           ctl(), o->tol, o->max_iter, err);
+    }
+
+    // alpha_k from the partial sums p1[0..n1) and p2[0..n2) of q . H q.
+    void end_alpha(const double* p1, int n1, const double* p2, uint64_t n2) {
+        if ((uint64_t)n1 + n2 > kAlphaOne) {
+            hipLaunchKernelGGL(k_sum_strided, dim3(kRedGrid), dim3(kRedBlock), 0, s, p2, n2, partial2(), done());
+            p2 = partial2();
+            n2 = kRedGrid;
+        }
+        hipLaunchKernelGGL(k_finalize_alpha, dim3(1), dim3(kAlphaBlock), 0, s, p1, n1, p2, (int)n2, alpha(), sc(),
+                           kptr(), done(), err);
+    }
+
     // One step of the three-term recurrence on unnormalised vectors (v_k =
     // sc[k] q_k): q = q_k, qp = q_{k-1}, w receives q_{k+1}.  H q_k comes in
     // two parts (w: diagonal + down hops, z: up hops) that the update adds;
@@ -771,6 +825,11 @@ struct Run {
     // passes of H.v, so no pass re-reads a D-sized vector for them.
     pdz_status step_scaled(T* q, T* qp, T* w, const SplitCounts& c) {
         mark(0);
+        double* norms = partial3();   // the update may still read the sums in partial()
+        AlphaSums as;
+        as.p1 = partial();
+        as.alpha = alpha();
+        as.err = err;
         if (c.ndn > 0) {
             HvSplit sd;   // down pass (no z: it would be cleared after a down-only launch)
             sd.dotp_dn = partial();
@@ -783,10 +842,9 @@ struct Run {
             st = launch_hv_any(p, (pdz_dtype)o->storage, q, w, s, done(), kPassUp, &su, pitch);
             if (st != PDZ_OK) return st;
             mark(2);
-            hipLaunchKernelGGL(k_sum_strided, dim3(kRedGrid), dim3(kRedBlock), 0, s, partial() + c.ndn,
-                               (uint64_t)c.nup, partial2(), done());
-            hipLaunchKernelGGL(k_finalize_alpha, dim3(1), dim3(kRedBlock), 0, s, partial(), c.ndn, partial2(),
-                               (int)kRedGrid, alpha(), sc(), kptr(), done(), err);
+            as.n1 = c.ndn;
+            as.p2 = partial() + c.ndn;
+            as.n2 = c.nup;
         } else if (c.nwhole > 0) {   // the H.v writes partial sums of q . H q
             HvSplit sw;
             sw.dotp_up = partial();
@@ -794,10 +852,7 @@ struct Run {
             if (st != PDZ_OK) return st;
             mark(1);
             mark(2);
-            hipLaunchKernelGGL(k_sum_strided, dim3(kRedGrid), dim3(kRedBlock), 0, s, partial(), (uint64_t)c.nwhole,
-                               partial2(), done());
-            hipLaunchKernelGGL(k_finalize_alpha, dim3(1), dim3(kRedBlock), 0, s, partial(), 0, partial2(),
-                               (int)kRedGrid, alpha(), sc(), kptr(), done(), err);
+            as.n1 = c.nwhole;
         } else {
             pdz_status st = launch_hv_any(p, (pdz_dtype)o->storage, q, w, s, done(), kPassDown | kPassUp, nullptr, pitch);
             if (st != PDZ_OK) return st;
@@ -805,18 +860,17 @@ struct Run {
             mark(2);
             hipLaunchKernelGGL((k_dot_partial<T, T>), dim3(kRedGrid), dim3(kRedBlock), 0, s, q, w, D, partial(),
                                done());
-            hipLaunchKernelGGL(k_finalize_alpha, dim3(1), dim3(kRedBlock), 0, s, partial(), (int)kRedGrid,
-                               (const double*)nullptr, 0, alpha(), sc(), kptr(), done(), err);
+            as.n1 = kRedGrid;
+        }
+        if ((uint64_t)as.n1 + as.n2 > kAlphaInUpdate) {
+            end_alpha(as.p1, as.n1, as.p2, as.n2);
+            as.p1 = nullptr;   // the update reads alpha[k]
         }
         mark(3);
         launch_update_scaled<T>(w, c.ndn > 0 ? (const T*)zbuf() : (const T*)nullptr, q, qp, D, alpha(), beta(), sc(),
-                                kptr(), partial(), done(), s, kept(0), ld(), L.nkept);
+                                kptr(), norms, done(), s, kept(0), ld(), L.nkept, as);
         mark(4);
-        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kRedBlock), 0, s, partial(), kRedGrid, beta(), kptr(), 1,
-                           (int)kStoreSqrt, done(), err);
-        hipLaunchKernelGGL(k_tridiag, dim3(1), dim3(kRedBlock), 0, s, alpha(), beta(), svec(), theta(), ctl(), o->tol,
-                           o->max_iter, err);
-        hipLaunchKernelGGL(k_next_scale, dim3(1), dim3(1), 0, s, beta(), sc(), ctl());
+        end_step(norms, kRedGrid, sc());
         mark(5);
         return launch_check();
     }
@@ -828,10 +882,7 @@ struct Run {
             sw.dotp_up = partial();
             pdz_status st = launch_hv_any(p, (pdz_dtype)o->storage, q, w, s, done(), kPassDown | kPassUp, &sw, pitch);
             if (st != PDZ_OK) return st;
-            hipLaunchKernelGGL(k_sum_strided, dim3(kRedGrid), dim3(kRedBlock), 0, s, partial(), (uint64_t)c.nwhole,
-                               partial2(), done());
-            hipLaunchKernelGGL(k_finalize_alpha, dim3(1), dim3(kRedBlock), 0, s, partial(), 0, partial2(),
-                               (int)kRedGrid, alpha(), sc(), kptr(), done(), err);
+            end_alpha(partial(), 0, partial(), c.nwhole);
             return launch_check();
         }
         HvSplit sp;
@@ -840,10 +891,7 @@ struct Run {
         sp.dotp_up = partial() + c.ndn;
         pdz_status st = launch_hv_any(p, (pdz_dtype)o->storage, q, w, s, done(), kPassDown | kPassUp, &sp, pitch);
         if (st != PDZ_OK) return st;
-        hipLaunchKernelGGL(k_sum_strided, dim3(kRedGrid), dim3(kRedBlock), 0, s, partial() + c.ndn, (uint64_t)c.nup,
-                           partial2(), done());
-        hipLaunchKernelGGL(k_finalize_alpha, dim3(1), dim3(kRedBlock), 0, s, partial(), c.ndn, partial2(),
-                           (int)kRedGrid, alpha(), sc(), kptr(), done(), err);
+        end_alpha(partial(), c.ndn, partial() + c.ndn, c.nup);
         return launch_check();
     }
 
@@ -872,11 +920,7 @@ struct Run {
         pdz_status st = launch_hv_any(p, (pdz_dtype)o->storage, q2, w, s, done(), kPassDown, &f, pitch);
         if (st != PDZ_OK) return st;
         mark(1);
-        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kRedBlock), 0, s, partial3(), c.ndn, beta(), kptr(), 1,
-                           (int)kStoreSqrt, done(), err);
-        hipLaunchKernelGGL(k_tridiag, dim3(1), dim3(kRedBlock), 0, s, alpha(), beta(), svec(), theta(), ctl(), o->tol,
-                           o->max_iter, err);
-        hipLaunchKernelGGL(k_next_scale, dim3(1), dim3(1), 0, s, beta(), sc(), ctl());
+        end_step(partial3(), c.ndn, sc());
         mark(2);
         HvSplit u;
         u.z = zbuf();
@@ -884,10 +928,7 @@ struct Run {
         st = launch_hv_any(p, (pdz_dtype)o->storage, q2, w, s, done(), kPassUp, &u, pitch);
         if (st != PDZ_OK) return st;
         mark(3);
-        hipLaunchKernelGGL(k_sum_strided, dim3(kRedGrid), dim3(kRedBlock), 0, s, partial() + c.ndn, (uint64_t)c.nup,
-                           partial2(), done());
-        hipLaunchKernelGGL(k_finalize_alpha, dim3(1), dim3(kRedBlock), 0, s, partial(), c.ndn, partial2(),
-                           (int)kRedGrid, alpha(), sc(), kptr(), done(), err);
+        end_alpha(partial(), c.ndn, partial() + c.ndn, c.nup);
         mark(4);
         mark(5);
         return launch_check();
@@ -915,21 +956,14 @@ struct Run {
         pdz_status st = launch_hv_any(p, dt, q2, w, s, done(), kPassDown, &f);
         if (st != PDZ_OK) return st;
         mark(1);
-        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kRedBlock), 0, s, partial3(), parity_fused_norms(p, dt), beta(),
-                           kptr(), 1, (int)kStoreSqrt, done(), err);
-        hipLaunchKernelGGL(k_tridiag, dim3(1), dim3(kRedBlock), 0, s, alpha(), beta(), svec(), theta(), ctl(), o->tol,
-                           o->max_iter, err);
-        hipLaunchKernelGGL(k_next_scale, dim3(1), dim3(1), 0, s, beta(), sc(), ctl());
+        end_step(partial3(), parity_fused_norms(p, dt), sc());
         mark(2);
         HvSplit u;
         u.dotp_up = partial();
         st = launch_hv_any(p, dt, q2, w, s, done(), kPassUp, &u);
         if (st != PDZ_OK) return st;
         mark(3);
-        hipLaunchKernelGGL(k_sum_strided, dim3(kRedGrid), dim3(kRedBlock), 0, s, partial(), (uint64_t)c.nwhole,
-                           partial2(), done());
-        hipLaunchKernelGGL(k_finalize_alpha, dim3(1), dim3(kRedBlock), 0, s, partial(), 0, partial2(), (int)kRedGrid,
-                           alpha(), sc(), kptr(), done(), err);
+        end_alpha(partial(), 0, partial(), c.nwhole);
         mark(4);
         mark(5);
         return launch_check();
@@ -1015,10 +1049,7 @@ struct Run {
             }
             hipLaunchKernelGGL((k_dot_partial<T, T>), dim3(kRedGrid), dim3(kRedBlock), 0, s, w, w, D, partial(), done());
         }
-        hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kRedBlock), 0, s, partial(), kRedGrid, beta(), kptr(), 1,
-                           (int)kStoreSqrt, done(), err);
-        hipLaunchKernelGGL(k_tridiag, dim3(1), dim3(kRedBlock), 0, s, alpha(), beta(), svec(), theta(), ctl(), o->tol,
-                           o->max_iter, err);
+        end_step(partial(), kRedGrid, nullptr);
         hipLaunchKernelGGL(k_scale<T>, dim3(g), dim3(kRedBlock), 0, s, w, D, beta(), kptr(), 0, done());
         return launch_check();
     }

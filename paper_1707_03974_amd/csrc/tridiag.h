@@ -1,140 +1,260 @@
 // Lowest eigenpair of the Lanczos tridiagonal T_k (FP64), shared by the
-// single-problem and the batched Lanczos kernels.
+// single-problem and the batched Lanczos kernels; one work group of kTriBlock
+// threads per matrix.
 //
 // T_k has diagonal a[0..k-1] and off-diagonal e[1..k-1] (e[0] = 0).  Its
-// lowest eigenvalue comes from Sturm-count multisection over the Gershgorin
-// interval: each round splits the bracket into blockDim + 1 pieces and keeps
-// the one where the count of eigenvalues below the point first reaches one.
-// The eigenvector comes from inverse iteration with a shift just below the
-// bracket, so T_k - sigma I is positive definite and its LDL^T factorisation
-// needs no pivoting.
+// lowest eigenvalue comes from multisection: each round evaluates T_k - x I at
+// kTriBlock points of the bracket and keeps the piece in which it stops being
+// positive definite.  The test at one point is the three-term recurrence of
+// the leading principal minors,
+//     p_i = (a_i - x) p_{i-1} - e_i^2 p_{i-2}
+// (x lies above the lowest eigenvalue exactly when some p_i < 0), with the
+// pair (p_{i-1}, p_i) rescaled by a power of two every kTriBatch steps: one
+// multiply-add on the serial chain per step.  The pivots q_i = p_i / p_{i-1}
+// obey q_i = (a_i - x) - e_i^2 / q_{i-1}, nine dependent operations a step
+// with a refined hardware reciprocal; with them a solve took 40 us on average
+// over k = 1..100.
+//
+// The eigenvector comes from three steps of inverse iteration with a shift
+// just below the bracket, so T_k - sigma I is positive definite and its
+// LDL^T factorisation needs no pivoting; its pivots are ratios of the same
+// minors, divided by all threads at once.
 #pragma once
 
 #include <hip/hip_runtime.h>
 
 namespace pdz {
 
-// 1/q in FP64 from the hardware reciprocal estimate and two steps of Newton's
-// iteration r <- r + r (1 - q r), each of which doubles the number of correct
-// bits; a few fused operations in place of a division on the serial chains
-// below (q finite, |q| >= 1e-300: the callers lift smaller pivots to 1e-300).
-__device__ inline double tridiag_recip(double q) {
-    double r = __builtin_amdgcn_rcp(q);
-    double t = fma(-q, r, 1.0);
-    r = fma(r, t, r);
-    t = fma(-q, r, 1.0);
-    return fma(r, t, r);
-}
-
-// Operands read ahead of the serial steps below: the LDS reads of a batch are
-// issued together, so one wait covers them, and the steps then run on
-// registers (the arithmetic and its order are those of the plain loops).
+constexpr int kTriBlock = 256;
 constexpr int kTriBatch = 8;
 
-// Number of eigenvalues of T below x (signs of the LDL^T pivots of T - x I).
-__device__ inline int tridiag_sturm_count(const double* a, const double* e, int k, double x) {
-    int cnt = 0;
-    double q = a[0] - x;
-    if (q < 0.0) ++cnt;
-    auto step = [&](double am, double e2) {
-        if (fabs(q) < 1e-300) q = q < 0.0 ? -1e-300 : 1e-300;   // the sign is counted already
-        q = am - e2 * tridiag_recip(q);
-        if (q < 0.0) ++cnt;
+// LDS of one solve of order at most N.
+template <int N>
+struct TriShared {
+    double2 ae[N];       // scaled a_i and e_i^2
+    double e[N + 1];     // scaled e_i (e[k] = 0)
+    double2 pp[N];       // (p_{i-1}, p_i) at the shift, then (e_i / pivot_{i-1}, 1 / pivot_i)
+    double z[N];         // eigenvector
+    double red[kTriBlock / 64], red2[kTriBlock / 64];
+    int first[2][kTriBlock / 64];
+    double nrm;
+};
+
+// Minors of T - x I from i = 1 on: calls f(i, p_{i-1}, p_i); both values of a
+// call carry the same scale.  Operands are read a batch ahead of their use.
+template <typename F>
+__device__ __forceinline__ void tri_minors(const double2* ae, int k, double x, F&& f) {
+    double p2 = 1.0, p1 = ae[0].x - x;
+    f(0, p2, p1);
+    auto step = [&](int i, double2 q) {
+        const double p = fma(q.x - x, p1, -(q.y * p2));
+        p2 = p1;
+        p1 = p;
+        f(i, p2, p1);
     };
     int i = 1;
-    for (; i + kTriBatch <= k; i += kTriBatch) {
-        double am[kTriBatch], e2[kTriBatch];
+    double2 cur[kTriBatch];
+    if (i + kTriBatch <= k)
 #pragma unroll
-        for (int j = 0; j < kTriBatch; ++j) {
-            am[j] = a[i + j] - x;
-            e2[j] = e[i + j] * e[i + j];
-        }
+        for (int j = 0; j < kTriBatch; ++j) cur[j] = ae[i + j];
+    while (i + kTriBatch <= k) {
+        const int n = i + kTriBatch;
+        double2 nxt[kTriBatch];
+        if (n + kTriBatch <= k)
 #pragma unroll
-        for (int j = 0; j < kTriBatch; ++j) step(am[j], e2[j]);
+            for (int j = 0; j < kTriBatch; ++j) nxt[j] = ae[n + j];
+#pragma unroll
+        for (int j = 0; j < kTriBatch; ++j) step(i + j, cur[j]);
+        const int ex = -__builtin_amdgcn_frexp_exp(fmax(fabs(p1), fabs(p2)));
+        p1 = __builtin_amdgcn_ldexp(p1, ex);
+        p2 = __builtin_amdgcn_ldexp(p2, ex);
+#pragma unroll
+        for (int j = 0; j < kTriBatch; ++j) cur[j] = nxt[j];
+        i = n;
     }
-    for (; i < k; ++i) step(a[i] - x, e[i] * e[i]);
-    return cnt;
+    for (; i < k; ++i) step(i, ae[i]);
 }
 
-// Whole work group: shrink [bounds[0], bounds[1]], which holds lambda_min,
-// by splitting it into blockDim + 1 pieces per round.
-__device__ inline void tridiag_multisect(const double* a, const double* e, int k, int* found, double* bounds) {
-    double lo, hi;
-    for (int round = 0; round < 64; ++round) {
-        lo = bounds[0];
-        hi = bounds[1];
-        if (!(hi - lo > 2.0 * 2.220446049250313e-16 * fmax(fabs(lo), fabs(hi)) + 1e-300)) break;
-        const double x = lo + (hi - lo) * (double)(threadIdx.x + 1) / (double)(blockDim.x + 1);
-        if (threadIdx.x == 0) *found = blockDim.x;
-        __syncthreads();
-        if (tridiag_sturm_count(a, e, k, x) >= 1) atomicMin(found, (int)threadIdx.x);
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            const int t = *found;
-            const double nlo = (t == 0) ? lo : lo + (hi - lo) * (double)t / (double)(blockDim.x + 1);
-            const double nhi = (t == (int)blockDim.x) ? hi : lo + (hi - lo) * (double)(t + 1) / (double)(blockDim.x + 1);
-            bounds[0] = nlo;
-            bounds[1] = nhi;
-        }
-        __syncthreads();
-    }
+// Whether T - x I has a negative eigenvalue.
+__device__ __forceinline__ bool tri_below(const double2* ae, int k, double x) {
+    bool neg = false;
+    tri_minors(ae, k, x, [&](int, double, double p) { neg = neg || p < 0.0; });
+    return neg;
 }
 
-// Whole work group: bracket [bounds[0], bounds[1]] of lambda_min(T_k) to a
-// few ulps.  a, e in LDS; lo_s, hi_s: blockDim doubles of LDS; found, bounds
-// in LDS.  Every thread must call it; bounds is valid for all on return.
-// A hint [hint_lo, hint_hi] (hint_lo < hint_hi) replaces the Gershgorin
-// interval when two Sturm counts confirm that it holds exactly the lowest
-// eigenvalue's side: none below hint_lo, at least one below hint_hi.  In
+// Index of the first thread of the group for which b holds (kTriBlock: none);
+// `round` alternates the LDS slot, so one barrier per call is enough.
+template <int N>
+__device__ __forceinline__ int tri_first(TriShared<N>& S, bool b, int round) {
+    const unsigned long long m = __ballot(b);
+    const int wave = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) S.first[round & 1][wave] = m ? 64 * wave + __ffsll(m) - 1 : kTriBlock;
+    __syncthreads();
+    int t = kTriBlock;
+    for (int w = 0; w < kTriBlock / 64; ++w) t = min(t, S.first[round & 1][w]);
+    return t;
+}
+
+// Whole work group: the lowest eigenpair.  alpha[0..k-1], beta[1..k-1] in
+// global memory; returns theta to every thread, the normalised eigenvector in
+// S.z.  A hint [hint_lo, hint_hi] (hint_lo < hint_hi) replaces the Gershgorin
+// interval when its ends test as below and above the lowest eigenvalue.  In
 // Lanczos the previous Ritz value bounds the new one from above (Cauchy
 // interlacing), and the last change estimates how far it moves.
-__device__ inline void tridiag_bracket_min(const double* a, const double* e, int k, double* lo_s, double* hi_s,
-                                           int* found, double* bounds, double hint_lo = 0.0,
-                                           double hint_hi = 0.0) {
-    if (hint_lo < hint_hi) {
-        if (threadIdx.x == 0) *found = 0;
-        __syncthreads();
-        if (threadIdx.x < 2) {
-            const int c = tridiag_sturm_count(a, e, k, threadIdx.x == 0 ? hint_lo : hint_hi);
-            const bool good = threadIdx.x == 0 ? (c == 0) : (c >= 1);
-            if (good) atomicAdd(found, 1);
+template <int N>
+__device__ double tridiag_min_pair(TriShared<N>& S, const double* alpha, const double* beta, int k, double hint_lo,
+                                   double hint_hi) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // ---- scale by a power of two so that no entry exceeds one
+    double mx = 0.0;
+    for (int i = tid; i < k; i += kTriBlock) {
+        const double a = alpha[i], e = i == 0 ? 0.0 : beta[i];
+        S.ae[i].x = a;
+        S.e[i] = e;
+        mx = fmax(mx, fmax(fabs(a), fabs(e)));
+    }
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1) mx = fmax(mx, __shfl_xor(mx, m));
+    if (lane == 0) S.red[wave] = mx;
+    __syncthreads();
+    for (int w = 0; w < kTriBlock / 64; ++w) mx = fmax(mx, S.red[w]);
+    const int ex = mx > 0.0 && mx < 1e308 ? __builtin_amdgcn_frexp_exp(mx) : 0;
+    for (int i = tid; i < k; i += kTriBlock) {
+        const double e = __builtin_amdgcn_ldexp(S.e[i], -ex);
+        S.e[i] = e;
+        S.ae[i] = double2{__builtin_amdgcn_ldexp(S.ae[i].x, -ex), e * e};
+    }
+    if (tid == 0) S.e[k] = 0.0;
+    __syncthreads();
+    // ---- bracket
+    double lo = __builtin_amdgcn_ldexp(hint_lo, -ex), hi = __builtin_amdgcn_ldexp(hint_hi, -ex);
+    int round = 0;
+    bool have = false;
+    if (lo < hi) {
+        const double w = (hi - lo) / (double)(kTriBlock - 1);
+        auto point = [&](int t) { return t == kTriBlock - 1 ? hi : lo + w * (double)t; };
+        const int t = tri_first(S, tri_below(S.ae, k, point(tid)), round++);
+        have = t > 0 && t < kTriBlock;
+        if (have) {
+            const double l = point(t - 1), h = point(t);
+            lo = l;
+            hi = h;
+        }
+    }
+    if (!have) {
+        double l = 1e300, h = -1e300;
+        for (int i = tid; i < k; i += kTriBlock) {
+            const double r = fabs(S.e[i]) + fabs(S.e[i + 1]);
+            l = fmin(l, S.ae[i].x - r);
+            h = fmax(h, S.ae[i].x + r);
+        }
+#pragma unroll
+        for (int m = 32; m > 0; m >>= 1) {
+            l = fmin(l, __shfl_xor(l, m));
+            h = fmax(h, __shfl_xor(h, m));
         }
         __syncthreads();
-        const bool use = *found == 2;
+        if (lane == 0) {
+            S.red[wave] = l;
+            S.red2[wave] = h;
+        }
         __syncthreads();
-        if (use) {
-            if (threadIdx.x == 0) {
-                bounds[0] = hint_lo;
-                bounds[1] = hint_hi;
+        for (int w = 0; w < kTriBlock / 64; ++w) {
+            l = fmin(l, S.red[w]);
+            h = fmax(h, S.red2[w]);
+        }
+        const double pad = 1e-12 * fmax(__builtin_amdgcn_ldexp(1.0, -ex), fmax(fabs(l), fabs(h)));
+        lo = l - pad;
+        hi = h + pad;
+    }
+    for (int r = 0; r < 64; ++r) {
+        if (!(hi - lo > 2.0 * 2.220446049250313e-16 * fmax(fabs(lo), fabs(hi)) + 1e-300)) break;
+        const double w = (hi - lo) / (double)(kTriBlock + 1);
+        const int t = tri_first(S, tri_below(S.ae, k, lo + w * (double)(tid + 1)), round++);
+        const double l = t == 0 ? lo : lo + w * (double)t;
+        const double h = t == kTriBlock ? hi : lo + w * (double)(t + 1);
+        lo = l;
+        hi = h;
+    }
+    // ---- eigenvector: T - sigma I = L D L^T, sigma just below the bracket
+    const double sigma = lo - 4.0 * 2.220446049250313e-16 * fmax(__builtin_amdgcn_ldexp(1.0, -ex), fabs(lo));
+    if (tid == 0) tri_minors(S.ae, k, sigma, [&](int i, double p2, double p1) { S.pp[i] = double2{p2, p1}; });
+    __syncthreads();
+    // reciprocal pivots r_i, then the sweep factors: forward m_i = e_i r_{i-1}, backward r_i and r_i e_{i+1}
+    for (int i = tid; i < k; i += kTriBlock) {
+        double2 q = S.pp[i];
+        if (fabs(q.y) < 1e-300) q.y = q.y < 0.0 ? -1e-300 : 1e-300;
+        S.z[i] = q.x / q.y;
+    }
+    __syncthreads();
+    for (int i = tid; i < k; i += kTriBlock) S.pp[i] = double2{i > 0 ? S.e[i] * S.z[i - 1] : 0.0, S.z[i]};
+    __syncthreads();
+    if (tid == 0) {
+        constexpr int B = kTriBatch;
+        double scale = 1.0, nrm = 0.0;
+        for (int it = 0; it < 3; ++it) {
+            // L y = z (forward; the first z is all ones), then D L^T x = y (backward); x overwrites z
+            double c = 0.0;
+            int i = 0;
+            for (; i + B <= k; i += B) {
+                double zv[B], mv[B];
+#pragma unroll
+                for (int j = 0; j < B; ++j) {
+                    zv[j] = it == 0 ? 1.0 : S.z[i + j] * scale;
+                    mv[j] = S.pp[i + j].x;
+                }
+#pragma unroll
+                for (int j = 0; j < B; ++j) {
+                    c = fma(-mv[j], c, zv[j]);
+                    zv[j] = c;
+                }
+#pragma unroll
+                for (int j = 0; j < B; ++j) S.z[i + j] = zv[j];
             }
-            __syncthreads();
-            tridiag_multisect(a, e, k, found, bounds);
-            return;
+            for (; i < k; ++i) {
+                c = fma(-S.pp[i].x, c, it == 0 ? 1.0 : S.z[i] * scale);
+                S.z[i] = c;
+            }
+            c = 0.0;
+            nrm = 0.0;
+            i = k - 1;
+            for (; i - B + 1 >= 0; i -= B) {   // i, i - 1, ..., i - B + 1
+                double yv[B], ev[B];
+#pragma unroll
+                for (int j = 0; j < B; ++j) {
+                    const double rv = S.pp[i - j].y;
+                    yv[j] = rv * S.z[i - j];
+                    ev[j] = rv * S.e[i - j + 1];
+                }
+#pragma unroll
+                for (int j = 0; j < B; ++j) {
+                    c = fma(-ev[j], c, yv[j]);
+                    yv[j] = c;
+                    nrm = fma(c, c, nrm);
+                }
+#pragma unroll
+                for (int j = 0; j < B; ++j) S.z[i - j] = yv[j];
+            }
+            for (; i >= 0; --i) {
+                const double rv = S.pp[i].y;
+                c = fma(-(rv * S.e[i + 1]), c, rv * S.z[i]);
+                S.z[i] = c;
+                nrm = fma(c, c, nrm);
+            }
+            nrm = sqrt(nrm);
+            if (!(nrm > 0.0) || !isfinite(nrm)) {
+                nrm = 1.0;
+                break;
+            }
+            scale = 1.0 / nrm;
         }
-    }
-    double lo = 1e300, hi = -1e300;
-    for (int i = threadIdx.x; i < k; i += blockDim.x) {
-        const double r = fabs(e[i]) + (i + 1 < k ? fabs(e[i + 1]) : 0.0);
-        lo = fmin(lo, a[i] - r);
-        hi = fmax(hi, a[i] + r);
-    }
-    lo_s[threadIdx.x] = lo;
-    hi_s[threadIdx.x] = hi;
-    __syncthreads();
-    for (int st = blockDim.x / 2; st > 0; st >>= 1) {
-        if (threadIdx.x < st) {
-            lo_s[threadIdx.x] = fmin(lo_s[threadIdx.x], lo_s[threadIdx.x + st]);
-            hi_s[threadIdx.x] = fmax(hi_s[threadIdx.x], hi_s[threadIdx.x + st]);
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        const double pad = 1e-12 * fmax(1.0, fmax(fabs(lo_s[0]), fabs(hi_s[0])));
-        bounds[0] = lo_s[0] - pad;
-        bounds[1] = hi_s[0] + pad;
+        S.nrm = 1.0 / nrm;
     }
     __syncthreads();
-    tridiag_multisect(a, e, k, found, bounds);
+    const double inv = S.nrm;
+    for (int i = tid; i < k; i += kTriBlock) S.z[i] *= inv;
+    __syncthreads();
+    return __builtin_amdgcn_ldexp(0.5 * (lo + hi), ex);
 }
 
 // Bracket hint for lambda_min(T_k) from the Ritz values of the two previous
@@ -146,103 +266,6 @@ __device__ inline void ritz_hint(double theta1, double theta2, double* lo, doubl
     const double w = fmax(8.0 * fabs(theta1 - theta2), 1e-12 * scale);
     *hi = theta1 + 8.0 * 2.220446049250313e-16 * scale;
     *lo = theta1 - w;
-}
-
-// One thread: normalised eigenvector z[0..k-1] for the eigenvalue bracketed
-// below by `lower`.  T - sigma I = L D L^T is factored once (reciprocal
-// pivots in rp), then three steps of inverse iteration reuse it.  a, e, z, rp
-// should live in LDS: the sweeps are serial recurrences, so only the carried
-// value stays on the critical path.
-__device__ inline void tridiag_min_vector(const double* a, const double* e, int k, double lower, double* z,
-                                          double* rp) {
-    constexpr int B = kTriBatch;
-    const double sigma = lower - 4.0 * 2.220446049250313e-16 * fmax(1.0, fabs(lower));
-    double d = a[0] - sigma;
-    if (fabs(d) < 1e-300) d = d < 0.0 ? -1e-300 : 1e-300;
-    double r = tridiag_recip(d);
-    rp[0] = r;
-    z[0] = 1.0;
-    auto pivot = [&](double am, double ei) {
-        d = am - (ei * r) * ei;
-        if (fabs(d) < 1e-300) d = d < 0.0 ? -1e-300 : 1e-300;
-        r = tridiag_recip(d);
-        return r;
-    };
-    int i = 1;
-    for (; i + B <= k; i += B) {
-        double am[B], ev[B], rv[B];
-#pragma unroll
-        for (int j = 0; j < B; ++j) {
-            am[j] = a[i + j] - sigma;
-            ev[j] = e[i + j];
-        }
-#pragma unroll
-        for (int j = 0; j < B; ++j) rv[j] = pivot(am[j], ev[j]);
-#pragma unroll
-        for (int j = 0; j < B; ++j) {
-            rp[i + j] = rv[j];
-            z[i + j] = 1.0;
-        }
-    }
-    for (; i < k; ++i) {
-        rp[i] = pivot(a[i] - sigma, e[i]);
-        z[i] = 1.0;
-    }
-    for (int it = 0; it < 3; ++it) {
-        // L y = z (forward), then D L^T x = y (backward); x overwrites z
-        double c = z[0];
-        i = 1;
-        for (; i + B <= k; i += B) {
-            double zv[B], mv[B];
-#pragma unroll
-            for (int j = 0; j < B; ++j) {
-                zv[j] = z[i + j];
-                mv[j] = e[i + j] * rp[i + j - 1];
-            }
-#pragma unroll
-            for (int j = 0; j < B; ++j) {
-                c = zv[j] - mv[j] * c;
-                zv[j] = c;
-            }
-#pragma unroll
-            for (int j = 0; j < B; ++j) z[i + j] = zv[j];
-        }
-        for (; i < k; ++i) {
-            c = z[i] - (e[i] * rp[i - 1]) * c;
-            z[i] = c;
-        }
-        c = z[k - 1] * rp[k - 1];
-        z[k - 1] = c;
-        double nrm = c * c;
-        i = k - 2;
-        for (; i - B + 1 >= 0; i -= B) {   // i, i - 1, ..., i - B + 1
-            double rv[B], zv[B], ev[B];
-#pragma unroll
-            for (int j = 0; j < B; ++j) {
-                rv[j] = rp[i - j];
-                zv[j] = z[i - j];
-                ev[j] = e[i - j + 1];
-            }
-#pragma unroll
-            for (int j = 0; j < B; ++j) {
-                c = rv[j] * (zv[j] - ev[j] * c);
-                zv[j] = c;
-                nrm += c * c;
-            }
-#pragma unroll
-            for (int j = 0; j < B; ++j) z[i - j] = zv[j];
-        }
-        for (; i >= 0; --i) {
-            c = rp[i] * (z[i] - e[i + 1] * c);
-            z[i] = c;
-            nrm += c * c;
-        }
-        nrm = sqrt(nrm);
-        if (!(nrm > 0.0) || !isfinite(nrm)) break;
-        const double inv = 1.0 / nrm;
-#pragma unroll 8
-        for (int t = 0; t < k; ++t) z[t] *= inv;
-    }
 }
 
 }  // namespace pdz
