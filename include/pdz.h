@@ -158,6 +158,10 @@ pdz_status pdz_hv_pitched(pdz_problem p, pdz_dtype dt, const void* x, void* y, u
  *       LDS banks at every step): 5, 6, 7 one, two, three rows per work
  *       group (needs rows of 1024 to 13280 down states, at most two hop
  *       magnitudes; 6 and 7 F32 only);
+ *       8: the whole product in one pass, a few rows per work group (rows of
+ *       33 to 1023 down states, D < 2^29; the summands of the looped family
+ *       in its order, so the same bits; the other fields are not used, and
+ *       the automatic choice is 8 only while they are automatic too);
  * up_cw: column-chunk width of the up-hop pass (F32: 32, 64, 128, 256;
  *       F64: 16, 32, 64, 128);
  * up: 1 the hops of a row are loaded in batches of 8, 2 all hops of a row are
@@ -206,8 +210,8 @@ pdz_status pdz_hv_tune(pdz_problem p, pdz_dtype dt, const void* x, void* y, int3
  * then `reps` products back to back.  ms[0]: mean duration of the down pass
  * (diagonal and down-spin hops, writes y); ms[1]: of the up pass (up-spin
  * hops added onto y; 0 when the up sector has no hops); ms[2]: of one whole
- * pdz_hv in the back-to-back run.  A problem on the on-the-fly path has one
- * kernel: ms[0] is its duration, ms[1] = 0.  x, y as in pdz_hv (y = H x on
+ * pdz_hv in the back-to-back run.  A problem on the on-the-fly path or under
+ * plan down 8 has one kernel: ms[0] is its duration, ms[1] = 0.  x, y as in pdz_hv (y = H x on
  * return).  reps in [1, 1000].  Synchronous.  Errors: PDZ_EINVAL. */
 pdz_status pdz_hv_kernel_times(pdz_problem p, pdz_dtype dt, const void* x, void* y, int32_t reps, double* ms,
                                void* stream);

@@ -9,7 +9,8 @@
 // (perfect hash), evaluated once per sector state when the problem is created
 // (hop tables, k_hash.hip), or per element on the fallback path below.
 //
-// Two passes with opposite locality:
+// Short rows (plan down 8): the whole product in one pass, a few rows per
+// work group (hv_rows.h).  Otherwise two passes with opposite locality:
 //  1. down pass (k_hv_down_*): rows of x are staged in LDS and each thread
 //     gathers the down-hop targets of its column from LDS; writes
 //     diag + down term to y.
@@ -21,6 +22,7 @@
 // reproducible, and the same order as the fallback path.
 #include <type_traits>
 
+#include "hv_rows.h"
 #include "pdz_internal.h"
 
 namespace pdz {
@@ -894,6 +896,24 @@ __global__ __launch_bounds__(kNarrowBlock) void k_hv_down_narrow(const DownArgs<
     if (a.dotp) block_dot_store<kNarrowBlock>(dsum, a.dotp + blockIdx.x);
 }
 
+// ------------------------------------------------------- short rows, one pass
+
+// y = H x, one tile of `tile_rows` rows per work group (hv_rows.h); dotp: NULL,
+// or one partial sum of x . y per work group.
+template <typename T, int RV, int BLOCK>
+__global__ __launch_bounds__(BLOCK) void k_hv_rows(const RowsProb<T> p, const T* __restrict__ coef_g, int ncoef,
+                                                   uint32_t tile_rows, const int* skip, double* dotp,
+                                                   const T* __restrict__ x, T* __restrict__ y) {
+    if (skip && *skip) return;
+    extern __shared__ __align__(16) unsigned char smem[];
+    T* coef = reinterpret_cast<T*>(smem);
+    load_coef(coef, coef_g, ncoef);   // read after the tile's own barrier
+    const uint32_t u0 = blockIdx.x * tile_rows;
+    const double dsum = rows_tile<T, RV, BLOCK>(p, u0, min(tile_rows, (uint32_t)p.D_up - u0), coef,
+                                            smem + kMaxCoef * sizeof(T), x, y);
+    if (dotp) block_dot_store<BLOCK>(dsum, dotp + blockIdx.x);
+}
+
 // ------------------------------------------------------------------ up pass
 
 // Block -> (column chunk, row tile).  map 1: blocks are dealt to the XCDs
@@ -1390,7 +1410,53 @@ bool row_fits(const pdz_problem_s* p, size_t es, int rows) {
 
 bool wide_down(const pdz_problem_s* p, size_t es) { return p->dn.D >= (uint64_t)kWideBlock && row_fits(p, es, 1); }
 
-HvPlan default_plan(const pdz_problem_s* p, pdz_dtype dt) {
+// One-pass H.v over short rows (plan down 8): rows of at least 33 columns (a
+// shorter row leaves half of every wave idle; the flattened narrow pass does
+// not) and less than 1024 (longer ones have the scheduled or the wide pass).
+// Against the two passes at their default plan (us, FP64 / FP32): 70 x 70 (ring
+// of 8) 11 / 11 -> 7.5 / 7.5; 924 x 924 (4x3) 25.5 / 21.1 -> 16.6 / 10.9;
+// 6435 x 455 121 / 83 -> 58 / 31; 12870 x 560 with next-nearest bonds 261 / 200
+// -> 225 / 116; 705432 x 231 11970 / 7290 -> 2185 / 1110.  Rows of more than
+// 4 MB in all are read past the L2 of every XCD by the up hops.
+constexpr int kRowsPlan = 8;
+constexpr uint64_t kRowsMinDn = 33;
+constexpr uint64_t kRowsFewPieces = 2560;
+bool rows_available(const pdz_problem_s* p, uint64_t pitch) {
+    return p->hv_path == 0 && p->dn.D >= kRowsMinDn && p->dn.D < (uint64_t)kWideBlock &&
+           p->up.D * pitch <= 0xFFFFFFFFull / 8;   // byte offsets of FP64 elements in 32 bits
+}
+bool rows_default(const pdz_problem_s* p) { return rows_available(p, p->dn.D); }
+
+struct RowsGeom {
+    int rv = 4;      // rows per LDS group
+    int block = 256;
+    uint32_t tile_rows = 1;
+    uint64_t grid = 0;
+    size_t lds = 0;
+};
+// Four rows per LDS group: a table entry and its amplitude serve them all.  In
+// FP64 two while there are fewer than ten pieces of four rows and 64 columns
+// per CU, where waves in flight count for more (4x3 torus, two against four:
+// 4+6 9.3 against 13.8 us, 6+4 9.8 / 11.5, 6+5 16.2 / 15.1, 6+6 17.5 / 16.6).
+// Groups per tile: as many as give each of four waves a piece, but one while
+// that leaves fewer than two tiles per CU.  One wave per piece up to eight; up
+// to 16 while there are fewer than two tiles per CU (4x3 6+6 FP32: 14.0 us with
+// eight waves, 10.9 with 16).
+RowsGeom rows_geom(const pdz_problem_s* p, size_t es) {
+    RowsGeom g;
+    const uint32_t nch = (uint32_t)((p->dn.D + 63) / 64);
+    g.rv = es == 8 && p->up.D / 4 * nch < kRowsFewPieces ? 2 : 4;
+    uint32_t groups = nch >= 4 ? 1 : 4 / nch;
+    if (p->up.D < 512ull * g.rv * groups) groups = 1;
+    g.block = groups * nch <= 4 ? 256 : groups * nch > 8 && p->up.D < 512ull * g.rv ? 1024 : 512;
+    g.tile_rows = g.rv * groups;
+    g.grid = (p->up.D + g.tile_rows - 1) / g.tile_rows;
+    g.lds = kMaxCoef * es + (size_t)groups * (p->dn.D + 1) * g.rv * es;
+    return g;
+}
+
+// Two-pass plan of a problem (every field resolved).
+HvPlan two_pass_plan(const pdz_problem_s* p, pdz_dtype dt) {
     const size_t es = dt == PDZ_F64 ? 8 : 4;
     HvPlan d;
     const bool compact = p->up.tbits16 > 0 && p->dn.tbits16 > 0;
@@ -1410,15 +1476,33 @@ HvPlan default_plan(const pdz_problem_s* p, pdz_dtype dt) {
     return d;
 }
 
+HvPlan default_plan(const pdz_problem_s* p, pdz_dtype dt) {
+    HvPlan d = two_pass_plan(p, dt);
+    if (rows_default(p)) d.down = kRowsPlan;
+    return d;
+}
+
+// Launch plan of the two-pass H.v where the resolved plan is the one-pass one
+// (a single pass asked for, or a pitch past its range).
+HvPlan pass_plan(const pdz_problem_s* p, pdz_dtype dt, HvPlan pl) {
+    if (pl.down == kRowsPlan) pl.down = two_pass_plan(p, dt).down;
+    return pl;
+}
+
+}  // namespace
+
 HvPlan hv_resolve(const pdz_problem_s* p, pdz_dtype dt) {
     HvPlan pl = p->plan[dt == PDZ_F64 ? 0 : 1];
-    const HvPlan d = default_plan(p, dt);
+    // a set field of the up pass asks for the two passes
+    const HvPlan d = pl.up_cw || pl.up || pl.map ? two_pass_plan(p, dt) : default_plan(p, dt);
     if (pl.down == 0) pl.down = d.down;
     if (pl.up_cw == 0) pl.up_cw = d.up_cw;
     if (pl.up == 0) pl.up = d.up;
     if (pl.map == 0) pl.map = d.map;
     return pl;
 }
+
+namespace {
 
 int down_rows(int variant) { return sched_plan(variant) ? sched_rows(variant) : variant == 4 ? 3 : variant == 3 ? 2 : 1; }
 
@@ -1560,6 +1644,45 @@ pdz_status up_pass(const pdz_problem_s* p, const T* coef, const T* x, T* yout, h
 }
 
 
+// y = H x in one pass (plan down 8).
+template <typename T>
+pdz_status run_rows(const pdz_problem_s* p, const T* coef, const T* x, T* y, hipStream_t s, const int* skip,
+                    double* dotp, uint64_t pitch) {
+    RowsProb<T> rp;
+    rp.D_up = p->up.D;
+    rp.D_dn = p->dn.D;
+    rp.pitch = pitch;
+    rp.up_states = p->up.states;
+    rp.dn_states = p->dn.states;
+    rp.up_count = p->up.count;
+    rp.dn_count = p->dn.count;
+    rp.up_ell = p->up.ell;
+    rp.dn_ell = p->dn.ell;
+    rp.U = (T)p->U;
+    rp.dn_max = p->dn.max_hops;
+    const RowsGeom g = rows_geom(p, sizeof(T));
+    const int nc = (int)p->coef_host.size();
+    const dim3 grid((unsigned)g.grid), block((unsigned)g.block);
+    const auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, g.lds, s, rp, coef, nc, g.tile_rows, skip, dotp, x, y);
+    };
+    if (g.rv == 2) {
+        if constexpr (sizeof(T) == 8) {
+            if (g.block == 1024) launch(k_hv_rows<T, 2, 1024>);
+            else if (g.block == 256) launch(k_hv_rows<T, 2, 256>);
+            else launch(k_hv_rows<T, 2, 512>);
+        }
+    } else if (g.block == 1024) {
+        launch(k_hv_rows<T, 4, 1024>);
+    } else if (g.block == 256) {
+        launch(k_hv_rows<T, 4, 256>);
+    } else {
+        launch(k_hv_rows<T, 4, 512>);
+    }
+    PDZ_HIP(hipGetLastError());
+    return ok();
+}
+
 template <typename T, typename E>
 pdz_status run_tables(const pdz_problem_s* p, const DeviceCtx* ctx, const T* coef, const T* x, T* y, hipStream_t s,
                       const int* skip, bool compact, unsigned passes, const HvSplit* split, uint64_t pitch) {
@@ -1593,7 +1716,8 @@ pdz_status run_tables(const pdz_problem_s* p, const DeviceCtx* ctx, const T* coe
     da.fsc = fused ? split->fsc : nullptr;
     da.fkidx = fused ? split->fkidx : nullptr;
     da.fnorm = fused ? split->fnorm : nullptr;
-    const HvPlan plan = hv_resolve(p, sizeof(T) == 8 ? PDZ_F64 : PDZ_F32);
+    const pdz_dtype dt = sizeof(T) == 8 ? PDZ_F64 : PDZ_F32;
+    const HvPlan plan = pass_plan(p, dt, hv_resolve(p, dt));
     const DownGeom gm = down_geom(p, sizeof(T), plan, (unsigned)ctx->cu_count);
     da.rows = gm.rows;
     if (gm.wide && sched_plan(plan.down) && pitch + 32 > (uint64_t)kSchedPlane)
@@ -1664,6 +1788,10 @@ pdz_status run_hv(const pdz_problem_s* p, const T* coef, const T* x, T* y, hipSt
     if (pitch == 0) pitch = p->dn.D;
     if (pitch < p->dn.D) return fail(PDZ_EINVAL, "row pitch shorter than a row");
     if (p->hv_path == 0) {
+        const bool whole = passes == (kPassDown | kPassUp) &&
+                           (!split || (!split->z && !split->dotp_dn && !split->fq2));
+        if (whole && rows_available(p, pitch) && hv_resolve(p, sizeof(T) == 8 ? PDZ_F64 : PDZ_F32).down == kRowsPlan)
+            return run_rows<T>(p, coef, x, y, s, skip, split ? split->dotp_up : nullptr, pitch);
         const bool compact = p->up.tbits16 > 0 && p->dn.tbits16 > 0;
         if (compact) return run_tables<T, uint16_t>(p, ctx, coef, x, y, s, skip, true, passes, split, pitch);
         return run_tables<T, uint32_t>(p, ctx, coef, x, y, s, skip, false, passes, split, pitch);
@@ -1765,6 +1893,11 @@ std::vector<HvPlan> hv_candidates(const pdz_problem_s* p, pdz_dtype dt, bool eve
     out.push_back(d);
     if (p->hv_path != 0) return out;
     const size_t es = dt == PDZ_F64 ? 8 : 4;
+    const HvPlan two = two_pass_plan(p, dt);
+    if (rows_available(p, p->dn.D) && d.down != kRowsPlan) {
+        out.push_back(two);
+        out.back().down = kRowsPlan;
+    }
     const bool compact = p->up.tbits16 > 0 && p->dn.tbits16 > 0;
     std::vector<int> downs;
     const bool sched = wide_down(p, es) && p->dn.sched.words;
@@ -1779,7 +1912,7 @@ std::vector<HvPlan> hv_candidates(const pdz_problem_s* p, pdz_dtype dt, bool eve
         if (row_fits(p, es, 2) && p->up.D >= 2) downs.push_back(3);
         if (row_fits(p, es, 3) && p->up.D >= 3) downs.push_back(4);
     } else if (!sched) {
-        downs.push_back(d.down);
+        downs.push_back(two.down);
     }
     const int* cws = dt == PDZ_F64 ? kUpCw64 : kUpCw32;
     const bool pre_ok = p->up.max_hops <= 48 && p->D <= 0xFFFFFFFFull;
@@ -1825,7 +1958,7 @@ bool hv_fused_available(const pdz_problem_s* p, pdz_dtype dt) {
     DeviceCtx* ctx = nullptr;
     if (device_ctx(&ctx) != PDZ_OK) return false;
     const size_t es = dt == PDZ_F64 ? 8 : 4;
-    const HvPlan plan = hv_resolve(p, dt);
+    const HvPlan plan = pass_plan(p, dt, hv_resolve(p, dt));
     const DownGeom gm = down_geom(p, es, plan, (unsigned)ctx->cu_count);
     return gm.wide && (plan.down == 2 || plan.down == 3 || plan.down == 4 || sched_plan(plan.down));
 }
@@ -1836,7 +1969,9 @@ size_t hv_dot_count_max(const pdz_problem_s* p, pdz_dtype dt) {
     if (device_ctx(&ctx) != PDZ_OK) return 0;
     const size_t es = dt == PDZ_F64 ? 8 : 4;
     size_t best = 0;
-    for (const HvPlan& c : hv_candidates(p, dt, true)) {
+    if (rows_available(p, p->dn.D)) best = (size_t)rows_geom(p, es).grid;
+    for (HvPlan c : hv_candidates(p, dt, true)) {
+        c = pass_plan(p, dt, c);
         const size_t n = (size_t)down_grid(p, es, c, (unsigned)ctx->cu_count) +
                          (p->up.max_hops == 0 ? 1 : (size_t)up_blocks(p, es, c));
         if (n > best) best = n;
@@ -1930,8 +2065,13 @@ pdz_status launch_sched_groups(const SchedGroups& g, pdz_dtype dt, const void* x
     return run_sched_groups<float>(g, static_cast<const float*>(x), static_cast<float*>(y), s, skip, fuse);
 }
 
+int hv_whole_dots(const pdz_problem_s* p, pdz_dtype dt) {
+    if (p->hv_path != 0 || !rows_available(p, p->dn.D) || hv_resolve(p, dt).down != kRowsPlan) return 0;
+    return (int)rows_geom(p, dt == PDZ_F64 ? 8 : 4).grid;
+}
+
 bool hv_dot_counts(const pdz_problem_s* p, pdz_dtype dt, int* n_dn, int* n_up) {
-    if (p->hv_path != 0) return false;
+    if (p->hv_path != 0 || hv_whole_dots(p, dt) > 0) return false;
     DeviceCtx* ctx = nullptr;
     if (device_ctx(&ctx) != PDZ_OK) return false;
     const size_t es = dt == PDZ_F64 ? 8 : 4;

@@ -790,14 +790,15 @@ struct Run {
 
     // Split H.v layout of this run: partial-sum counts of its two passes
     // (ndn = 0: the on-the-fly path, which takes a separate dot kernel).
-    // nwhole: partial sums of q . H q that the whole (unsplit) H.v writes (parity).
+    // nwhole: partial sums of q . H q that the whole (unsplit) H.v writes (parity,
+    // one-pass H.v over short rows).
     struct SplitCounts {
         int ndn = 0, nup = 0, nwhole = 0;
     };
     SplitCounts split_counts() const {
         SplitCounts c;
         if (!hv_dot_counts(p, (pdz_dtype)o->storage, &c.ndn, &c.nup)) c.ndn = c.nup = 0;
-        c.nwhole = parity_dot_count(p, (pdz_dtype)o->storage);
+        c.nwhole = p->par ? parity_dot_count(p, (pdz_dtype)o->storage) : hv_whole_dots(p, (pdz_dtype)o->storage);
         return c;
     }
 

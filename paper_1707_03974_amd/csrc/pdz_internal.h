@@ -75,7 +75,7 @@ struct ParSpace; // inversion-parity tables (k_parity.hip)
 // H.v launch plan for one precision (0 = automatic choice).
 struct HvPlan {
     int down = 0;    // 1: one row per group, hop table loaded up front; 2: one row, table in a loop;
-                     // 3: two rows per group, table in a loop
+                     // 3: two rows per group, table in a loop; 8: short rows, the whole product in one pass
     int up_cw = 0;   // up-pass chunk width in columns
     int up = 0;      // 1: hops of a row loaded in batches of 8; 2: all hops of a row loaded up front
     int map = 0;     // up-pass tile order: 1 XCD-aware chunk pairs, 2 chunk-major, 3 XCD-aware single chunks
@@ -184,6 +184,10 @@ pdz_status launch_hvk(const pdz_problem_s* p, pdz_dtype dt, const void* x, void*
 // family, which a caller may still select.
 std::vector<HvPlan> hv_candidates(const pdz_problem_s* p, pdz_dtype dt, bool every = false);
 bool hv_plan_valid(const pdz_problem_s* p, pdz_dtype dt, const HvPlan& plan);
+HvPlan hv_resolve(const pdz_problem_s* p, pdz_dtype dt);   // the problem's plan, automatic fields resolved
+// x . y partials that a whole real-space H.v (launch_hv with split->dotp_up
+// alone) writes under the problem's plan; 0: it has two passes (hv_dot_counts)
+int hv_whole_dots(const pdz_problem_s* p, pdz_dtype dt);
 // passes: kPassDown | kPassUp for y = H x; one bit alone launches only that
 // pass of the table path (the down pass writes y, the up pass adds onto it).
 // split (table path only): the up term goes to split->z instead of being

@@ -25,12 +25,7 @@ pdz_status pdz_hv_get_plan(pdz_problem p, pdz_dtype dt, pdz_hv_plan* out) {
     pdz_status st = check_dt(p, dt);
     if (st != PDZ_OK) return st;
     if (!out) return fail(PDZ_EINVAL, "out is NULL");
-    const std::vector<HvPlan> c = hv_candidates(p, dt);
-    HvPlan pl = p->plan[dt];
-    if (pl.down == 0) pl.down = c[0].down;
-    if (pl.up_cw == 0) pl.up_cw = c[0].up_cw;
-    if (pl.up == 0) pl.up = c[0].up;
-    if (pl.map == 0) pl.map = c[0].map;
+    const HvPlan pl = hv_resolve(p, dt);
     out->down = pl.down;
     out->up_cw = pl.up_cw;
     out->up = pl.up;
@@ -132,7 +127,7 @@ pdz_status pdz_hv_kernel_times(pdz_problem p, pdz_dtype dt, const void* x, void*
             break;
         }
     }
-    const bool two = p->hv_path == 0;
+    const bool two = p->hv_path == 0 && hv_whole_dots(p, dt) == 0;   // else one kernel
     if (st == PDZ_OK) st = launch_hv(p, dt, x, y, s);   // warm-up
     for (int r = 0; r < reps && st == PDZ_OK; ++r) {
         hipError_t he = hipEventRecord(ev[3 * r], s);
