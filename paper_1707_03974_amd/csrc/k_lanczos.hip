@@ -206,12 +206,21 @@ constexpr int kUpdBlock = 512;   // 32 waves per CU at kRedGrid work groups: mor
 // alpha_k itself (p1 = NULL: alpha[k] is read).  Up to kAlphaInUpdate of them:
 // four loads a thread, against a launch of 4.7 us for one work group.
 constexpr uint64_t kAlphaInUpdate = 2048;
-struct AlphaSums {
+struct StepSums {
     const double* p1 = nullptr;
     const double* p2 = nullptr;
     int n1 = 0, n2 = 0;
     double* alpha = nullptr;
     uint32_t* err = nullptr;
+    // Blocks of steps (lag): the step is *kidx + koff, dropped from kmax on;
+    // beta_k and its scale come from the n partials of |q_k|^2 that the update
+    // before wrote (norms[k & 1]), and this one writes norms[(k + 1) & 1].
+    bool lag = false;
+    int koff = 0, kmax = 0;
+    double* norms[2] = {nullptr, nullptr};
+    int n = 0;
+    double* beta = nullptr;
+    double* sc = nullptr;
 };
 
 // Sum over a work group of BLOCK threads (fixed order), valid in thread 0.
@@ -259,22 +268,38 @@ __global__ __launch_bounds__(kUpdBlock) void k_update_scaled(T* __restrict__ w, 
                                                              uint64_t D, const double* alpha, const double* beta,
                                                              const double* sc, const int* kidx, double* partial,
                                                              const int* skip, int vec, T* __restrict__ keep,
-                                                             uint64_t keep_ld, int keep_cap, const AlphaSums as) {
+                                                             uint64_t keep_ld, int keep_cap, const StepSums as) {
     if (skip && *skip) return;
-    const int k = *kidx;
-    const double a = sc[k];
+    const int k = *kidx + as.koff;
+    const bool first = blockIdx.x == 0 && threadIdx.x == 0;
+    double a, c;
+    if (as.lag) {
+        if (k >= as.kmax) return;
+        partial = as.norms[(k + 1) & 1];
+    }
+    if (as.lag && k > 0) {
+        const double bk = sqrt(sum_two<kUpdBlock>(as.norms[k & 1], as.n, nullptr, 0));
+        a = 1.0 / bk;
+        c = bk * sc[k - 1];
+        if (first) {
+            as.beta[k] = bk;
+            as.sc[k] = a;
+        }
+    } else {
+        a = sc[k];
+        c = k > 0 ? beta[k] * sc[k - 1] : 0.0;
+    }
     double ak;
     if (as.p1) {
         ak = a * a * sum_two<kUpdBlock>(as.p1, as.n1, as.p2, as.n2);
-        if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (first) {
             as.alpha[k] = ak;
-            if (!isfinite(ak)) atomicOr(as.err, kErrNonFinite);
+            if (as.err && !isfinite(ak)) atomicOr(as.err, kErrNonFinite);
         }
     } else {
         ak = alpha[k];
     }
     const double b = ak * a;
-    const double c = k > 0 ? beta[k] * sc[k - 1] : 0.0;
     const uint64_t tid = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     T* kept = (KEEP && k + 1 < keep_cap) ? keep + (uint64_t)(k + 1) * keep_ld : nullptr;
@@ -334,7 +359,7 @@ __global__ __launch_bounds__(kUpdBlock) void k_update_scaled(T* __restrict__ w, 
 template <typename T, bool KEEP>
 void launch_update_scaled_k(T* w, const T* z, const T* q, const T* qp, uint64_t D, const double* alpha,
                             const double* beta, const double* sc, const int* kidx, double* partial, const int* skip,
-                            hipStream_t s, int vec, T* keep, uint64_t keep_ld, int keep_cap, const AlphaSums& as) {
+                            hipStream_t s, int vec, T* keep, uint64_t keep_ld, int keep_cap, const StepSums& as) {
     if (z)
         hipLaunchKernelGGL((k_update_scaled<T, true, KEEP>), dim3(kRedGrid), dim3(kUpdBlock), 0, s, w, z, q, qp, D,
                            alpha, beta, sc, kidx, partial, skip, vec, keep, keep_ld, keep_cap, as);
@@ -348,7 +373,7 @@ template <typename T>
 void launch_update_scaled(T* w, const T* z, const T* q, const T* qp, uint64_t D, const double* alpha,
                           const double* beta, const double* sc, const int* kidx, double* partial, const int* skip,
                           hipStream_t s, T* keep = nullptr, uint64_t keep_ld = 0, int keep_cap = 0,
-                          const AlphaSums& as = AlphaSums()) {
+                          const StepSums& as = StepSums()) {
     auto al = [](const void* x) { return ((uintptr_t)x & 15) == 0; };
     const int vec = al(w) && al(q) && al(qp) && (!z || al(z)) && (!keep || (al(keep) && keep_ld % 4 == 0));
     if (keep)
@@ -527,6 +552,51 @@ __global__ __launch_bounds__(kTriBlock) void k_ritz(const double* partial, int n
             sc[k] = 1.0 / bk1;
     }
 }
+
+// Ritz pairs of a block of `steps` steps, work group t the pair of step
+// ctl->k + t (tridiag.h); norms[j]: the n partials of |q|^2 of the vectors of
+// parity j, of which the last step's beta is formed.
+__global__ __launch_bounds__(kTriBlock) void k_ritz_block(const double* norm0, const double* norm1, int n,
+                                                          const double* alpha, double* beta, double* theta,
+                                                          double* resid, const Ctl* ctl, int max_iter) {
+    const int k = ctl->k + blockIdx.x + 1;
+    if (ctl->done || k > max_iter) return;
+    __shared__ TriShared<kMaxIter> S;
+    __shared__ double red[kRedBlock];
+    double bk1;
+    if (blockIdx.x + 1 == gridDim.x || k == max_iter) {   // no update after this step has formed beta_{k+1}
+        const double* p = (k & 1) ? norm1 : norm0;
+        double acc = 0.0;
+        for (int i = threadIdx.x; i < n; i += blockDim.x) acc += p[i];
+        bk1 = sqrt(block_sum(acc, red));
+        if (threadIdx.x == 0) beta[k] = bk1;
+    } else {
+        bk1 = beta[k];
+    }
+    ritz_block_step(S, ctl, (int)blockIdx.x, alpha, beta, bk1, theta, resid);
+}
+
+__global__ void k_ritz_block_end(Ctl* ctl, int steps, const double* alpha, const double* beta, const double* theta,
+                                 const double* resid, double tol, int max_iter, uint32_t* err) {
+    if (threadIdx.x == 0 && blockIdx.x == 0 && !ctl->done)
+        ritz_block_end(ctl, steps, alpha, beta, theta, resid, tol, max_iter, err, kErrNonFinite);
+}
+
+// Eigenvector of the last step's T_k.
+__global__ __launch_bounds__(kTriBlock) void k_ritz_vector(const double* alpha, const double* beta, const Ctl* ctl,
+                                                           double* s_out) {
+    __shared__ TriShared<kMaxIter> S;
+    const int k = ctl->k;
+    if (k < 1) return;
+    tridiag_min_pair(S, alpha, beta, k, 0.0, 0.0);
+    for (int i = threadIdx.x; i < k; i += blockDim.x) s_out[i] = S.z[i];
+}
+
+// Vectors up to which the Ritz pairs run by blocks of steps: up to 11 steps past
+// the last one are then taken for nothing, against one solve (25 us on average
+// over the first 100 steps) saved in every step.
+constexpr uint64_t kLagElems = 1ull << 22;
+constexpr int kLagSums = 8192;   // partial sums of alpha the update may have to add
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
@@ -824,10 +894,11 @@ struct Run {
     // two parts (w: diagonal + down hops, z: up hops) that the update adds;
     // alpha comes from partial sums of q . (each part) written by the two
     // passes of H.v, so no pass re-reads a D-sized vector for them.
-    pdz_status step_scaled(T* q, T* qp, T* w, const SplitCounts& c) {
+    // lag >= 0: step number `lag` of a block (no Ritz solve of its own).
+    pdz_status step_scaled(T* q, T* qp, T* w, const SplitCounts& c, int lag = -1) {
         mark(0);
         double* norms = partial3();   // the update may still read the sums in partial()
-        AlphaSums as;
+        StepSums as;
         as.p1 = partial();
         as.alpha = alpha();
         as.err = err;
@@ -863,7 +934,17 @@ struct Run {
                                done());
             as.n1 = kRedGrid;
         }
-        if ((uint64_t)as.n1 + as.n2 > kAlphaInUpdate) {
+        if (lag >= 0) {
+            as.err = nullptr;   // steps past the last one may hold anything; the block's end looks at the others
+            as.lag = true;
+            as.koff = lag;
+            as.kmax = o->max_iter;
+            as.norms[0] = partial2();
+            as.norms[1] = partial3();
+            as.n = kRedGrid;
+            as.beta = beta();
+            as.sc = sc();
+        } else if ((uint64_t)as.n1 + as.n2 > kAlphaInUpdate) {
             end_alpha(as.p1, as.n1, as.p2, as.n2);
             as.p1 = nullptr;   // the update reads alpha[k]
         }
@@ -871,9 +952,24 @@ struct Run {
         launch_update_scaled<T>(w, c.ndn > 0 ? (const T*)zbuf() : (const T*)nullptr, q, qp, D, alpha(), beta(), sc(),
                                 kptr(), norms, done(), s, kept(0), ld(), L.nkept, as);
         mark(4);
-        end_step(norms, kRedGrid, sc());
+        if (lag < 0) end_step(norms, kRedGrid, sc());
         mark(5);
         return launch_check();
+    }
+
+    // Whether the Ritz pairs run by blocks of steps.
+    bool lag_path(const SplitCounts& c) const {
+        const int n = c.ndn > 0 ? c.ndn + c.nup : c.nwhole > 0 ? c.nwhole : (int)kRedGrid;
+        return !o->reorth && D <= kLagElems && n <= kLagSums;
+    }
+
+    // Ritz pairs of the `steps` steps just taken and the stopping test.
+    void end_block(int steps) {
+        double* resid = theta() + o->max_iter + 8;   // the second half of the theta area
+        hipLaunchKernelGGL(k_ritz_block, dim3((unsigned)steps), dim3(kTriBlock), 0, s, partial2(), partial3(),
+                           (int)kRedGrid, alpha(), beta(), theta(), resid, ctl(), o->max_iter);
+        hipLaunchKernelGGL(k_ritz_block_end, dim3(1), dim3(64), 0, s, ctl(), steps, alpha(), beta(), theta(), resid,
+                           o->tol, o->max_iter, err);
     }
 
     // The two passes of H q_k and alpha_k (the first half of step_scaled).
@@ -1110,6 +1206,7 @@ struct Run {
             st = head_step(buf(0), buf(2), counts);
             if (st != PDZ_OK) return st;
         }
+        const bool lag = !fuse && lag_path(counts);
         auto enqueue_block = [&]() -> pdz_status {
             for (int t = 0; t < period; ++t) {
                 pdz_status s2;
@@ -1118,11 +1215,12 @@ struct Run {
                     s2 = fused_step(buf(a), buf(1 - a), buf(2), counts);
                 } else {
                     const int a = t % 3;
-                    s2 = step_scaled(buf(a), buf((a + 2) % 3), buf((a + 1) % 3), counts);
+                    s2 = step_scaled(buf(a), buf((a + 2) % 3), buf((a + 1) % 3), counts, lag ? t % kRitzBlock : -1);
                 }
                 if (s2 != PDZ_OK) return s2;
+                if (lag && ((t + 1) % kRitzBlock == 0 || t + 1 == period)) end_block(t % kRitzBlock + 1);
             }
-            return ok();
+            return launch_check();
         };
         hipGraphExec_t exec = nullptr;
         hipGraph_t graph = nullptr;
@@ -1167,6 +1265,8 @@ struct Run {
     // Ritz vector y = sum_j s_j v_j (FP64), normalised; FP64 Rayleigh quotient and residual.
     pdz_status refine(const void* v0, int m, double* E_ref, double* r_ref) {
         const unsigned g = grid_elems(D);
+        if (!fused_path() && lag_path(split_counts()))
+            hipLaunchKernelGGL(k_ritz_vector, dim3(1), dim3(kTriBlock), 0, s, alpha(), beta(), ctl(), svec());
         if (o->reorth) {
             hipLaunchKernelGGL(k_combine_basis<T>, dim3(g), dim3(kRedBlock), 0, s, y(), basis(0), ld(), D, m, svec());
         } else if (kept(0) && m <= L.nkept) {

@@ -102,7 +102,7 @@ __device__ __forceinline__ int tri_first(TriShared<N>& S, bool b, int round) {
 // Lanczos the previous Ritz value bounds the new one from above (Cauchy
 // interlacing), and the last change estimates how far it moves.
 template <int N>
-__device__ double tridiag_min_pair(TriShared<N>& S, const double* alpha, const double* beta, int k, double hint_lo,
+__device__ __forceinline__ double tridiag_min_pair(TriShared<N>& S, const double* alpha, const double* beta, int k, double hint_lo,
                                    double hint_hi) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // ---- scale by a power of two so that no entry exceeds one
@@ -266,6 +266,59 @@ __device__ inline void ritz_hint(double theta1, double theta2, double* lo, doubl
     const double w = fmax(8.0 * fabs(theta1 - theta2), 1e-12 * scale);
     *hi = theta1 + 8.0 * 2.220446049250313e-16 * scale;
     *lo = theta1 - w;
+}
+
+// ---- Ritz pairs of a block of Lanczos steps at once.
+//
+// Only the stopping test needs a step's Ritz pair, so for vectors whose step is
+// short the solves of kRitzBlock steps run side by side after the block, one
+// work group per step, instead of one between every two steps; the steps past
+// the first that meets the test are dropped.  Step t of a block is step
+// ctl->k + t of the run: ctl->k stays what it was until ritz_block_end.
+constexpr int kRitzBlock = 12;
+
+// Work group t of the block: the pair of T_k, k = ctl->k + t + 1.  bk1 =
+// beta[k]; theta, resid: Ritz values and residuals beta[k] |s_k| by step.  No
+// hint from earlier steps: which of them are known depends on where the blocks
+// lie, and the last bits of the bracket on the hint.
+template <int N, typename C>
+__device__ __forceinline__ void ritz_block_step(TriShared<N>& S, const C* ctl, int t, const double* alpha,
+                                                const double* beta, double bk1, double* theta, double* resid) {
+    const int k = ctl->k + t + 1;
+    const double th = tridiag_min_pair(S, alpha, beta, k, 0.0, 0.0);
+    if (threadIdx.x == 0) {
+        theta[k - 1] = th;
+        resid[k - 1] = fabs(bk1 * S.z[k - 1]);
+    }
+}
+
+// One thread: the steps of the block in turn, up to the first that ends the run.
+template <typename C>
+__device__ __forceinline__ void ritz_block_end(C* ctl, int steps, const double* alpha, const double* beta,
+                                               const double* theta, const double* resid, double tol, int max_iter,
+                                               uint32_t* err, uint32_t nonfinite) {
+    const int k0 = ctl->k;
+    for (int k = k0 + 1; k <= k0 + steps && k <= max_iter; ++k) {
+        const double th = theta[k - 1], rs = resid[k - 1], bk1 = beta[k];
+        ctl->theta = th;
+        ctl->resid = rs;
+        ctl->k = k;
+        const bool breakdown = !(bk1 > 1e-14 * fmax(1.0, fabs(th)));
+        bool done = k >= max_iter;
+        if (!isfinite(th) || !isfinite(bk1) || !isfinite(alpha[k - 1])) {
+            atomicOr(err, nonfinite);
+            done = true;
+        }
+        if (breakdown || rs <= tol * fmax(fabs(th), 1e-300)) {
+            ctl->converged = 1;
+            ctl->breakdown = breakdown ? 1 : 0;
+            done = true;
+        }
+        if (done) {
+            ctl->done = 1;
+            break;
+        }
+    }
 }
 
 }  // namespace pdz

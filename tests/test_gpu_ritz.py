@@ -48,3 +48,34 @@ def test_ritz_values_of_matrices_far_from_one(power):
     s = 2.0 ** power
     g = pdz.Problem(8, [(b.i, b.j, b.t * s) for b in w.bonds], w.U * s, w.n_up, w.n_dn)
     _check(g.lanczos(max_iter=25, tol=0.0, history=True, coefficients=True), s)
+
+
+@pytest.mark.parametrize("max_iter,tol", [(1, 0.0), (5, 0.0), (12, 0.0), (13, 0.0), (40, 1e-6), (300, 1e-12)])
+def test_blocks_of_steps_stop_where_the_test_is_first_met(max_iter, tol):
+    """Ritz pairs solved for a block of steps at a time: steps, energy and history do not depend on the
+    block lengths, and stop at the first step that meets the test (found here from a run without one)."""
+    import paper_1707_03974_amd as pdz
+    torch_cuda()
+    g = pdz.Problem.from_workload(synth.workload("ring8"))
+    runs = [g.lanczos(max_iter=max_iter, tol=tol, check_every=ce, use_graph=ug, history=True, coefficients=True)
+            for ce, ug in ((1, 1), (2, 0), (7, 1), (12, 0), (13, 1), (40, 1))]
+    for r in runs[1:]:
+        for k in ("E0", "iters", "resid_est", "converged", "thetas", "alpha", "beta"):
+            assert r[k] == runs[0][k], (k, r[k], runs[0][k])
+    full = g.lanczos(max_iter=max_iter, tol=0.0, history=True)
+    n = runs[0]["iters"]
+    assert runs[0]["thetas"] == full["thetas"][:n]
+    assert runs[0]["resid_est"] <= tol * abs(runs[0]["E0"]) if runs[0]["converged"] and tol else n == full["iters"]
+
+
+def test_invariant_subspace_in_the_middle_of_a_block():
+    """A start vector with three eigencomponents closes the Krylov space after three steps; the steps the
+    block still holds divide by a vanishing norm and must leave no trace."""
+    import paper_1707_03974_amd as pdz
+    torch = torch_cuda()
+    g = pdz.Problem(4, [(0, 1, 0.0)], 2.0, 2, 2)      # diagonal H: U times the doubly occupied sites (0, 1, 2)
+    v0 = torch.ones(g.D, dtype=torch.float64, device="cuda")
+    r = g.lanczos(v0=v0, max_iter=50, tol=0.0, history=True, coefficients=True, refine=1)
+    assert r["converged"] == 1 and r["iters"] == 3 and len(r["thetas"]) == 3
+    assert abs(r["E0"]) <= 1e-13 and abs(r["E0_refined"]) <= 1e-13
+    assert np.all(np.isfinite(r["alpha"])) and np.all(np.isfinite(r["beta"]))
