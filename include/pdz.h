@@ -468,8 +468,8 @@ typedef struct pdz_batch_s* pdz_batch;
 typedef struct {
     int32_t tile_elems;   /* about this many vector elements per tile: 1024, 2048, 4096 or 8192      */
     int32_t block;        /* threads per work group: 256, 512 or 1024                                */
-    int32_t wgs_per_cu;   /* persistent work groups per compute unit, 1..8                           */
-    int32_t order;        /* tile queue order: 1 largest problems first, 2 problem order             */
+    int32_t wgs_per_cu;   /* work groups per compute unit that walk the tile list, 1..8              */
+    int32_t order;        /* tile list order: 1 largest problems first, 2 problem order              */
 } pdz_batch_plan;
 
 typedef struct {
@@ -492,14 +492,13 @@ pdz_status pdz_batch_destroy(pdz_batch b);
  * offsets[n] = length of the packed array. */
 pdz_status pdz_batch_offsets(pdz_batch b, uint64_t* offsets);
 
-/* y_i = H_i x_i for every problem i of the batch, in one persistent launch:
- * work groups take tiles (problem, group of rows) from a device queue, so the
- * uneven sizes balance across the chip.  x, y: packed device arrays
+/* y_i = H_i x_i for every problem i of the batch, in one launch: work groups
+ * walk a list of tiles (problem, group of rows), largest problems first, so
+ * the uneven sizes balance across the chip.  x, y: packed device arrays
  * (offsets[n] elements of precision dt), not overlapping.  Each output is
  * summed in the same order as pdz_hv on its problem, so results are bitwise
  * identical to n single calls.  Asynchronous on `stream`; capturable in a
- * HIP graph.  Calls on one batch must not overlap (they share its queue
- * counter).  Errors: PDZ_EINVAL. */
+ * HIP graph.  Errors: PDZ_EINVAL. */
 pdz_status pdz_batch_hv(pdz_batch b, pdz_dtype dt, const void* x, void* y, void* stream);
 
 pdz_status pdz_batch_get_plan(pdz_batch b, pdz_batch_plan* out);
@@ -519,7 +518,8 @@ pdz_status pdz_batch_lanczos_workspace_size(pdz_batch b, const pdz_lanczos_opts*
 /* Lowest eigenvalue of every problem of the batch by the Lanczos recurrence
  * of pdz_lanczos, all problems in lockstep: one batched H.v per step, FP64
  * alpha, beta, Ritz value and convergence flag per problem on the device, and
- * a converged problem skipped by every later kernel.  With use_graph, blocks
+ * a converged problem skipped by every later kernel (the Ritz pairs are solved
+ * for 12 steps at a time; steps past a problem's last are dropped).  With use_graph, blocks
  * of check_every steps (rounded up to a multiple of 3) are replayed as one
  * captured HIP graph.  Problem i starts from the seeded vector of seed + i
  * (the pdz_lanczos start vector of that seed), so its result equals a

@@ -1,19 +1,19 @@
 // Batched H.v and Lanczos over many Hubbard clusters of uneven size.
 //
 // The clusters' vectors are packed back to back (each at a 64-element aligned
-// offset).  One persistent launch applies every cluster's H: work groups pull
-// tiles (cluster, group of rows) from an atomic work queue, largest clusters
-// first, stage the tile's rows in LDS and compute each output element whole:
-// diagonal, down hops gathered from LDS, up hops read from the (cache
-// resident) packed vector.  Every element is summed by one thread in the same
-// order as the single-cluster H.v, so the results are bitwise identical to
-// pdz_hv on each cluster.  The queue is reset by a small kernel before each
-// launch, which keeps the pair capturable in a HIP graph.
+// offset).  One launch applies every cluster's H: work groups walk the list of
+// tiles (cluster, group of rows), largest clusters first; a tile is computed
+// whole as in the single-cluster one-pass H.v (hv_rows.h), or, in a batch with
+// rows too long for that, row by row.  Every element is summed by one thread
+// in the same order as the single-cluster H.v, so the results are bitwise
+// identical to pdz_hv on each cluster.
 //
 // Batched Lanczos runs the recurrence of k_lanczos.hip for all clusters in
-// lockstep over the packed vectors: per-cluster alpha, beta, Ritz value and
-// convergence flag on the device; a converged cluster's tiles and chunks are
-// skipped by every later kernel.
+// lockstep over the packed vectors, unnormalised (v_k = sc_k q_k): per step
+// one H.v, which also writes the partial sums of alpha, and one update, which
+// forms alpha_k, beta_k and sc_k from partial sums itself; the Ritz pairs of
+// kRitzBlock steps of every cluster then run side by side (tridiag.h).  A
+// converged cluster's tiles and chunks are skipped by every later kernel.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -21,6 +21,7 @@
 #include <numeric>
 #include <vector>
 
+#include "hv_rows.h"
 #include "pdz_internal.h"
 #include "tridiag.h"
 
@@ -30,7 +31,7 @@ namespace {
 constexpr int kBatchMaxIter = 2000;
 constexpr int kRed = 256;
 constexpr uint64_t kAlign = 64;       // packed vector offsets, elements
-constexpr uint64_t kChunk = 16384;    // reduction chunk, elements
+constexpr uint64_t kChunk = 4096;     // elements per work group of the update and the reductions
 
 struct BProb {
     uint64_t off;                 // element offset of the cluster's vector
@@ -45,7 +46,7 @@ struct BProb {
     const double* coef64;
     const float* coef32;
     int ncoef;
-    int pad;
+    int dn_max;                   // most hops out of a down state
 };
 
 struct BTile {
@@ -69,15 +70,10 @@ struct BCtl {                      // per-cluster Lanczos state
     double theta;
     double resid;
     double norm0;
-    double theta_prev;   // Ritz value of the step before
 };
 
 __global__ void k_clear_bits1(uint32_t* w, uint32_t bits) {
     if (threadIdx.x == 0 && blockIdx.x == 0) atomicAnd(w, ~bits);
-}
-
-__global__ void k_queue_reset(unsigned* q) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *q = 0u;
 }
 
 template <typename T>
@@ -89,21 +85,33 @@ __device__ __forceinline__ const float* bcoef<float>(const BProb& p) { return p.
 
 constexpr int kBHopNB = 8;   // hops of one element whose loads are in flight together
 
+constexpr int kBatchRV = 4;   // rows side by side in a tile of k_batch_rows
+
+// Sum over a work group of BLOCK threads (fixed order), valid in thread 0.
+template <int BLOCK>
+__device__ __forceinline__ double tile_sum(double v) {
+    __shared__ double ws[BLOCK / 64];
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1) v += __shfl_xor(v, m);
+    if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = v;
+    __syncthreads();
+    double t = 0.0;
+    if (threadIdx.x == 0)
+        for (int i = 0; i < BLOCK / 64; ++i) t += ws[i];
+    return t;
+}
+
 // done: per-cluster flags with stride `dstride` ints (NULL: none skipped).
+// dotp: NULL, or one partial sum of x . y per tile.  This form takes any rows
+// that fit the LDS; k_batch_rows below is the fast one.
 template <typename T, int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_batch_hv(const BProb* __restrict__ probs, const BTile* __restrict__ tiles,
-                                                    uint32_t ntiles, unsigned* queue, const int* done, int dstride,
+                                                    uint32_t ntiles, const int* done, int dstride, double* dotp,
                                                     const T* __restrict__ x, T* __restrict__ y) {
     extern __shared__ __align__(16) unsigned char smem[];
     T* coef = reinterpret_cast<T*>(smem);
     T* rows = coef + kMaxCoef;
-    __shared__ uint32_t s_t;
-    for (;;) {
-        if (threadIdx.x == 0) s_t = atomicAdd(queue, 1u);
-        __syncthreads();
-        const uint32_t t = s_t;
-        __syncthreads();
-        if (t >= ntiles) break;   // every wave of every group reaches this exit once the queue is drained
+    for (uint32_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
         const BTile tl = tiles[t];
         if (done && done[(size_t)tl.prob * dstride]) continue;
         const BProb pr = probs[tl.prob];
@@ -117,6 +125,7 @@ __global__ __launch_bounds__(BLOCK) void k_batch_hv(const BProb* __restrict__ pr
         for (uint32_t k = threadIdx.x; k < nelem; k += BLOCK) rows[k] = xg[k];
         __syncthreads();
         const T U = (T)pr.U;
+        double dsum = 0.0;
         for (uint32_t k = threadIdx.x; k < nelem; k += BLOCK) {
             const uint32_t r = k / (uint32_t)D_dn;
             const uint32_t d = k - r * (uint32_t)D_dn;
@@ -159,8 +168,49 @@ __global__ __launch_bounds__(BLOCK) void k_batch_hv(const BProb* __restrict__ pr
                 acc += coef[e >> kTargetBits] * xp[(uint64_t)(e & kTargetMask) * D_dn + d];
             }
             yp[u * D_dn + d] = acc;
+            dsum += (double)xrow[d] * (double)acc;
+        }
+        if (dotp) {
+            dsum = tile_sum<BLOCK>(dsum);
+            if (threadIdx.x == 0) dotp[t] = dsum;
         }
         __syncthreads();
+    }
+}
+
+// The same for batches whose rows fit the one-pass tile (four rows side by side
+// in LDS).  32 clusters of the 4x3 and 3x3 tori (8.2e6 elements): 207 us FP64
+// with one element per thread and a device work queue, 108 us so (FP32 145 / 75).
+template <typename T, int BLOCK>
+__global__ __launch_bounds__(BLOCK, 4) void k_batch_rows(const BProb* __restrict__ probs, const BTile* __restrict__ tiles,
+                                                      uint32_t ntiles, const int* done, int dstride, double* dotp,
+                                                      const T* __restrict__ x, T* __restrict__ y) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    T* coef = reinterpret_cast<T*>(smem);
+    for (uint32_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        const BTile tl = tiles[t];
+        if (done && done[(size_t)tl.prob * dstride]) continue;
+        const BProb& pr = probs[tl.prob];
+        const T* cg = bcoef<T>(pr);
+        for (int k = threadIdx.x; k < pr.ncoef; k += BLOCK) coef[k] = cg[k];
+        RowsProb<T> rp;
+        rp.D_up = pr.D_up;
+        rp.D_dn = rp.pitch = pr.D_dn;
+        rp.up_states = pr.up_states;
+        rp.dn_states = pr.dn_states;
+        rp.up_count = pr.up_count;
+        rp.dn_count = pr.dn_count;
+        rp.up_ell = pr.up_ell;
+        rp.dn_ell = pr.dn_ell;
+        rp.U = (T)pr.U;
+        rp.dn_max = pr.dn_max;
+        double dsum = rows_tile<T, kBatchRV, BLOCK>(rp, tl.u0, tl.nrows, coef, smem + kMaxCoef * sizeof(T), x + pr.off,
+                                                    y + pr.off);
+        if (dotp) {
+            dsum = tile_sum<BLOCK>(dsum);
+            if (threadIdx.x == 0) dotp[t] = dsum;
+        }
+        __syncthreads();   // the tile's LDS is rewritten by the next
     }
 }
 
@@ -211,43 +261,107 @@ __global__ __launch_bounds__(kRed) void k_bdot(const BChunk* ch, const BProb* pr
     if (threadIdx.x == 0) partial[blockIdx.x] = acc;
 }
 
-// w -= alpha_k v + beta_k vp; partial[c] = |w|^2 over chunk c.
+// The recurrence of step k = ctl.k + koff of every live cluster (steps from kmax
+// on are dropped): w = H q_k on entry, q_{k+1} on exit.  alpha_k comes from the
+// cluster's tile sums of q_k . H q_k, beta_k and sc_k = 1 / beta_k from its
+// chunk sums of |q_k|^2 (norms[k & 1]; sc_0 is given); each work group adds them
+// itself and the cluster's first one stores them.  norms[(k + 1) & 1][c] =
+// |q_{k+1}|^2 over chunk c.  One launch in place of dot, sum, update, sum and
+// scale: 83 us of a step of 32 mixed clusters (FP64) became 31.
+struct BStep {
+    const uint32_t* tile_begin;    // first tile of each cluster, and its tile count
+    const uint32_t* tile_count;
+    const uint32_t* chunk_begin;
+    const double* dots;
+    double* norms[2];
+    double *alpha, *beta, *sc;
+    int ld, koff, kmax;
+};
+__device__ __forceinline__ double brange_sum(const double* v, uint32_t n) {
+    __shared__ double ws[kRed / 64];
+    double acc = 0.0;
+    for (uint32_t i = threadIdx.x; i < n; i += kRed) acc += v[i];
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1) acc += __shfl_xor(acc, m);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    return ((ws[0] + ws[1]) + ws[2]) + ws[3];
+}
 template <typename T>
-__global__ __launch_bounds__(kRed) void k_bupdate(const BChunk* ch, const BProb* probs, const BCtl* ctl,
-                                                  const double* alpha, const double* beta, int ld, T* w, const T* v,
-                                                  const T* vp, double* partial) {
-    __shared__ double red[kRed];
+__global__ __launch_bounds__(kRed) void k_bupdate(const BChunk* ch, const BProb* probs, const BCtl* ctl, const BStep b,
+                                                  T* __restrict__ w, const T* __restrict__ q,
+                                                  const T* __restrict__ qp) {
     const BChunk c = ch[blockIdx.x];
     const BCtl st = ctl[c.prob];
-    if (st.done) return;
-    const double a = alpha[(size_t)c.prob * ld + st.k], bt = beta[(size_t)c.prob * ld + st.k];
-    const uint64_t off = probs[c.prob].off;
+    const int k = st.k + b.koff;
+    if (st.done || k >= b.kmax) return;
+    const size_t row = (size_t)c.prob * b.ld;
+    const double dot = brange_sum(b.dots + b.tile_begin[c.prob], b.tile_count[c.prob]);
+    double a, cc = 0.0, bk = 0.0;
+    if (k > 0) {
+        const uint32_t c0 = b.chunk_begin[c.prob];
+        bk = sqrt(brange_sum(b.norms[k & 1] + c0, b.chunk_begin[c.prob + 1] - c0));
+        a = 1.0 / bk;
+        cc = bk * b.sc[row + k - 1];
+    } else {
+        a = b.sc[row];
+    }
+    const double ak = a * a * dot, bb = ak * a;
+    if (c.begin == 0 && threadIdx.x == 0) {
+        b.alpha[row + k] = ak;
+        if (k > 0) {
+            b.beta[row + k] = bk;
+            b.sc[row + k] = a;
+        }
+    }
+    // chunks begin at multiples of 4096 of a 64-element aligned vector: 16-byte loads
+    constexpr int N = 16 / sizeof(T);
+    typedef T V __attribute__((ext_vector_type(N)));
+    const uint64_t off = probs[c.prob].off + c.begin;
+    const uint32_t n = (uint32_t)(c.end - c.begin), nv = n / N;
+    V* wv = reinterpret_cast<V*>(w + off);
+    const V* qv = reinterpret_cast<const V*>(q + off);
+    const V* pv = reinterpret_cast<const V*>(qp + off);
     double acc = 0.0;
-    for (uint64_t i = c.begin + threadIdx.x; i < c.end; i += blockDim.x) {
-        const T r = (T)((double)w[off + i] - a * (double)v[off + i] - bt * (double)vp[off + i]);
+#pragma unroll 4
+    for (uint32_t i = threadIdx.x; i < nv; i += kRed) {
+        const V w0 = wv[i], q0 = qv[i], p0 = pv[i];
+        V r;
+#pragma unroll
+        for (int e = 0; e < N; ++e) {
+            r[e] = lanczos_recurrence<T>(w0[e], T(0), q0[e], p0[e], a, bb, cc);
+            acc += (double)r[e] * (double)r[e];
+        }
+        wv[i] = r;
+    }
+    for (uint32_t i = nv * N + threadIdx.x; i < n; i += kRed) {
+        const T r = lanczos_recurrence<T>(w[off + i], T(0), q[off + i], qp[off + i], a, bb, cc);
         w[off + i] = r;
         acc += (double)r * (double)r;
     }
-    acc = bsum(acc, red);
-    if (threadIdx.x == 0) partial[blockIdx.x] = acc;
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1) acc += __shfl_xor(acc, m);
+    __shared__ double ws[kRed / 64];
+    if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) b.norms[(k + 1) & 1][blockIdx.x] = ((ws[0] + ws[1]) + ws[2]) + ws[3];
 }
 
-// v *= 1 / s[p * ld + k + koff] (or 1 / norm0 when norm is set)
-template <typename T>
-__global__ __launch_bounds__(kRed) void k_bscale(const BChunk* ch, const BProb* probs, const BCtl* ctl, const double* s,
-                                                 int ld, int koff, int use_norm, T* v) {
+// v *= 1 / norm0
+__global__ __launch_bounds__(kRed) void k_bscale(const BChunk* ch, const BProb* probs, const BCtl* ctl, double* v) {
     const BChunk c = ch[blockIdx.x];
     const BCtl st = ctl[c.prob];
     if (st.done) return;
-    const double inv = 1.0 / (use_norm ? st.norm0 : s[(size_t)c.prob * ld + st.k + koff]);
+    const double inv = 1.0 / st.norm0;
     const uint64_t off = probs[c.prob].off;
-    for (uint64_t i = c.begin + threadIdx.x; i < c.end; i += blockDim.x) v[off + i] = (T)((double)v[off + i] * inv);
+    for (uint64_t i = c.begin + threadIdx.x; i < c.end; i += blockDim.x) v[off + i] *= inv;
 }
 
-// One block per cluster: sum its chunk partials in order.
-// mode 0: alpha[k] = sum; 1: beta[k+1] = sqrt(sum); 2: norm0 = sqrt(sum).
-__global__ __launch_bounds__(kRed) void k_bfinal(const uint32_t* ch_begin, const double* partial, BCtl* ctl,
-                                                 double* alpha, double* beta, int ld, int mode, uint32_t* err) {
+// One block per cluster: norm0 = sqrt of the sum of its chunk partials, and
+// sc[0] = 1 / norm0 (sc != NULL).
+__global__ __launch_bounds__(kRed) void k_bnorm0(const uint32_t* ch_begin, const double* partial, BCtl* ctl,
+                                                 double* sc, int ld, uint32_t* err) {
     __shared__ double red[kRed];
     const uint32_t p = blockIdx.x;
     BCtl* st = ctl + p;
@@ -256,17 +370,9 @@ __global__ __launch_bounds__(kRed) void k_bfinal(const uint32_t* ch_begin, const
     for (uint32_t c = ch_begin[p] + threadIdx.x; c < ch_begin[p + 1]; c += blockDim.x) acc += partial[c];
     acc = bsum(acc, red);
     if (threadIdx.x == 0) {
-        const int k = st->k;
-        double v = acc;
-        if (mode == 0) {
-            alpha[(size_t)p * ld + k] = v;
-        } else {
-            v = sqrt(acc);
-            if (mode == 1)
-                beta[(size_t)p * ld + k + 1] = v;
-            else
-                st->norm0 = v;
-        }
+        const double v = sqrt(acc);
+        st->norm0 = v;
+        if (sc) sc[(size_t)p * ld] = 1.0 / v;
         if (!isfinite(v)) atomicOr(err, kErrNonFinite);
     }
 }
@@ -282,45 +388,54 @@ __global__ void k_binit(BCtl* ctl, double* beta, int ld, uint32_t n) {
     c.theta = 0.0;
     c.resid = 0.0;
     c.norm0 = 0.0;
-    c.theta_prev = 0.0;
     ctl[p] = c;
     beta[(size_t)p * ld] = 0.0;
 }
 
-// One block per cluster: lowest eigenpair of its T_k, convergence test, step
-// counter.  Row p of svec receives the eigenvector.
-__global__ __launch_bounds__(kTriBlock) void k_btridiag(BCtl* ctl, const double* alpha, const double* beta, double* svec,
-                                                   int ld, double tol, int max_iter, uint32_t* err) {
-    const uint32_t p = blockIdx.x;
-    BCtl* st = ctl + p;
-    if (st->done) return;
+// Ritz pairs of a block of steps of every cluster: work group (t, p) the pair of
+// step ctl[p].k + t of cluster p (tridiag.h).
+__global__ __launch_bounds__(kTriBlock) void k_britz_block(const BCtl* ctl, const uint32_t* ch_begin,
+                                                           const double* norm0, const double* norm1,
+                                                           const double* alpha, double* beta, double* theta,
+                                                           double* resid, int ld, int max_iter) {
+    const uint32_t p = blockIdx.y;
+    const BCtl* st = ctl + p;
+    const int k = st->k + blockIdx.x + 1;
+    if (st->done || k > max_iter) return;
     __shared__ TriShared<kBatchMaxIter> S;
-    const int k = st->k + 1;
-    const double* be = beta + (size_t)p * ld;
-    double hint_lo = 0.0, hint_hi = 0.0;
-    if (k >= 3) ritz_hint(st->theta, st->theta_prev, &hint_lo, &hint_hi);
-    const double theta = tridiag_min_pair(S, alpha + (size_t)p * ld, be, k, hint_lo, hint_hi);
-    double* z = svec + (size_t)p * ld;
-    for (int i = threadIdx.x; i < k; i += blockDim.x) z[i] = S.z[i];
-    if (threadIdx.x == 0) {
-        const double bk1 = be[k];
-        const double resid = fabs(bk1 * S.z[k - 1]);
-        st->theta_prev = st->theta;
-        st->theta = theta;
-        st->resid = resid;
-        st->k = k;
-        const bool breakdown = !(bk1 > 1e-14 * fmax(1.0, fabs(theta)));
-        if (!isfinite(theta) || !isfinite(bk1)) {
-            atomicOr(err, kErrNonFinite);
-            st->done = 1;
-        }
-        if (breakdown || resid <= tol * fmax(fabs(theta), 1e-300)) {
-            st->converged = 1;
-            st->breakdown = breakdown ? 1 : 0;
-            st->done = 1;
-        }
-        if (k >= max_iter) st->done = 1;
+    __shared__ double red[kRed];
+    const size_t row = (size_t)p * ld;
+    double bk1;
+    if (blockIdx.x + 1 == gridDim.x || k == max_iter) {   // no update after this step has formed beta_{k+1}
+        const double* v = (k & 1) ? norm1 : norm0;
+        double acc = 0.0;
+        for (uint32_t c = ch_begin[p] + threadIdx.x; c < ch_begin[p + 1]; c += blockDim.x) acc += v[c];
+        bk1 = sqrt(bsum(acc, red));
+        if (threadIdx.x == 0) beta[row + k] = bk1;
+    } else {
+        bk1 = beta[row + k];
     }
+    ritz_block_step(S, st, (int)blockIdx.x, alpha + row, beta + row, bk1, theta + row, resid + row);
+}
+
+__global__ void k_britz_end(BCtl* ctl, uint32_t n, int steps, const double* alpha, const double* beta,
+                            const double* theta, const double* resid, int ld, double tol, int max_iter, uint32_t* err) {
+    const uint32_t p = blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= n || ctl[p].done) return;
+    const size_t row = (size_t)p * ld;
+    ritz_block_end(ctl + p, steps, alpha + row, beta + row, theta + row, resid + row, tol, max_iter, err,
+                   kErrNonFinite);
+}
+
+// Eigenvector of every cluster's last T_k into row p of svec.
+__global__ __launch_bounds__(kTriBlock) void k_britz_vector(const BCtl* ctl, const double* alpha, const double* beta,
+                                                            double* svec, int ld) {
+    __shared__ TriShared<kBatchMaxIter> S;
+    const size_t row = (size_t)blockIdx.x * ld;
+    const int k = ctl[blockIdx.x].k;
+    if (k < 1) return;
+    tridiag_min_pair(S, alpha + row, beta + row, k, 0.0, 0.0);
+    for (int i = threadIdx.x; i < k; i += blockDim.x) svec[row + i] = S.z[i];
 }
 
 // ---- FP64 refinement of the Ritz vectors (storage FP32 or FP64)
@@ -335,14 +450,15 @@ __global__ void k_bregen_init(BCtl* ctl, int* kfin, uint32_t n) {
     ctl[p].done = k > 0 ? 0 : 1;
 }
 
-// y += s_k v_k (FP64) for every live cluster, s = row p of svec (eigenvector of T_kfin).
+// y += s_k sc_k q_k (FP64) for every live cluster, s = row p of svec (eigenvector of T_kfin).
 template <typename T>
 __global__ __launch_bounds__(kRed) void k_baxpy_ritz(const BChunk* ch, const BProb* probs, const BCtl* ctl,
-                                                     const double* svec, int ld, const T* v, double* y) {
+                                                     const double* svec, const double* sc, int ld, const T* v,
+                                                     double* y) {
     const BChunk c = ch[blockIdx.x];
     const BCtl st = ctl[c.prob];
     if (st.done) return;
-    const double sk = svec[(size_t)c.prob * ld + st.k];
+    const double sk = svec[(size_t)c.prob * ld + st.k] * sc[(size_t)c.prob * ld + st.k];
     const uint64_t off = probs[c.prob].off;
     for (uint64_t i = c.begin + threadIdx.x; i < c.end; i += blockDim.x) y[off + i] += sk * (double)v[off + i];
 }
@@ -354,24 +470,21 @@ __global__ void k_bregen_mark(BCtl* ctl, const int* kfin, uint32_t n) {
     if (ctl[p].k + 1 >= kfin[p]) ctl[p].done = 1;
 }
 
-// v_{k+1} from w = H v_k with the stored alpha_k, beta_k, beta_{k+1}: the same
-// two roundings as the run (recurrence, then scaling), so the vectors are the
-// run's bit for bit.
+// q_{k+1} from w = H q_k with the stored alpha_k, beta_k and scales: the run's
+// recurrence, so the vectors are the run's bit for bit.
 template <typename T>
 __global__ __launch_bounds__(kRed) void k_bregen_update(const BChunk* ch, const BProb* probs, const BCtl* ctl,
-                                                        const double* alpha, const double* beta, int ld, T* w,
-                                                        const T* v, const T* vp) {
+                                                        const double* alpha, const double* beta, const double* sc,
+                                                        int ld, T* w, const T* q, const T* qp) {
     const BChunk c = ch[blockIdx.x];
     const BCtl st = ctl[c.prob];
     if (st.done) return;
     const size_t row = (size_t)c.prob * ld;
-    const double a = alpha[row + st.k], bt = beta[row + st.k];
-    const double inv = 1.0 / beta[row + st.k + 1];
+    const double a = sc[row + st.k], b = alpha[row + st.k] * a;
+    const double cc = st.k > 0 ? beta[row + st.k] * sc[row + st.k - 1] : 0.0;
     const uint64_t off = probs[c.prob].off;
-    for (uint64_t i = c.begin + threadIdx.x; i < c.end; i += blockDim.x) {
-        const T r = (T)((double)w[off + i] - a * (double)v[off + i] - bt * (double)vp[off + i]);
-        w[off + i] = (T)((double)r * inv);
-    }
+    for (uint64_t i = c.begin + threadIdx.x; i < c.end; i += blockDim.x)
+        w[off + i] = lanczos_recurrence<T>(w[off + i], T(0), q[off + i], qp[off + i], a, b, cc);
 }
 
 __global__ void k_bregen_next(BCtl* ctl, uint32_t n) {
@@ -419,11 +532,13 @@ __global__ __launch_bounds__(kRed) void k_bresid(const BChunk* ch, const BProb* 
 
 size_t al256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-constexpr size_t kBatchLds = 159 * 1024;   // dynamic LDS limit: 160 KiB less the static queue slot
+constexpr size_t kBatchLds = 159 * 1024;   // dynamic LDS limit: 160 KiB less the kernels' static words
 
 template <typename T, int BLOCK>
 pdz_status set_batch_lds() {
     PDZ_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_batch_hv<T, BLOCK>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBatchLds));
+    PDZ_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&k_batch_rows<T, BLOCK>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBatchLds));
     return ok();
 }
@@ -456,8 +571,9 @@ struct pdz_batch_s {
     BChunk* d_chunks = nullptr;
     uint32_t* d_chunk_begin = nullptr;   // n + 1
     uint32_t nchunks = 0;
-    unsigned* d_queue = nullptr;
+    uint32_t* d_tile_begin = nullptr;    // n first tiles, then n tile counts, for the current plan
     uint64_t max_D_dn = 0;
+    bool rows_form = false;              // every tile fits the one-pass form (k_batch_rows)
     pdz_batch_plan plan{0, 0, 0, 0};
     pdz_batch_plan tiles_for{-1, -1, -1, -1};
 };
@@ -467,8 +583,10 @@ namespace {
 pdz_batch_plan resolve(const pdz_batch_s* b) {
     pdz_batch_plan p = b->plan;
     if (p.tile_elems == 0) p.tile_elems = 4096;
-    if (p.block == 0) p.block = 256;
-    if (p.wgs_per_cu == 0) p.wgs_per_cu = 4;
+    // the fastest of the search space in FP64 on 32 mixed clusters (108 us; 256
+    // threads and four groups per CU 118), within 5 % of it in FP32
+    if (p.block == 0) p.block = 512;
+    if (p.wgs_per_cu == 0) p.wgs_per_cu = 8;
     if (p.order == 0) p.order = 1;
     return p;
 }
@@ -483,6 +601,38 @@ bool plan_ok(const pdz_batch_s* b, const pdz_batch_plan& p) {
     return te && bl && wg && od && fits;
 }
 
+// Rows per tile of a cluster: about tile_elems elements, whole groups of
+// kBatchRV rows in the one-pass form, no more than the LDS holds.
+uint64_t tile_rows(const pdz_batch_s* b, const pdz_problem q, int tile_elems) {
+    const uint64_t Dn = q->dn.D;
+    uint64_t rows = (uint64_t)tile_elems / Dn;
+    if (b->rows_form) {
+        rows = rows / kBatchRV * kBatchRV;
+        return rows < kBatchRV ? kBatchRV : rows;
+    }
+    const uint64_t cap = (160 * 1024 - kMaxCoef * 8 - 1024) / 8;   // elements, FP64 worst case
+    if (rows * Dn > cap) rows = cap / Dn;
+    return rows < 1 ? 1 : rows;
+}
+
+// Whether every tile fits the one-pass form: four rows of the widest cluster in
+// FP64, byte offsets of a cluster's elements in 32 bits.
+bool rows_form_fits(const pdz_batch_s* b) {
+    for (const pdz_problem q : b->problems)
+        if (q->D > 0xFFFFFFFFull / 8) return false;
+    return kMaxCoef * 8 + (b->max_D_dn + 1) * kBatchRV * 8 <= kBatchLds;
+}
+
+// Most tiles of any plan (the smallest tiles).
+size_t max_tiles(const pdz_batch_s* b) {
+    size_t n = 0;
+    for (const pdz_problem q : b->problems) {
+        const uint64_t rows = tile_rows(b, q, 1024);
+        n += (size_t)((q->up.D + rows - 1) / rows);
+    }
+    return n;
+}
+
 // Tiles: rows of each cluster in groups of about tile_elems elements;
 // order 1 = largest clusters first, 2 = cluster order.
 pdz_status build_tiles(pdz_batch_s* b, const pdz_batch_plan& p) {
@@ -492,14 +642,12 @@ pdz_status build_tiles(pdz_batch_s* b, const pdz_batch_plan& p) {
     if (p.order == 1)
         std::stable_sort(idx.begin(), idx.end(), [&](int a, int c) { return b->problems[a]->D > b->problems[c]->D; });
     std::vector<BTile> tiles;
-    const size_t lds_rows_cap = (160 * 1024 - kMaxCoef * 8 - 1024) / 8;   // elements, FP64 worst case
+    std::vector<uint32_t> range(2 * (size_t)b->n);
     for (int i : idx) {
         const pdz_problem q = b->problems[i];
-        const uint64_t Dn = q->dn.D, Du = q->up.D;
-        uint64_t rows = (uint64_t)p.tile_elems / Dn;
-        if (rows < 1) rows = 1;
-        if (rows * Dn > lds_rows_cap) rows = lds_rows_cap / Dn;
-        if (rows < 1) return fail(PDZ_ERANGE, "a cluster row does not fit the batched kernel's LDS");
+        const uint64_t Du = q->up.D;
+        const uint64_t rows = tile_rows(b, q, p.tile_elems);
+        range[i] = (uint32_t)tiles.size();
         for (uint64_t u0 = 0; u0 < Du; u0 += rows) {
             BTile t;
             t.prob = (uint32_t)i;
@@ -508,60 +656,65 @@ pdz_status build_tiles(pdz_batch_s* b, const pdz_batch_plan& p) {
             t.pad = 0;
             tiles.push_back(t);
         }
+        range[b->n + i] = (uint32_t)tiles.size() - range[i];
     }
     if (b->d_tiles) (void)hipFree(b->d_tiles);
     b->d_tiles = nullptr;
     PDZ_HIP(hipMalloc(&b->d_tiles, tiles.size() * sizeof(BTile)));
     PDZ_HIP(hipMemcpy(b->d_tiles, tiles.data(), tiles.size() * sizeof(BTile), hipMemcpyHostToDevice));
+    PDZ_HIP(hipMemcpy(b->d_tile_begin, range.data(), range.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
     b->ntiles = (uint32_t)tiles.size();
     b->tiles_for = p;
     return ok();
 }
 
+// dotp: NULL, or one partial sum of x . y per tile
 template <typename T>
 pdz_status batch_hv_launch(pdz_batch_s* b, const pdz_batch_plan& p, const T* x, T* y, hipStream_t s, const int* done,
-                           int dstride) {
+                           int dstride, double* dotp) {
     DeviceCtx* ctx = nullptr;
     pdz_status st = device_ctx(&ctx);
     if (st != PDZ_OK) return st;
-    size_t max_tile = 0;
-    for (int i = 0; i < b->n; ++i) {
-        const uint64_t Dn = b->problems[i]->dn.D;
-        uint64_t rows = (uint64_t)p.tile_elems / Dn;
-        if (rows < 1) rows = 1;
-        const uint64_t Du = b->problems[i]->up.D;
-        if (rows > Du) rows = Du;
-        max_tile = std::max<size_t>(max_tile, rows * Dn);
+    size_t max_tile = 0;   // elements
+    for (const pdz_problem q : b->problems) {
+        const uint64_t rows = std::min<uint64_t>(tile_rows(b, q, p.tile_elems), q->up.D);
+        const size_t n = b->rows_form ? (size_t)(rows + kBatchRV - 1) / kBatchRV * kBatchRV * (q->dn.D + 1)
+                                      : (size_t)rows * q->dn.D;
+        max_tile = std::max(max_tile, n);
     }
-    const size_t lds = kMaxCoef * sizeof(T) + max_tile * sizeof(T);
-    const unsigned grid = (unsigned)(ctx->cu_count * p.wgs_per_cu);
-    hipLaunchKernelGGL(k_queue_reset, dim3(1), dim3(1), 0, s, b->d_queue);
-    if (p.block == 1024)
-        hipLaunchKernelGGL((k_batch_hv<T, 1024>), dim3(grid), dim3(1024), lds, s, b->d_probs, b->d_tiles, b->ntiles,
-                           b->d_queue, done, dstride, x, y);
-    else if (p.block == 512)
-        hipLaunchKernelGGL((k_batch_hv<T, 512>), dim3(grid), dim3(512), lds, s, b->d_probs, b->d_tiles, b->ntiles,
-                           b->d_queue, done, dstride, x, y);
-    else
-        hipLaunchKernelGGL((k_batch_hv<T, 256>), dim3(grid), dim3(256), lds, s, b->d_probs, b->d_tiles, b->ntiles,
-                           b->d_queue, done, dstride, x, y);
+    const size_t lds = (kMaxCoef + max_tile) * sizeof(T);
+    const dim3 grid(std::min<unsigned>((unsigned)(ctx->cu_count * p.wgs_per_cu), b->ntiles)), block((unsigned)p.block);
+    const auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, lds, s, b->d_probs, b->d_tiles, b->ntiles, done, dstride, dotp, x, y);
+    };
+    if (b->rows_form) {
+        if (p.block == 1024) launch(k_batch_rows<T, 1024>);
+        else if (p.block == 512) launch(k_batch_rows<T, 512>);
+        else launch(k_batch_rows<T, 256>);
+    } else {
+        if (p.block == 1024) launch(k_batch_hv<T, 1024>);
+        else if (p.block == 512) launch(k_batch_hv<T, 512>);
+        else launch(k_batch_hv<T, 256>);
+    }
     PDZ_HIP(hipGetLastError());
     return ok();
 }
 
 pdz_status batch_hv_any(pdz_batch_s* b, pdz_dtype dt, const void* x, void* y, hipStream_t s, const int* done,
-                        int dstride) {
+                        int dstride, double* dotp = nullptr) {
     const pdz_batch_plan p = resolve(b);
     pdz_status st = build_tiles(b, p);
     if (st != PDZ_OK) return st;
     if (dt == PDZ_F64)
         return batch_hv_launch<double>(b, p, static_cast<const double*>(x), static_cast<double*>(y), s, done,
-                                       dstride);
-    return batch_hv_launch<float>(b, p, static_cast<const float*>(x), static_cast<float*>(y), s, done, dstride);
+                                       dstride, dotp);
+    return batch_hv_launch<float>(b, p, static_cast<const float*>(x), static_cast<float*>(y), s, done, dstride,
+                                  dotp);
 }
 
 struct BLayout {
-    size_t vec = 0, buf[3] = {0, 0, 0}, alpha = 0, beta = 0, svec = 0, partial = 0, ctl = 0, total = 0;
+    size_t vec = 0, buf[3] = {0, 0, 0}, alpha = 0, beta = 0, sc = 0, theta = 0, resid = 0, svec = 0, partial = 0,
+           norms[2] = {0, 0}, dots = 0, ctl = 0, total = 0;
     size_t y = 0, hy = 0, kfin = 0, eref = 0;   // refinement (refine == 1)
     int ld = 0;
 };
@@ -575,16 +728,18 @@ BLayout blayout(const pdz_batch_s* b, const pdz_lanczos_opts* o) {
         L.buf[i] = off;
         off += L.vec;
     }
-    L.ld = 2 * (o->max_iter + 8);
+    L.ld = o->max_iter + 8;
     const size_t per = (size_t)L.ld * b->n * 8;
-    L.alpha = off;
-    off += al256(per);
-    L.beta = off;
-    off += al256(per);
-    L.svec = off;
-    off += al256(per);
-    L.partial = off;
-    off += al256((size_t)b->nchunks * 8);
+    for (size_t* a : {&L.alpha, &L.beta, &L.sc, &L.theta, &L.resid, &L.svec}) {
+        *a = off;
+        off += al256(per);
+    }
+    for (size_t* a : {&L.partial, &L.norms[0], &L.norms[1]}) {
+        *a = off;
+        off += al256((size_t)b->nchunks * 8);
+    }
+    L.dots = off;
+    off += al256(max_tiles(b) * 8);
     L.ctl = off;
     off += al256((size_t)b->n * sizeof(BCtl));
     if (o->refine) {
@@ -608,44 +763,63 @@ pdz_status batch_lanczos_run(pdz_batch_s* b, const pdz_lanczos_opts* o, char* ws
     for (int i = 0; i < 3; ++i) buf[i] = reinterpret_cast<T*>(ws + L.buf[i]);
     double* alpha = reinterpret_cast<double*>(ws + L.alpha);
     double* beta = reinterpret_cast<double*>(ws + L.beta);
+    double* sc = reinterpret_cast<double*>(ws + L.sc);
+    double* theta = reinterpret_cast<double*>(ws + L.theta);
+    double* resid = reinterpret_cast<double*>(ws + L.resid);
     double* svec = reinterpret_cast<double*>(ws + L.svec);
     double* partial = reinterpret_cast<double*>(ws + L.partial);
     BCtl* ctl = reinterpret_cast<BCtl*>(ws + L.ctl);
     const int ld = L.ld;
-    const dim3 nch(b->nchunks), np(b->n), blk(kRed);
+    const dim3 nch(b->nchunks), np(b->n), blk(kRed), npg((b->n + 255) / 256), b256(256);
     const pdz_dtype dt = o->storage == PDZ_F64 ? PDZ_F64 : PDZ_F32;
-    // start: v_1 = SplitMix64 vectors normalised per cluster, v_0 = 0
+    BStep bs;
+    bs.tile_begin = b->d_tile_begin;
+    bs.tile_count = b->d_tile_begin + b->n;
+    bs.chunk_begin = b->d_chunk_begin;
+    bs.dots = reinterpret_cast<double*>(ws + L.dots);
+    for (int i = 0; i < 2; ++i) bs.norms[i] = reinterpret_cast<double*>(ws + L.norms[i]);
+    bs.alpha = alpha;
+    bs.beta = beta;
+    bs.sc = sc;
+    bs.ld = ld;
+    bs.koff = 0;
+    bs.kmax = o->max_iter;
+    // start: q_0 = SplitMix64 vectors, sc_0 = 1 / |q_0| per cluster, q_{-1} = 0
+    const auto start = [&]() {
+        hipLaunchKernelGGL(k_bzero<T>, dim3(1024), blk, 0, s, b->total, buf[0], buf[2]);
+        hipLaunchKernelGGL(k_bfill<T>, nch, blk, 0, s, b->d_chunks, b->d_probs, o->seed, buf[0]);
+        hipLaunchKernelGGL(k_bdot<T>, nch, blk, 0, s, b->d_chunks, b->d_probs, ctl, buf[0], buf[0], partial);
+        hipLaunchKernelGGL(k_bnorm0, np, blk, 0, s, b->d_chunk_begin, partial, ctl, sc, ld, err);
+    };
     hipLaunchKernelGGL(k_clear_bits1, dim3(1), dim3(1), 0, s, err, kErrNonFinite);
-    hipLaunchKernelGGL(k_binit, dim3((b->n + 255) / 256), dim3(256), 0, s, ctl, beta, ld, (uint32_t)b->n);
-    hipLaunchKernelGGL(k_bzero<T>, dim3(1024), blk, 0, s, b->total, buf[0], buf[2]);
-    hipLaunchKernelGGL(k_bfill<T>, nch, blk, 0, s, b->d_chunks, b->d_probs, o->seed, buf[0]);
-    hipLaunchKernelGGL(k_bdot<T>, nch, blk, 0, s, b->d_chunks, b->d_probs, ctl, buf[0], buf[0], partial);
-    hipLaunchKernelGGL(k_bfinal, np, blk, 0, s, b->d_chunk_begin, partial, ctl, alpha, beta, ld, 2, err);
-    hipLaunchKernelGGL(k_bscale<T>, nch, blk, 0, s, b->d_chunks, b->d_probs, ctl, beta, ld, 0, 1, buf[0]);
+    hipLaunchKernelGGL(k_binit, npg, b256, 0, s, ctl, beta, ld, (uint32_t)b->n);
+    start();
     PDZ_HIP(hipGetLastError());
     const int* done = &ctl[0].done;
     const int dstride = (int)(sizeof(BCtl) / sizeof(int));
     int period = o->check_every;
     if (period % 3) period += 3 - period % 3;
-    auto step = [&](T* v, T* vp, T* w) -> pdz_status {
-        pdz_status st = batch_hv_any(b, dt, v, w, s, done, dstride);
+    auto step = [&](T* q, T* qp, T* w, int koff) -> pdz_status {
+        pdz_status st = batch_hv_any(b, dt, q, w, s, done, dstride, const_cast<double*>(bs.dots));
         if (st != PDZ_OK) return st;
-        hipLaunchKernelGGL(k_bdot<T>, nch, blk, 0, s, b->d_chunks, b->d_probs, ctl, v, w, partial);
-        hipLaunchKernelGGL(k_bfinal, np, blk, 0, s, b->d_chunk_begin, partial, ctl, alpha, beta, ld, 0, err);
-        hipLaunchKernelGGL(k_bupdate<T>, nch, blk, 0, s, b->d_chunks, b->d_probs, ctl, alpha, beta, ld, w, v, vp,
-                           partial);
-        hipLaunchKernelGGL(k_bfinal, np, blk, 0, s, b->d_chunk_begin, partial, ctl, alpha, beta, ld, 1, err);
-        hipLaunchKernelGGL(k_btridiag, np, dim3(kTriBlock), 0, s, ctl, alpha, beta, svec, ld, o->tol, o->max_iter, err);
-        hipLaunchKernelGGL(k_bscale<T>, nch, blk, 0, s, b->d_chunks, b->d_probs, ctl, beta, ld, 0, 0, w);
-        PDZ_HIP(hipGetLastError());
+        bs.koff = koff;
+        hipLaunchKernelGGL(k_bupdate<T>, nch, blk, 0, s, b->d_chunks, b->d_probs, ctl, bs, w, q, qp);
         return ok();
+    };
+    auto end_block = [&](int steps) {
+        hipLaunchKernelGGL(k_britz_block, dim3((unsigned)steps, (unsigned)b->n), dim3(kTriBlock), 0, s, ctl,
+                           b->d_chunk_begin, bs.norms[0], bs.norms[1], alpha, beta, theta, resid, ld, o->max_iter);
+        hipLaunchKernelGGL(k_britz_end, npg, b256, 0, s, ctl, (uint32_t)b->n, steps, alpha, beta, theta, resid, ld,
+                           o->tol, o->max_iter, err);
     };
     auto enqueue = [&]() -> pdz_status {
         for (int t = 0; t < period; ++t) {
             const int a = t % 3;
-            pdz_status st = step(buf[a], buf[(a + 2) % 3], buf[(a + 1) % 3]);
+            pdz_status st = step(buf[a], buf[(a + 2) % 3], buf[(a + 1) % 3], t % kRitzBlock);
             if (st != PDZ_OK) return st;
+            if ((t + 1) % kRitzBlock == 0 || t + 1 == period) end_block(t % kRitzBlock + 1);
         }
+        PDZ_HIP(hipGetLastError());
         return ok();
     };
     // tiles for the current plan must exist before capture (no allocation inside a graph)
@@ -720,38 +894,34 @@ pdz_status batch_lanczos_run(pdz_batch_s* b, const pdz_lanczos_opts* o, char* ws
         kmax = std::max(kmax, h[i].k);
     }
     if (o->refine && kmax > 0) {
-        // Ritz vector y_p = sum_j s_{p,j} v_{p,j} in FP64 from the regenerated
+        // Ritz vector y_p = sum_j s_{p,j} sc_{p,j} q_{p,j} in FP64 from the regenerated
         // Lanczos vectors, normalised; its FP64 Rayleigh quotient and residual.
         double* y = reinterpret_cast<double*>(ws + L.y);
         double* hy = reinterpret_cast<double*>(ws + L.hy);
         int* kfin = reinterpret_cast<int*>(ws + L.kfin);
         double* eref = reinterpret_cast<double*>(ws + L.eref);
-        const dim3 npg((b->n + 255) / 256), b256(256);
+        hipLaunchKernelGGL(k_britz_vector, np, dim3(kTriBlock), 0, s, ctl, alpha, beta, svec, ld);
         hipLaunchKernelGGL(k_bregen_init, npg, b256, 0, s, ctl, kfin, (uint32_t)b->n);
-        hipLaunchKernelGGL(k_bzero<T>, dim3(1024), blk, 0, s, b->total, buf[0], buf[2]);
         hipLaunchKernelGGL(k_bzero<double>, dim3(1024), blk, 0, s, b->total, y, hy);
-        hipLaunchKernelGGL(k_bfill<T>, nch, blk, 0, s, b->d_chunks, b->d_probs, o->seed, buf[0]);
-        hipLaunchKernelGGL(k_bdot<T>, nch, blk, 0, s, b->d_chunks, b->d_probs, ctl, buf[0], buf[0], partial);
-        hipLaunchKernelGGL(k_bfinal, np, blk, 0, s, b->d_chunk_begin, partial, ctl, alpha, beta, ld, 2, err);
-        hipLaunchKernelGGL(k_bscale<T>, nch, blk, 0, s, b->d_chunks, b->d_probs, ctl, beta, ld, 0, 1, buf[0]);
+        start();
         for (int j = 0; j < kmax; ++j) {
             const int a = j % 3;
             T* v = buf[a];
             T* vp = buf[(a + 2) % 3];
             T* w = buf[(a + 1) % 3];
-            hipLaunchKernelGGL(k_baxpy_ritz<T>, nch, blk, 0, s, b->d_chunks, b->d_probs, ctl, svec, ld, v, y);
+            hipLaunchKernelGGL(k_baxpy_ritz<T>, nch, blk, 0, s, b->d_chunks, b->d_probs, ctl, svec, sc, ld, v, y);
             if (j + 1 >= kmax) break;
             hipLaunchKernelGGL(k_bregen_mark, npg, b256, 0, s, ctl, kfin, (uint32_t)b->n);
             st = batch_hv_any(b, dt, v, w, s, done, dstride);
             if (st != PDZ_OK) return st;
-            hipLaunchKernelGGL(k_bregen_update<T>, nch, blk, 0, s, b->d_chunks, b->d_probs, ctl, alpha, beta, ld, w,
-                               v, vp);
+            hipLaunchKernelGGL(k_bregen_update<T>, nch, blk, 0, s, b->d_chunks, b->d_probs, ctl, alpha, beta, sc,
+                               ld, w, v, vp);
             hipLaunchKernelGGL(k_bregen_next, npg, b256, 0, s, ctl, (uint32_t)b->n);
         }
         hipLaunchKernelGGL(k_bregen_reopen, npg, b256, 0, s, ctl, kfin, (uint32_t)b->n);
         hipLaunchKernelGGL(k_bdot<double>, nch, blk, 0, s, b->d_chunks, b->d_probs, ctl, y, y, partial);
-        hipLaunchKernelGGL(k_bfinal, np, blk, 0, s, b->d_chunk_begin, partial, ctl, alpha, beta, ld, 2, err);
-        hipLaunchKernelGGL(k_bscale<double>, nch, blk, 0, s, b->d_chunks, b->d_probs, ctl, beta, ld, 0, 1, y);
+        hipLaunchKernelGGL(k_bnorm0, np, blk, 0, s, b->d_chunk_begin, partial, ctl, (double*)nullptr, ld, err);
+        hipLaunchKernelGGL(k_bscale, nch, blk, 0, s, b->d_chunks, b->d_probs, ctl, y);
         st = batch_hv_any(b, PDZ_F64, y, hy, s, done, dstride);
         if (st != PDZ_OK) return st;
         hipLaunchKernelGGL(k_bdot<double>, nch, blk, 0, s, b->d_chunks, b->d_probs, ctl, y, hy, partial);
@@ -816,7 +986,7 @@ pdz_status pdz_batch_create(const pdz_problem* problems, int32_t n, pdz_batch* o
         hp[i].coef64 = q->d_coef64;
         hp[i].coef32 = q->d_coef32;
         hp[i].ncoef = (int)q->coef_host.size();
-        hp[i].pad = 0;
+        hp[i].dn_max = q->dn.max_hops;
         b->max_D_dn = std::max<uint64_t>(b->max_D_dn, q->dn.D);
         cb[i] = (uint32_t)chunks.size();
         for (uint64_t s0 = 0; s0 < q->D; s0 += kChunk) {
@@ -848,9 +1018,10 @@ pdz_status pdz_batch_create(const pdz_problem* problems, int32_t n, pdz_batch* o
     BCK(hipMemcpy(b->d_chunks, chunks.data(), chunks.size() * sizeof(BChunk), hipMemcpyHostToDevice));
     BCK(hipMalloc(&b->d_chunk_begin, (n + 1) * sizeof(uint32_t)));
     BCK(hipMemcpy(b->d_chunk_begin, cb.data(), (n + 1) * sizeof(uint32_t), hipMemcpyHostToDevice));
-    BCK(hipMalloc(&b->d_queue, 256));
+    BCK(hipMalloc(&b->d_tile_begin, 2 * (size_t)n * sizeof(uint32_t)));
 #undef BCK
     if (!plan_ok(b, resolve(b))) return cleanup(fail(PDZ_ERANGE, "a cluster row does not fit the batched kernel's LDS"));
+    b->rows_form = rows_form_fits(b);
     pdz_status st = build_tiles(b, resolve(b));
     if (st != PDZ_OK) return cleanup(st);
     *out = b;
@@ -867,7 +1038,7 @@ pdz_status pdz_batch_destroy(pdz_batch b) {
     if (b->d_tiles) (void)hipFree(b->d_tiles);
     if (b->d_chunks) (void)hipFree(b->d_chunks);
     if (b->d_chunk_begin) (void)hipFree(b->d_chunk_begin);
-    if (b->d_queue) (void)hipFree(b->d_queue);
+    if (b->d_tile_begin) (void)hipFree(b->d_tile_begin);
     (void)hipSetDevice(prev);
     delete b;
     return ok();
