@@ -1470,8 +1470,15 @@ HvPlan two_pass_plan(const pdz_problem_s* p, pdz_dtype dt) {
         d.down = 1;
     else
         d.down = 2;
+    // Up pass, 128 columns: 16-byte lanes in FP32 (four rows of a chunk per wave),
+    // batches of 16 hops in FP64; batches of 8 where offsets need 64 bits.  H.v
+    // in us with these against batches of 8 and narrower lanes: 4x4 next-nearest
+    // 8+8 2290 against 2680 (FP32), 4620 / 4790 (FP64); 4x4 7+7 1172 / 1430,
+    // 2515 / 2630; 5x3 6+5 153 / 169, 285 / 308; ring of 14 7+6 89 / 93, 163 /
+    // 178; within 5 % of the fastest plan in every case but rings in FP32
+    // (256 columns: 1037 against 1089 on a ring of 16, 8+7).
     d.up_cw = 128;
-    d.up = 1;
+    d.up = p->D > 0xFFFFFFFFull || p->dn.D < kRowsMinDn ? 1 : dt == PDZ_F32 ? 4 : 3;
     d.map = 3;
     return d;
 }
