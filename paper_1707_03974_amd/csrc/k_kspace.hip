@@ -80,6 +80,11 @@ struct KSpace {
     uint8_t* d_row_kd = nullptr;    // D_up: momentum K - K_up of the row's down strings
     double* d_eps_up = nullptr;     // D_up: band energy of each up string
     uint32_t* d_rows = nullptr;     // nrows: non-empty rows ordered by down momentum
+    // H.v over groups of rows (k_hvk_rows; groups == 0: not used)
+    uint32_t groups[2] = {0, 0};        // FP64, FP32
+    uint32_t* d_groups[2] = {nullptr, nullptr};   // first row of the group in d_rows << 3 | its rows
+    uint16_t* d_gtab = nullptr;     // d_dtab with kz_pos positions and a zero for every slot past the count
+    uint8_t* d_gmax = nullptr;      // N x N: most down moves of one string of (target momentum, q)
 };
 
 namespace {
@@ -695,8 +700,291 @@ __global__ __launch_bounds__(kKBlock) void k_hvk(const KArgs a, const T* __restr
     }
 }
 
+// H.v over groups of up to R target rows of one down momentum, which share
+// their down-move tables: Z_q of the R rows lies side by side in LDS, so one
+// table entry and one 16-byte read serve R elements.  A thread holds E
+// consecutive columns.  Sums run in the order of k_hvk: moves, then slots.
+//
+// A table entry is the LDS byte offset of its source and the sign, placed so
+// that either takes one instruction to get.  The slots past a string's count
+// name a position that holds -0.0, which leaves a sum as it is: the gathers read
+// no counts, and a momentum pair runs to the most moves any of its strings has.
+// Moves that all R rows have are taken without a branch between their loads.
+//
+// Bound by the source-row loads (64 rows a target row at 8+8 sites, a third of
+// them past L2: without them 167 us of 260), so one Z buffer and one move in
+// flight a row, which leave room for 7 waves a SIMD, beat two buffers and two
+// moves (386 us at 4 waves).  4x4 with diagonals, 8+8, K = 0, against one row
+// per work group: FP32 595 -> 260 us, FP64 980 -> 578 us; 5x3 7+7 226 -> 66 us
+// and 249 -> 88 us.
+template <typename T>
+constexpr int kKRows = 16 / (int)sizeof(T);   // R
+// Position of element d in Z: one in five left out, so that the E stores of
+// neighbouring threads (64 bytes apart without it) fall into different banks.
+__host__ __device__ constexpr uint32_t kz_pos(uint32_t d) { return d + (d >> 2); }
+__host__ __device__ constexpr uint32_t kz_len(uint32_t Lmax) { return kz_pos(Lmax - 1) + 2; }   // the last one: -0.0
+constexpr uint32_t kKRowsMaxZ = 2048;   // positions: byte offsets of 15 bits
+// A group takes longer than a row (its q run one after another, R rows at a
+// time), so it pays where rows fill the chip several times over or are long.
+// 4x4 4+4 (114 columns): 1.8 groups a CU 37.7 us by rows and 36.0 by groups;
+// 4x3 6+6 (77 columns): 0.9 groups a CU 18.8 and 32.6; 5x3 7+3 (30 columns): 6
+// groups a CU 77 and 43; 5x3 3+7 (429 columns): 0.4 groups a CU 39.1 and 34.5.
+constexpr int kKRowsMin = 4;              // groups per CU
+constexpr uint32_t kKRowsLong = 256;      // or columns
+
+// One block per (target momentum, q).
+__global__ __launch_bounds__(kKBlock) void k_kgtab(const KArgs a, uint16_t* gtab) {
+    const uint16_t* dtab = static_cast<const uint16_t*>(a.dtab);
+    const uint32_t none = kz_len(a.Lmax) - 1;
+    const int k = blockIdx.x / a.N, q = blockIdx.x % a.N;
+    if (q == 0) return;
+    const uint32_t L = a.Lp[k];
+    const uint64_t tb = a.tb_off[k * a.N + q];
+    const uint8_t* cnt = a.dcnt + a.cnt_off[k] + (uint64_t)q * L;
+    for (uint32_t d = threadIdx.x; d < L; d += kKBlock)
+        for (int s = 0; s < a.slots; ++s) {
+            const uint64_t i = tb + (uint64_t)s * L + d;
+            const uint32_t e = dtab[i], real = s < (int)cnt[d] ? 1u : 0u;
+            const uint32_t pos = real ? kz_pos(e & 0x7FFFu) : none, neg = real & (e >> 15);
+            gtab[i] = (uint16_t)(d & 1u ? neg << 15 | pos << 4 : pos << 4 | neg);
+        }
+}
+
+// +-1 by the top bit of v.
+__device__ __forceinline__ float k_pm1(uint32_t v, float) { return __uint_as_float(0x3F800000u | (v & 0x80000000u)); }
+__device__ __forceinline__ double k_pm1(uint32_t v, double) {
+    return __hiloint2double((int)(0x3FF00000u | (v & 0x80000000u)), 0);
+}
+
+template <typename T, int E>
+__device__ __forceinline__ void kvec_load_global(const T __attribute__((address_space(1)))* p, T (&o)[E]) {
+    constexpr int C = (E * (int)sizeof(T) >= 16) ? 16 / (int)sizeof(T) : E;
+    typedef T ct __attribute__((ext_vector_type(C), aligned(sizeof(T))));
+#pragma unroll
+    for (int c = 0; c < E; c += C) {
+        const ct t = *reinterpret_cast<const __attribute__((address_space(1))) ct*>(p + c);
+#pragma unroll
+        for (int i = 0; i < C; ++i) o[c + i] = t[i];
+    }
+}
+
+template <typename T, int E, int BLOCK>
+__global__ __launch_bounds__(BLOCK, E <= 4 ? 7 : 4) void k_hvk_rows(const KArgs a, const uint32_t* __restrict__ groups,
+                                                         uint32_t ngroups, const uint16_t* __restrict__ gtab,
+                                                         const uint8_t* __restrict__ gmax, const T* __restrict__ x,
+                                                         T* __restrict__ y, const int* skip) {
+    if (skip && *skip) return;
+    constexpr int R = kKRows<T>;
+    typedef T vec __attribute__((ext_vector_type(R)));
+    typedef const T __attribute__((address_space(1)))* GT;
+    extern __shared__ __align__(16) unsigned char kdyn[];
+    const uint32_t zl = kz_len(a.Lmax);
+    const int nmv = (a.N - 1) * a.uslots;
+    vec* Z = reinterpret_cast<vec*>(kdyn);                       // zl
+    uint64_t* smv = reinterpret_cast<uint64_t*>(Z + zl);         // (N-1) x uslots x R up moves
+    uint64_t* stb = smv + R * nmv;                               // N: table of q | its slots << 48
+    int* snv = reinterpret_cast<int*>(stb + a.N);                // N x R: valid up moves per q and row
+    uint8_t* skadd = reinterpret_cast<uint8_t*>(snv + R * a.N);  // N x N
+    const uint32_t per = (ngroups + 7) / 8;
+    const uint32_t gi = (blockIdx.x % 8) * per + blockIdx.x / 8;
+    if (gi >= ngroups) return;
+    const uint32_t first = groups[gi] >> 3, n = groups[gi] & 7u;
+    const int tid = threadIdx.x;
+    const uint64_t none = 0;   // address of a source row | its sign << 63
+    for (int r = 0; r < R; ++r) {
+        const uint64_t src = (uint64_t)a.rows[first + min((uint32_t)r, n - 1)] * nmv;
+        for (int i = tid; i < nmv; i += BLOCK) {
+            const uint64_t e = (uint32_t)r < n ? a.upm[src + i] : kMoveNone;
+            smv[i * R + r] = e == kMoveNone ? none : (uint64_t)(x + (e & ~(1ull << 63))) | (e & 1ull << 63);
+        }
+    }
+    if (tid == 0) Z[zl - 1] = (vec)(T)(-0.0);
+    stage_kadd(skadd, a.kadd, a.N);   // its barrier also publishes smv
+    const int kd = __builtin_amdgcn_readfirstlane((int)a.row_kd[a.rows[first]]);
+    for (int i = tid; i < a.N; i += BLOCK) stb[i] = a.tb_off[kd * a.N + i] | (uint64_t)gmax[kd * a.N + i] << 48;
+    for (int i = tid; i < R * a.N; i += BLOCK) {   // moves of q, 0 when its source rows are empty
+        const int r = i / a.N, q = i - r * a.N;
+        int m = 0;
+        if (q > 0 && a.Ld[skadd[kd * a.N + q]] > 0)
+            while (m < a.uslots && smv[((q - 1) * a.uslots + m) * R + r] != none) ++m;
+        snv[q * R + r] = m;
+    }
+    __syncthreads();
+    const uint32_t L = __builtin_amdgcn_readfirstlane((int)a.Ld[kd]), Lp = __builtin_amdgcn_readfirstlane((int)a.Lp[kd]);
+    const uint32_t d0 = E * (uint32_t)tid;
+    T acc[E][R];
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[e][r] = (T)0;
+    auto next_q = [&](int q0) {   // next q >= q0 with an up move of some row (uniform)
+        int q = q0;
+        for (; q < a.N; ++q) {
+            int any = 0;
+#pragma unroll
+            for (int r = 0; r < R; ++r) any |= snv[q * R + r];
+            if (any) break;
+        }
+        return q;
+    };
+    // Moves of q: sums of the E columns from d (E in range unless PART) of every row.
+    auto sums = [&](int q, uint32_t d, uint32_t Ls, auto part, T (&z)[R][E]) {
+        constexpr bool PART = decltype(part)::value;
+        int nv[R], most = 0, least = a.uslots;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            nv[r] = __builtin_amdgcn_readfirstlane(snv[q * R + r]);
+            most = max(most, nv[r]);
+            least = min(least, nv[r]);
+#pragma unroll
+            for (int e = 0; e < E; ++e) z[r][e] = (T)0;
+        }
+        // Move m of every row (ALL) or of those that have it: the loads, then the sums.
+        const auto add = [&](int m, auto all) {
+            constexpr bool ALL = decltype(all)::value;
+            T v[R][E];
+            uint32_t hi[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const uint64_t e = smv[((q - 1) * a.uslots + m) * R + r];
+                const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)e);
+                hi[r] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(e >> 32));
+                const GT src = (GT)((uint64_t)(hi[r] & 0x7FFFFFFFu) << 32 | lo);
+                if (!ALL && m >= nv[r]) continue;
+                if constexpr (PART) {
+#pragma unroll
+                    for (int i = 0; i < E; ++i) v[r][i] = d + i < Ls ? src[d + i] : (T)0;
+                } else {
+                    kvec_load_global<T, E>(src + d, v[r]);
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (!ALL && m >= nv[r]) continue;
+                const T sg = k_pm1(hi[r], T(0));
+#pragma unroll
+                for (int i = 0; i < E; ++i) z[r][i] = fma(sg, v[r][i], z[r][i]);
+            }
+        };
+        int m = 0;
+        for (; m < least; ++m) add(m, std::true_type{});
+        for (; m < most; ++m) add(m, std::false_type{});
+    };
+    auto put = [&](uint32_t d, const T (&z)[R][E], int e) {
+        vec t;
+#pragma unroll
+        for (int r = 0; r < R; ++r) t[r] = z[r][e];
+        Z[kz_pos(d)] = t;
+    };
+    auto stage = [&](int q) {
+        const uint32_t Ls = __builtin_amdgcn_readfirstlane((int)a.Ld[skadd[kd * a.N + q]]);
+        if (d0 >= Ls) return;
+        T z[R][E];
+        if (Ls >= E) {   // the last thread takes the last E columns, some of them twice
+            const uint32_t d = min(d0, Ls - E);
+            sums(q, d, Ls, std::false_type{}, z);
+#pragma unroll
+            for (int e = 0; e < E; ++e) put(d + e, z, e);
+        } else {
+            sums(q, d0, Ls, std::true_type{}, z);
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                if (d0 + e < Ls) put(d0 + e, z, e);
+        }
+    };
+    auto gather = [&](int q) {
+        if (d0 >= L) return;
+        const uint64_t tn = stb[q];
+        const uint32_t tlo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)tn);
+        const uint32_t thi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(tn >> 32));
+        const int ns = (int)(thi >> 16);
+        const uint32_t* t = reinterpret_cast<const uint32_t*>(gtab + ((uint64_t)(thi & 0xFFFFu) << 32 | tlo));
+        const uint32_t p2 = Lp / 2, o = (uint32_t)tid * (E / 2);
+        auto batch = [&](int s0, auto nb) {   // nb slots: their entries, then their gathers
+            constexpr int SB = decltype(nb)::value;
+            uint32_t ent[SB][E / 2];
+#pragma unroll
+            for (int j = 0; j < SB; ++j) kvec_load_aligned<uint32_t, E / 2>(t + (s0 + j) * p2 + o, ent[j]);
+#pragma unroll
+            for (int j = 0; j < SB; ++j)
+#pragma unroll
+                for (int e = 0; e < E; ++e) {
+                    const uint32_t w = ent[j][e / 2];
+                    const vec v = *(const __attribute__((address_space(3))) vec*)(uintptr_t)(e & 1 ? w >> 16 & 0x7FF0u : w & 0xFFF0u);
+                    const T s = k_pm1(e & 1 ? w : w << 31, T(0));
+#pragma unroll
+                    for (int r = 0; r < R; ++r) acc[e][r] = fma(s, v[r], acc[e][r]);
+                }
+        };
+        int s0 = 0;
+        for (; s0 + 4 <= ns; s0 += 4) batch(s0, std::integral_constant<int, 4>{});
+        if (ns - s0 >= 2) {
+            batch(s0, std::integral_constant<int, 2>{});
+            s0 += 2;
+        }
+        if (s0 < ns) batch(s0, std::integral_constant<int, 1>{});
+    };
+    int q = next_q(1);
+    if (q < a.N) stage(q);
+    __syncthreads();
+    while (q < a.N) {
+        const int qn = next_q(q + 1);
+        gather(q);
+        __syncthreads();
+        if (qn < a.N) stage(qn);
+        __syncthreads();
+        q = qn;
+    }
+    if (d0 >= L) return;
+    const uint64_t dbase = a.dn_off[kd];
+    for (uint32_t r = 0; r < n; ++r) {
+        const uint32_t row = a.rows[first + r];
+        const uint64_t off = a.row_off[row];
+        const double eu = a.eps_up[row] + a.diag_u;
+        T xv[E], yv[E];
+        const bool full = d0 + E <= L;
+        if (full) {
+            kvec_load<T, E>(x + off + d0, xv);
+        } else {
+#pragma unroll
+            for (int e = 0; e < E; ++e) xv[e] = d0 + e < L ? x[off + d0 + e] : (T)0;
+        }
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            T ac = acc[e][0];
+#pragma unroll
+            for (int k = 1; k < R; ++k) ac = r == (uint32_t)k ? acc[e][k] : ac;
+            const T dg = (T)(eu + (d0 + e < L ? a.eps_dn[dbase + d0 + e] : 0.0));
+            yv[e] = dg * xv[e] + (T)a.u_n * ac;
+        }
+        if (full) {
+            kvec_store<T, E>(y + off + d0, yv);
+        } else {
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                if (d0 + e < L) y[off + d0 + e] = yv[e];
+        }
+    }
+}
+
+size_t hvk_rows_lds(uint32_t Lmax, int N, int uslots, size_t es) {
+    const size_t R = 16 / es;
+    return (size_t)kz_len(Lmax) * 16 + R * (size_t)(N - 1) * uslots * 8 + (size_t)N * 8 + R * N * 4 + (size_t)N * N;
+}
+
 size_t hvk_lds_bytes(uint32_t Lmax, size_t es, int N, int uslots) {
     return 2 * hvk_z_bytes(Lmax, es) + (size_t)(N > 1 ? N - 1 : 0) * uslots * 8;
+}
+
+template <typename T, int E, int BLOCK>
+pdz_status set_hvk_rows_lds() {
+    const void* f = reinterpret_cast<const void*>(&k_hvk_rows<T, E, BLOCK>);
+    PDZ_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)hvk_rows_lds(E * BLOCK, kMaxSites, kMaxSites, sizeof(T))));
+    hipFuncAttributes fa{};
+    PDZ_HIP(hipFuncGetAttributes(&fa, f));
+    if (fa.sharedSizeBytes != 0) return fail(PDZ_EHIP, "k_hvk_rows: its LDS does not start at 0");
+    return ok();
 }
 
 template <typename T, int E>
@@ -774,6 +1062,26 @@ template <typename T>
 pdz_status run_hvk(const pdz_problem_s* p, const T* x, T* y, hipStream_t s, const int* skip) {
     const KArgs a = kargs(p);
     if (a.nrows == 0) return ok();
+    const KSpace* ks = p->ks;
+    const int fi = sizeof(T) == 8 ? 0 : 1;
+    if (ks->groups[fi] > 0) {
+        const size_t rl = hvk_rows_lds(ks->Lmax, ks->N, ks->uslots, sizeof(T));
+        const unsigned grid = 8 * ((ks->groups[fi] + 7) / 8);
+        const auto launch = [&](auto kernel, unsigned block) {
+            hipLaunchKernelGGL(kernel, dim3(grid), dim3(block), rl, s, a, ks->d_groups[fi], ks->groups[fi], ks->d_gtab,
+                               ks->d_gmax, x, y, skip);
+        };
+        if (ks->Lmax <= 256)
+            launch(k_hvk_rows<T, 4, 64>, 64);
+        else if (ks->Lmax <= 512)
+            launch(k_hvk_rows<T, 4, 128>, 128);
+        else if (ks->Lmax <= 1024)
+            launch(k_hvk_rows<T, 4, 256>, 256);
+        else
+            launch(k_hvk_rows<T, 8, 256>, 256);
+        PDZ_HIP(hipGetLastError());
+        return ok();
+    }
     const size_t lds = hvk_lds_bytes(p->ks->Lmax, sizeof(T), p->ks->N, p->ks->uslots);
     const bool t16 = p->ks->dtab16;
     switch (hvk_elems(p->ks->Lmax)) {
@@ -809,7 +1117,7 @@ void kspace_free(KSpace* ks) {
     void* ptrs[] = {ks->d_kadd,   ks->d_Ck,      ks->d_Ct,     ks->d_Ld,      ks->d_dn_off, ks->d_tb_off,
                     ks->d_Lp,     ks->d_cnt_off, ks->d_eps,    ks->d_dn_str,  ks->d_eps_dn, ks->d_dcnt,
                     ks->d_dtab,   ks->d_up_str,  ks->d_row_off, ks->d_row_kd, ks->d_eps_up, ks->d_rows,
-                    ks->d_upm};
+                    ks->d_upm,    ks->d_groups[0], ks->d_groups[1], ks->d_gtab,  ks->d_gmax};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
     delete ks;
@@ -822,6 +1130,11 @@ pdz_status kspace_prepare() {
     KP(double, 1) KP(double, 2) KP(double, 4) KP(double, 8) KP(double, 16) KP(double, 32)
     KP(float, 1) KP(float, 2) KP(float, 4) KP(float, 8) KP(float, 16) KP(float, 32)
 #undef KP
+#define KR(E, B)                                                           \
+    if (st == PDZ_OK) st = set_hvk_rows_lds<double, E, B>();               \
+    if (st == PDZ_OK) st = set_hvk_rows_lds<float, E, B>();
+    KR(4, 64) KR(4, 128) KR(4, 256) KR(8, 256)
+#undef KR
     return st;
 }
 
@@ -988,6 +1301,34 @@ pdz_status kspace_build(pdz_problem_s* p, int L1, int L2, const double* eps, int
     for (int k = 0; k < N; ++k) rows.insert(rows.end(), by_kd[k].begin(), by_kd[k].end());
     ks->nrows = rows.size();
     if ((st = upload(&ks->d_rows, rows)) != PDZ_OK) return st;
+    // Groups of rows of one down momentum, where k_hvk_rows takes them.
+    const bool fits = ks->dtab16 && ks->entries < (1ull << 48) && kz_len(ks->Lmax) <= kKRowsMaxZ && ks->slots > 0 && ks->uslots > 0 && N > 1;
+    for (int f = 0; fits && f < 2; ++f) {
+        const uint32_t R = f == 0 ? kKRows<double> : kKRows<float>;
+        std::vector<uint32_t> gr;
+        uint32_t pos = 0;
+        for (int k = 0; k < N; ++k) {
+            for (size_t i = 0; i < by_kd[k].size(); i += R)
+                gr.push_back((uint32_t)(pos + i) << 3 | (uint32_t)std::min<size_t>(R, by_kd[k].size() - i));
+            pos += (uint32_t)by_kd[k].size();
+        }
+        if ((gr.size() < (size_t)kKRowsMin * cu && ks->Lmax <= kKRowsLong) || ks->nrows >= (1u << 29)) continue;
+        if ((st = upload(&ks->d_groups[f], gr)) != PDZ_OK) return st;
+        ks->groups[f] = (uint32_t)gr.size();
+    }
+    if (ks->groups[0] || ks->groups[1]) {
+        std::vector<uint8_t> gm((size_t)N * N, 0);
+        for (int k = 0; k < N; ++k)
+            for (int q = 1; q < N; ++q) {
+                const uint8_t* c = cnt.data() + ks->cnt_off[k] + (uint64_t)q * ks->Lp[k];
+                for (uint32_t d = 0; d < ks->Ld[k]; ++d) gm[(size_t)k * N + q] = std::max(gm[(size_t)k * N + q], c[d]);
+            }
+        if ((st = upload(&ks->d_gmax, gm)) != PDZ_OK) return st;
+        if ((st = alloc(&ks->d_gtab, ks->entries)) != PDZ_OK) return st;
+        hipLaunchKernelGGL(k_kgtab, dim3(N * N), dim3(kKBlock), 0, nullptr, kargs(p), ks->d_gtab);
+        PDZ_HIP(hipGetLastError());
+        PDZ_HIP(hipStreamSynchronize(nullptr));
+    }
     // structural nonzeros: D diagonal entries plus, per row and q, up moves x down moves
     std::vector<uint64_t> mdn((size_t)N * N, 0);   // [momentum][q]: down moves summed over the strings
     for (int k = 0; k < N; ++k)
