@@ -16,14 +16,13 @@ def lib():
     return _lib.load()
 
 
-def _stream_handle(stream=None):
-    import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+_stream_handle = _lib.raw_stream
 
 
 def _dtype_code(dtype):
     import torch
+    if dtype is torch.float32:
+        return PDZ_F32
     if dtype in (torch.float64, "f64", PDZ_F64):
         return PDZ_F64
     if dtype in (torch.float32, "f32", PDZ_F32):
@@ -82,15 +81,15 @@ class Problem:
 
     def hv(self, x, y=None, stream=None):
         """y = H x for a contiguous device tensor x (float64 or float32)."""
-        import torch
-        if not x.is_cuda or not x.is_contiguous() or x.numel() != self.D:
+        D = self.info["D"]
+        if not x.is_cuda or not x.is_contiguous() or x.numel() != D:
             raise ValueError("x must be a contiguous device tensor of D elements")
         if y is None:
+            import torch
             y = torch.empty_like(x)
-        if y.dtype != x.dtype or y.numel() != self.D or not y.is_contiguous():
+        if y.dtype != x.dtype or y.numel() != D or not y.is_contiguous():
             raise ValueError("y must match x")
-        _lib.check(lib().pdz_hv(self._h, _dtype_code(x.dtype), ctypes.c_void_p(x.data_ptr()),
-                                ctypes.c_void_p(y.data_ptr()), _stream_handle(stream)))
+        _lib.check(lib().pdz_hv(self._h, _dtype_code(x.dtype), x.data_ptr(), y.data_ptr(), _stream_handle(stream)))
         return y
 
     def hv_pitched(self, x, pitch, y=None, stream=None):

@@ -185,6 +185,19 @@ def load(path: str = LIB_PATH):
     return lib
 
 
+def raw_stream(stream=None):
+    """hipStream_t of `stream` (a torch stream) or, if None, of the current stream.
+
+    A small H.v is bound by the host: 8-site ring, 4+4, 7.5 us a call when the
+    current stream came as a torch Stream object and every pointer was wrapped in
+    a c_void_p, 4.9 us with the handle read directly and plain integers passed.
+    """
+    if stream is not None:
+        return stream.cuda_stream
+    import torch
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+
+
 def check(status: int, allow=()):
     if status != PDZ_OK and status not in allow:
         msg = load().pdz_last_error()

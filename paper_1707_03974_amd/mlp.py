@@ -11,13 +11,10 @@ from ._lib import PDZ_F64, PDZ_F32
 
 
 def _p(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
-def _s(stream=None):
-    import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return ctypes.c_void_p(s.cuda_stream)
+_s = _lib.raw_stream
 
 
 def param_count():
