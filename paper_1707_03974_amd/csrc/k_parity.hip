@@ -78,6 +78,14 @@ struct ParSpace {
     uint32_t* d_rows_full = nullptr;  // rows of non-palindromic up strings (every down string)
     uint32_t* d_rows_pal = nullptr;   // rows of palindromic up strings
     uint64_t n_full = 0, n_pal = 0;
+    // Palindromic rows, whose sources are found once: per column its string,
+    // full-row columns and kind; its down hops (slot major, pitch Lp); the up
+    // hops of each row (stride pup_stride).  Formats: k_ppal, kPupOff.
+    uint4* d_pinfo = nullptr;
+    uint8_t* d_pcnt = nullptr;
+    uint64_t* d_pell = nullptr;
+    uint64_t* d_pup = nullptr;
+    int pup_stride = 0;
     uint32_t* d_S = nullptr;          // (N+1) x (nmax+1): representatives (palindromes included), Sec. IV.B
     // Scheduled down pass of the full rows (two-pass form): the gather
     // schedule of the column hop table (fcnt, fell), the down string of each
@@ -181,6 +189,11 @@ struct PArgs {
     const uint64_t* row_off;
     const uint8_t* row_pal;
     const uint32_t* uinv;
+    const uint4* pinfo;
+    const uint8_t* pcnt;
+    const uint64_t* pell;
+    const uint64_t* pup;
+    int pup_stride;
     const uint32_t* rows;   // the rows a launch covers
     uint64_t nrows, nlist, Lp;
     double U;
@@ -202,8 +215,39 @@ __device__ __forceinline__ void block_sum_store(double v, double* out) {
     }
 }
 
-// Rows of palindromic up strings (few): one work group per row, threads over
-// its columns (down representatives).
+// An up hop of a palindromic row: source row start, whether the source is an
+// image, amplitude index.
+constexpr uint64_t kPupOff = (1ull << 55) - 1, kPupImage = 1ull << 55;
+constexpr int kPupCoef = 56;
+
+// Tables of the palindromic rows: per column its string, the full-row columns
+// of the string and of its mirror, 1 when it is a palindrome; its down hops as
+// source column | class << 32 | amplitude index << 40, excluded palindromes
+// left out.
+__global__ __launch_bounds__(kPBlock) void k_ppal(const PArgs a, uint4* info, uint8_t* cnt, uint64_t* ell) {
+    for (uint64_t c = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; c < a.Lp; c += (uint64_t)gridDim.x * blockDim.x) {
+        const uint32_t rd = a.dlist[c];
+        info[c] = make_uint4(a.dn_states[rd], a.dcolf[rd], a.dcolf[a.dinv[rd]], a.dcls[rd] == kClsPal ? 1u : 0u);
+        const int n = a.dn_cnt[rd];
+        int kept = 0;
+        for (int h = 0; h < n; ++h) {
+            const uint32_t e = a.dn_ell[(uint64_t)h * a.Ddn + rd];
+            const uint32_t rd2 = e & kTargetMask;
+            const uint8_t cl = a.dcls[rd2];
+            if (cl == kClsPal && !a.pal_in) continue;
+            ell[(uint64_t)kept * a.Lp + c] = a.dcol[cl == kClsImage ? a.dinv[rd2] : rd2] | (uint64_t)cl << 32 |
+                                             (uint64_t)(e >> kTargetBits) << 40;
+            ++kept;
+        }
+        cnt[c] = (uint8_t)kept;
+    }
+}
+
+// Rows of palindromic up strings (few): a work group per kPBlock columns (down
+// representatives) of a row, an element's hops in order, kPHopNB at a time.
+// Few waves, so its time is the chain of dependent loads: entry, operand.  4x4
+// with diagonals, 8+8, P = +1 (70 rows of 6,470 columns): 61 us FP64, 118 us
+// with every hop's class, row and column looked up on the way (four loads deep).
 // With dotp set, work group b writes dotp[b] = its elements' sum of x y.
 template <typename T>
 __global__ __launch_bounds__(kPBlock) void k_hvp(const PArgs a, const T* __restrict__ coef, const T* __restrict__ x,
@@ -214,99 +258,54 @@ __global__ __launch_bounds__(kPBlock) void k_hvp(const PArgs a, const T* __restr
     const uint64_t chunks = (a.Lp + kPBlock - 1) / kPBlock;
     double dsum = 0.0;
     for (uint64_t b = blockIdx.x; b < a.nlist * chunks; b += gridDim.x) {
-        const uint64_t k = a.rows[b / chunks];
+        const uint64_t kk = b / chunks;
+        const uint64_t k = a.rows[kk];
         const uint32_t ru = a.row_rank[k];
         const uint64_t off = a.row_off[k];
-        const uint64_t len = a.row_off[k + 1] - off;
         const uint32_t phu = a.up_states[ru];
         const int nup_h = a.up_cnt[ru];
+        const uint64_t* up = a.pup + kk * (uint64_t)a.pup_stride;
         const uint64_t c = (b % chunks) * kPBlock + threadIdx.x;
-        if (c < len) {
-            const uint32_t rd = a.dlist[c];
-            const T wt = a.dcls[rd] == kClsPal ? (T)1 : r2;
+        if (c < a.Lp) {
+            const uint4 in = a.pinfo[c];
+            const int ndh = a.pcnt[c];
+            const T wt = in.w ? (T)1 : r2;
             const T xc = x[off + c];
-            T acc = (T)(a.U * __builtin_popcount(phu & a.dn_states[rd])) * xc;
-            const int ndh = a.dn_cnt[rd];
-            // hops in order, kPHopNB at a time: each level of a batch's lookups
-            // (entries, classes, columns, operands) is loaded before the next
-            int h = 0;
-            for (; h + kPHopNB <= ndh; h += kPHopNB) {   // the up string stays: a column of this row
-                uint32_t rd2[kPHopNB], col[kPHopNB];
-                uint8_t cl[kPHopNB];
+            T acc = (T)(a.U * __builtin_popcount(phu & in.x)) * xc;
+            for (int h = 0; h < ndh; h += kPHopNB) {   // the up string stays: a column of this row
+                uint64_t e[kPHopNB];
                 T cf[kPHopNB], xv[kPHopNB];
 #pragma unroll
-                for (int j = 0; j < kPHopNB; ++j) {
-                    const uint32_t e = a.dn_ell[(uint64_t)(h + j) * a.Ddn + rd];
-                    rd2[j] = e & kTargetMask;
-                    cf[j] = coef[e >> kTargetBits];
-                }
+                for (int j = 0; j < kPHopNB; ++j)
+                    if (h + j < ndh) e[j] = a.pell[(uint64_t)(h + j) * a.Lp + c];
 #pragma unroll
-                for (int j = 0; j < kPHopNB; ++j) cl[j] = a.dcls[rd2[j]];
+                for (int j = 0; j < kPHopNB; ++j)
+                    if (h + j < ndh) {
+                        xv[j] = x[off + (uint32_t)e[j]];
+                        cf[j] = coef[e[j] >> 40];
+                    }
 #pragma unroll
-                for (int j = 0; j < kPHopNB; ++j) col[j] = a.dcol[cl[j] == kClsImage ? a.dinv[rd2[j]] : rd2[j]];
-#pragma unroll
-                for (int j = 0; j < kPHopNB; ++j)   // excluded palindromes have no column
-                    xv[j] = (cl[j] != kClsPal || a.pal_in) ? x[off + col[j]] : (T)0;
-#pragma unroll
-                for (int j = 0; j < kPHopNB; ++j) {
-                    if (cl[j] == kClsA)
-                        acc += wt * ir2 * cf[j] * xv[j];
-                    else if (cl[j] == kClsImage)
-                        acc += wt * ir2 * ps * cf[j] * xv[j];
-                    else if (a.pal_in)
-                        acc += wt * cf[j] * xv[j];
-                }
-            }
-            for (; h < ndh; ++h) {
-                const uint32_t e = a.dn_ell[(uint64_t)h * a.Ddn + rd];
-                const uint32_t rd2 = e & kTargetMask;
-                const T cf = coef[e >> kTargetBits];
-                const uint8_t cl = a.dcls[rd2];
-                if (cl == kClsA)
-                    acc += wt * ir2 * cf * x[off + a.dcol[rd2]];
-                else if (cl == kClsImage)
-                    acc += wt * ir2 * ps * cf * x[off + a.dcol[a.dinv[rd2]]];
-                else if (a.pal_in)
-                    acc += wt * cf * x[off + a.dcol[rd2]];
+                for (int j = 0; j < kPHopNB; ++j)
+                    if (h + j < ndh) {
+                        const uint32_t cl = (uint32_t)(e[j] >> 32) & 3u;
+                        const T w = cl == kClsPal ? wt : cl == kClsA ? wt * ir2 : wt * ir2 * ps;
+                        acc += w * cf[j] * xv[j];
+                    }
             }
             // one hop never leaves a palindrome a palindrome: a full row
-            const uint32_t cA = a.dcolf[rd], cI = a.dcolf[a.dinv[rd]];
-            h = 0;
-            for (; h + kPHopNB <= nup_h; h += kPHopNB) {
-                uint32_t ru2[kPHopNB];
-                uint64_t off2[kPHopNB];
-                bool isA[kPHopNB];
-                T cf[kPHopNB], xv[kPHopNB];
+            for (int h = 0; h < nup_h; h += kPHopNB) {
+                T f[kPHopNB], xv[kPHopNB];
 #pragma unroll
-                for (int j = 0; j < kPHopNB; ++j) {
-                    const uint32_t e = a.up_ell[(uint64_t)(h + j) * a.Dup + ru];
-                    ru2[j] = e & kTargetMask;
-                    cf[j] = coef[e >> kTargetBits];
-                }
+                for (int j = 0; j < kPHopNB; ++j)
+                    if (h + j < nup_h) {
+                        const uint64_t e = up[h + j];
+                        const bool img = e & kPupImage;
+                        xv[j] = x[(e & kPupOff) + (img ? in.z : in.y)];
+                        f[j] = (img ? wt * ir2 * ps : wt * ir2) * coef[e >> kPupCoef];
+                    }
 #pragma unroll
-                for (int j = 0; j < kPHopNB; ++j) {
-                    off2[j] = a.row_off[a.urow[ru2[j]]];
-                    isA[j] = a.ucls[ru2[j]] == kClsA;
-                }
-#pragma unroll
-                for (int j = 0; j < kPHopNB; ++j) xv[j] = x[off2[j] + (isA[j] ? cA : cI)];
-#pragma unroll
-                for (int j = 0; j < kPHopNB; ++j) {
-                    if (isA[j])
-                        acc += wt * ir2 * cf[j] * xv[j];
-                    else
-                        acc += wt * ir2 * ps * cf[j] * xv[j];
-                }
-            }
-            for (; h < nup_h; ++h) {
-                const uint32_t e = a.up_ell[(uint64_t)h * a.Dup + ru];
-                const uint32_t ru2 = e & kTargetMask;
-                const T cf = coef[e >> kTargetBits];
-                const uint64_t off2 = a.row_off[a.urow[ru2]];
-                if (a.ucls[ru2] == kClsA)
-                    acc += wt * ir2 * cf * x[off2 + cA];
-                else
-                    acc += wt * ir2 * ps * cf * x[off2 + cI];
+                for (int j = 0; j < kPHopNB; ++j)
+                    if (h + j < nup_h) acc += f[j] * xv[j];
             }
             y[off + c] = acc;
             dsum += (double)xc * (double)acc;
@@ -856,6 +855,11 @@ PArgs pargs(const pdz_problem_s* p) {
     a.row_off = q->d_row_off;
     a.row_pal = q->d_row_pal;
     a.uinv = q->d_uinv;
+    a.pinfo = q->d_pinfo;
+    a.pcnt = q->d_pcnt;
+    a.pell = q->d_pell;
+    a.pup = q->d_pup;
+    a.pup_stride = q->pup_stride;
     a.rows = nullptr;
     a.nlist = 0;
     a.nrows = q->nrows;
@@ -879,7 +883,8 @@ void parity_free(ParSpace* q) {
     if (!q) return;
     void* ptrs[] = {q->d_ucls, q->d_uinv, q->d_utree, q->d_urow, q->d_dcls, q->d_dinv, q->d_dtree, q->d_dcol,
                     q->d_dlist, q->d_row_rank, q->d_row_off, q->d_row_pal, q->d_S, q->d_rows_full, q->d_rows_pal,
-                    q->d_dcolf, q->d_dlistf, q->d_fmir, q->d_fcnt, q->d_fell, q->d_fell2, q->d_fup};
+                    q->d_dcolf, q->d_dlistf, q->d_fmir, q->d_fcnt, q->d_fell, q->d_fell2, q->d_fup,
+                    q->d_pinfo, q->d_pcnt, q->d_pell, q->d_pup};
     for (void* v : ptrs)
         if (v) (void)hipFree(v);
     void* gptrs[] = {q->d_col_dn, q->d_goff[0], q->d_goff[1], q->d_gnr[0], q->d_gnr[1], q->d_grp_up[0], q->d_grp_up[1]};
@@ -1317,6 +1322,32 @@ pdz_status parity_build(pdz_problem_s* p, int P) {
         }
     }
     if ((st = dupload(&q->d_rows_pal, rows_pal)) != PDZ_OK) return st;
+    if (q->n_pal > 0) {
+        const int mhd = std::max(p->dn.max_hops, 1), mhu = std::max(p->up.max_hops, 1);
+        std::vector<uint8_t> ucnt_h(Du);
+        std::vector<uint32_t> uell_h((size_t)mhu * Du);
+        PDZ_HIP(hipMemcpy(ucnt_h.data(), p->up.count, Du, hipMemcpyDeviceToHost));
+        if (p->up.max_hops > 0) PDZ_HIP(hipMemcpy(uell_h.data(), p->up.ell, (size_t)mhu * Du * 4, hipMemcpyDeviceToHost));
+        std::vector<uint64_t> pup((size_t)rows_pal.size() * mhu, 0);
+        for (size_t kk = 0; kk < rows_pal.size(); ++kk) {
+            const uint32_t ru = row_rank[rows_pal[kk]];
+            for (int h = 0; h < ucnt_h[ru]; ++h) {
+                const uint32_t e = uell_h[(size_t)h * Du + ru];
+                const uint32_t ru2 = e & kTargetMask;
+                pup[kk * mhu + h] = (row_off[urow[ru2]] & kPupOff) | (ucls[ru2] == kClsA ? 0 : kPupImage) |
+                                    (uint64_t)(e >> kTargetBits) << kPupCoef;
+            }
+        }
+        q->pup_stride = mhu;
+        if ((st = dupload(&q->d_pup, pup)) != PDZ_OK) return st;
+        if ((st = dalloc(&q->d_pinfo, q->Lp)) != PDZ_OK) return st;
+        if ((st = dalloc(&q->d_pcnt, q->Lp)) != PDZ_OK) return st;
+        if ((st = dalloc(&q->d_pell, (uint64_t)mhd * q->Lp)) != PDZ_OK) return st;
+        hipLaunchKernelGGL(k_ppal, dim3(pgrid(q->Lp, cu)), dim3(kPBlock), 0, nullptr, pargs(p), q->d_pinfo, q->d_pcnt,
+                           q->d_pell);
+        PDZ_HIP(hipGetLastError());
+        PDZ_HIP(hipStreamSynchronize(nullptr));
+    }
     if (!q->force_loop && q->n_full > 0 && p->dn.max_hops > 0) {
         // the scheduled down pass: the column hop table's gather schedule
         // (none when it does not apply), then the row groups
