@@ -147,7 +147,8 @@ pdz_status pdz_hv_pitched(pdz_problem p, pdz_dtype dt, const void* x, void* y, u
 
 /* ------------------------------------------------------ H.v launch plans */
 
-/* Launch geometry of pdz_hv for one precision.  0 in a field = automatic.
+/* Launch geometry of pdz_hv for one precision.  0 in a field = automatic: a
+ * value that runs with the fields that are set.
  * down: looped family (summands of each element in hop-table order):
  *       1 one row per work group with the column's hop table loaded up front,
  *       2 one row with the table read in a loop, 3 two rows per work group,

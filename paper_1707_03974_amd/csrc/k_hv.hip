@@ -1496,18 +1496,36 @@ HvPlan pass_plan(const pdz_problem_s* p, pdz_dtype dt, HvPlan pl) {
     return pl;
 }
 
-}  // namespace
+// Whether the up-pass variant `up` runs on chunks of cw columns.
+bool up_pair(const pdz_problem_s* p, size_t es, int cw, int up) {
+    if (up != 1 && p->D > 0xFFFFFFFFull) return false;              // the others have 32-bit offsets
+    if (up == 2) return p->up.max_hops <= 48 && cw <= 64;           // one column per lane
+    if (up == 4) return (size_t)cw * es / 16 <= 32;                 // at most 32 lanes of 16 bytes per row segment
+    return true;
+}
 
-HvPlan hv_resolve(const pdz_problem_s* p, pdz_dtype dt) {
-    HvPlan pl = p->plan[dt == PDZ_F64 ? 0 : 1];
+// `pl` with its automatic fields filled in.  A field that is automatic follows
+// the one that is set where its default does not go with it: an up-pass width
+// without wide lanes takes batches of 8 hops, a variant without the default
+// width its widest.
+HvPlan plan_fill(const pdz_problem_s* p, pdz_dtype dt, HvPlan pl) {
+    const size_t es = dt == PDZ_F64 ? 8 : 4;
     // a set field of the up pass asks for the two passes
     const HvPlan d = pl.up_cw || pl.up || pl.map ? two_pass_plan(p, dt) : default_plan(p, dt);
+    const int* cws = dt == PDZ_F64 ? kUpCw64 : kUpCw32;
     if (pl.down == 0) pl.down = d.down;
-    if (pl.up_cw == 0) pl.up_cw = d.up_cw;
-    if (pl.up == 0) pl.up = d.up;
+    if (pl.up_cw == 0) {
+        pl.up_cw = d.up_cw;
+        for (int k = kNumCw; pl.up && !up_pair(p, es, pl.up_cw, pl.up) && k-- > 0;) pl.up_cw = cws[k];
+    }
+    if (pl.up == 0) pl.up = up_pair(p, es, pl.up_cw, d.up) ? d.up : 1;
     if (pl.map == 0) pl.map = d.map;
     return pl;
 }
+
+}  // namespace
+
+HvPlan hv_resolve(const pdz_problem_s* p, pdz_dtype dt) { return plan_fill(p, dt, p->plan[dt == PDZ_F64 ? 0 : 1]); }
 
 namespace {
 
@@ -1603,49 +1621,42 @@ pdz_status up_pass(const pdz_problem_s* p, const T* coef, const T* x, T* yout, h
     ua.map = plan.map;
     const uint64_t blocks = up_blocks(p, sizeof(T), plan);
     const int nb = plan.up == 3 ? 16 : 8;
+    bool known = true;   // the grid is sized for CW columns: no other width's kernel may take it
     if (plan.up == 4 && !idx64) {
-        if (sizeof(T) == 8) {
-            if (CW == 16)
-                launch_up_wide<T, E, 16>(blocks, lds, s, ua, x, yout);
-            else if (CW == 32)
-                launch_up_wide<T, E, 32>(blocks, lds, s, ua, x, yout);
-            else
-                launch_up_wide<T, E, 64>(blocks, lds, s, ua, x, yout);
-        } else {
-            if (CW == 32)
-                launch_up_wide<T, E, 32>(blocks, lds, s, ua, x, yout);
-            else if (CW == 64)
-                launch_up_wide<T, E, 64>(blocks, lds, s, ua, x, yout);
-            else
-                launch_up_wide<T, E, 128>(blocks, lds, s, ua, x, yout);
-        }
+        if (sizeof(T) == 8 && CW == 16)
+            launch_up_wide<T, E, 16>(blocks, lds, s, ua, x, yout);
+        else if (CW == 32)
+            launch_up_wide<T, E, 32>(blocks, lds, s, ua, x, yout);
+        else if (CW == 64)
+            launch_up_wide<T, E, 64>(blocks, lds, s, ua, x, yout);
+        else if (sizeof(T) == 4 && CW == 128)
+            launch_up_wide<T, E, 128>(blocks, lds, s, ua, x, yout);
+        else
+            known = false;
     } else if (plan.up == 2 && !idx64) {
         // preloaded rows: one column per lane (CW <= 64)
         if (sizeof(T) == 8 && CW == 16)
             launch_up_pre<T, E, 16>(ua.max_hops, blocks, lds, s, ua, x, yout);
         else if (CW == 32)
             launch_up_pre<T, E, 32>(ua.max_hops, blocks, lds, s, ua, x, yout);
-        else
+        else if (CW == 64)
             launch_up_pre<T, E, 64>(ua.max_hops, blocks, lds, s, ua, x, yout);
-    } else if (sizeof(T) == 8) {
-        if (CW == 16)
-            launch_up<T, E, 16>(idx64, nb, blocks, lds, s, ua, x, yout);
-        else if (CW == 32)
-            launch_up<T, E, 32>(idx64, nb, blocks, lds, s, ua, x, yout);
-        else if (CW == 64)
-            launch_up<T, E, 64>(idx64, nb, blocks, lds, s, ua, x, yout);
         else
-            launch_up<T, E, 128>(idx64, nb, blocks, lds, s, ua, x, yout);
+            known = false;
+    } else if (sizeof(T) == 8 && CW == 16) {
+        launch_up<T, E, 16>(idx64, nb, blocks, lds, s, ua, x, yout);
+    } else if (CW == 32) {
+        launch_up<T, E, 32>(idx64, nb, blocks, lds, s, ua, x, yout);
+    } else if (CW == 64) {
+        launch_up<T, E, 64>(idx64, nb, blocks, lds, s, ua, x, yout);
+    } else if (CW == 128) {
+        launch_up<T, E, 128>(idx64, nb, blocks, lds, s, ua, x, yout);
+    } else if (sizeof(T) == 4 && CW == 256) {
+        launch_up<T, E, 256>(idx64, nb, blocks, lds, s, ua, x, yout);
     } else {
-        if (CW == 32)
-            launch_up<T, E, 32>(idx64, nb, blocks, lds, s, ua, x, yout);
-        else if (CW == 64)
-            launch_up<T, E, 64>(idx64, nb, blocks, lds, s, ua, x, yout);
-        else if (CW == 128)
-            launch_up<T, E, 128>(idx64, nb, blocks, lds, s, ua, x, yout);
-        else
-            launch_up<T, E, 256>(idx64, nb, blocks, lds, s, ua, x, yout);
+        known = false;
     }
+    if (!known) return fail(PDZ_EINVAL, "no up-pass kernel of this chunk width");
     PDZ_HIP(hipGetLastError());
     return ok();
 }
@@ -1901,10 +1912,6 @@ std::vector<HvPlan> hv_candidates(const pdz_problem_s* p, pdz_dtype dt, bool eve
     if (p->hv_path != 0) return out;
     const size_t es = dt == PDZ_F64 ? 8 : 4;
     const HvPlan two = two_pass_plan(p, dt);
-    if (rows_available(p, p->dn.D) && d.down != kRowsPlan) {
-        out.push_back(two);
-        out.back().down = kRowsPlan;
-    }
     const bool compact = p->up.tbits16 > 0 && p->dn.tbits16 > 0;
     std::vector<int> downs;
     const bool sched = wide_down(p, es) && p->dn.sched.words;
@@ -1922,7 +1929,6 @@ std::vector<HvPlan> hv_candidates(const pdz_problem_s* p, pdz_dtype dt, bool eve
         downs.push_back(two.down);
     }
     const int* cws = dt == PDZ_F64 ? kUpCw64 : kUpCw32;
-    const bool pre_ok = p->up.max_hops <= 48 && p->D <= 0xFFFFFFFFull;
     for (int dv : downs)
         for (int k = 0; k < kNumCw; ++k)
             for (int um = 1; um <= 4; ++um)
@@ -1932,10 +1938,7 @@ std::vector<HvPlan> hv_candidates(const pdz_problem_s* p, pdz_dtype dt, bool eve
                     c.up_cw = cws[k];
                     c.up = um;
                     c.map = mp;
-                    if (um == 2 && (!pre_ok || cws[k] > 64)) continue;
-                    if (um == 3 && p->D > 0xFFFFFFFFull) continue;
-                    // wide lanes: 16-byte lanes, at most 32 lanes per row segment
-                    if (um == 4 && (p->D > 0xFFFFFFFFull || (size_t)cws[k] * es / 16 > 32)) continue;
+                    if (!up_pair(p, es, cws[k], um)) continue;
                     if (c.down != d.down || c.up_cw != d.up_cw || c.up != d.up || c.map != d.map) out.push_back(c);
                 }
     return out;
@@ -1943,10 +1946,9 @@ std::vector<HvPlan> hv_candidates(const pdz_problem_s* p, pdz_dtype dt, bool eve
 
 bool hv_plan_valid(const pdz_problem_s* p, pdz_dtype dt, const HvPlan& plan) {
     if (plan.down == 0 && plan.up_cw == 0 && plan.up == 0 && plan.map == 0) return true;
+    const HvPlan r = plan_fill(p, dt, plan);   // what will run, not the set fields alone
     for (const HvPlan& c : hv_candidates(p, dt, true))
-        if ((plan.down == 0 || plan.down == c.down) && (plan.up_cw == 0 || plan.up_cw == c.up_cw) &&
-            (plan.up == 0 || plan.up == c.up) && (plan.map == 0 || plan.map == c.map))
-            return true;
+        if (r.down == c.down && r.up_cw == c.up_cw && r.up == c.up && r.map == c.map) return true;
     return false;
 }
 
