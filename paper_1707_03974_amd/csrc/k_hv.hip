@@ -1577,6 +1577,12 @@ uint64_t down_grid(const pdz_problem_s* p, size_t es, const HvPlan& plan, unsign
     return down_geom(p, es, plan, cu).grid;
 }
 
+// The plan at a row pitch: element offsets past 32 bits have one up pass.
+HvPlan pitch_plan(const pdz_problem_s* p, HvPlan plan, uint64_t pitch) {
+    if (p->up.D * pitch > 0xFFFFFFFFull) plan.up = 1;
+    return plan;
+}
+
 // Rows per up-pass tile: 8, or one per lane group with wide lanes (plan up 4).
 int up_tile_rows(size_t es, const HvPlan& plan) {
     if (plan.up == 4) return kUpBlock / (int)((size_t)plan.up_cw * es / 16);
@@ -1622,7 +1628,7 @@ pdz_status up_pass(const pdz_problem_s* p, const T* coef, const T* x, T* yout, h
     const uint64_t blocks = up_blocks(p, sizeof(T), plan);
     const int nb = plan.up == 3 ? 16 : 8;
     bool known = true;   // the grid is sized for CW columns: no other width's kernel may take it
-    if (plan.up == 4 && !idx64) {
+    if (plan.up == 4) {
         if (sizeof(T) == 8 && CW == 16)
             launch_up_wide<T, E, 16>(blocks, lds, s, ua, x, yout);
         else if (CW == 32)
@@ -1633,7 +1639,7 @@ pdz_status up_pass(const pdz_problem_s* p, const T* coef, const T* x, T* yout, h
             launch_up_wide<T, E, 128>(blocks, lds, s, ua, x, yout);
         else
             known = false;
-    } else if (plan.up == 2 && !idx64) {
+    } else if (plan.up == 2) {
         // preloaded rows: one column per lane (CW <= 64)
         if (sizeof(T) == 8 && CW == 16)
             launch_up_pre<T, E, 16>(ua.max_hops, blocks, lds, s, ua, x, yout);
@@ -1735,7 +1741,7 @@ pdz_status run_tables(const pdz_problem_s* p, const DeviceCtx* ctx, const T* coe
     da.fkidx = fused ? split->fkidx : nullptr;
     da.fnorm = fused ? split->fnorm : nullptr;
     const pdz_dtype dt = sizeof(T) == 8 ? PDZ_F64 : PDZ_F32;
-    const HvPlan plan = pass_plan(p, dt, hv_resolve(p, dt));
+    const HvPlan plan = pitch_plan(p, pass_plan(p, dt, hv_resolve(p, dt)), pitch);
     const DownGeom gm = down_geom(p, sizeof(T), plan, (unsigned)ctx->cu_count);
     da.rows = gm.rows;
     if (gm.wide && sched_plan(plan.down) && pitch + 32 > (uint64_t)kSchedPlane)
@@ -2079,12 +2085,12 @@ int hv_whole_dots(const pdz_problem_s* p, pdz_dtype dt) {
     return (int)rows_geom(p, dt == PDZ_F64 ? 8 : 4).grid;
 }
 
-bool hv_dot_counts(const pdz_problem_s* p, pdz_dtype dt, int* n_dn, int* n_up) {
+bool hv_dot_counts(const pdz_problem_s* p, pdz_dtype dt, uint64_t pitch, int* n_dn, int* n_up) {
     if (p->hv_path != 0 || hv_whole_dots(p, dt) > 0) return false;
     DeviceCtx* ctx = nullptr;
     if (device_ctx(&ctx) != PDZ_OK) return false;
     const size_t es = dt == PDZ_F64 ? 8 : 4;
-    const HvPlan plan = hv_resolve(p, dt);
+    const HvPlan plan = pitch_plan(p, hv_resolve(p, dt), pitch ? pitch : p->dn.D);
     *n_dn = (int)down_grid(p, es, plan, (unsigned)ctx->cu_count);
     *n_up = p->up.max_hops == 0 ? 1 : (int)up_blocks(p, es, plan);
     return true;

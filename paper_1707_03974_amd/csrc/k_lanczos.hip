@@ -867,7 +867,7 @@ struct Run {
     };
     SplitCounts split_counts() const {
         SplitCounts c;
-        if (!hv_dot_counts(p, (pdz_dtype)o->storage, &c.ndn, &c.nup)) c.ndn = c.nup = 0;
+        if (!hv_dot_counts(p, (pdz_dtype)o->storage, pitch, &c.ndn, &c.nup)) c.ndn = c.nup = 0;
         c.nwhole = p->par ? parity_dot_count(p, (pdz_dtype)o->storage) : hv_whole_dots(p, (pdz_dtype)o->storage);
         return c;
     }

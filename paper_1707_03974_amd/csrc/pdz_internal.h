@@ -263,7 +263,8 @@ pdz_status launch_hv(const pdz_problem_s* p, pdz_dtype dt, const void* x, void* 
 pdz_status launch_hv_any(const pdz_problem_s* p, pdz_dtype dt, const void* x, void* y, hipStream_t s,
                          const int* skip = nullptr, unsigned passes = kPassDown | kPassUp,
                          const HvSplit* split = nullptr, uint64_t pitch = 0);
-bool hv_dot_counts(const pdz_problem_s* p, pdz_dtype dt, int* n_dn, int* n_up);   // false: no split path
+// partials of the two passes at a row pitch (0: D_dn); false: no split path
+bool hv_dot_counts(const pdz_problem_s* p, pdz_dtype dt, uint64_t pitch, int* n_dn, int* n_up);
 size_t hv_dot_count_max(const pdz_problem_s* p, pdz_dtype dt);   // n_dn + n_up over every valid plan
 
 }  // namespace pdz

@@ -49,3 +49,20 @@ def test_partial_plans_run_a_kernel_of_their_width(name, n, nu, nd):
         # what is set holds: the resolved plan, set whole, is the same plan
         g.set_plan(name, *(pl[k] for k in ("down", "up_cw", "up", "map")))
         assert g.get_plan(name) == pl
+
+
+@pytest.mark.parametrize("cw,up", [(32, 4), (64, 4), (64, 0), (64, 2), (256, 0), (0, 0)])
+def test_rows_past_32_bit_offsets_are_all_summed(cw, up):
+    """A pitch that puts the last rows past 2^32 elements: one up pass, whatever the plan's (17 GB vectors)."""
+    torch = torch_cuda()
+    import paper_1707_03974_amd as pdz
+    g = pdz.Problem(9, _ring(9), 3.25, 4, 4)
+    x = to_dev(synth.random_vector(g.D, 6), torch.float32)
+    ref = g.hv(x).view(g.info["D_up"], -1)
+    rows, cols = ref.shape
+    pitch = 2 ** 32 // rows + 1
+    xp, yp = (torch.empty(rows * pitch, dtype=torch.float32, device="cuda") for _ in range(2))
+    xp.view(rows, pitch)[:, :cols] = x.view(rows, cols)
+    g.set_plan("f32", 0, cw, up, 0)
+    g.hv_pitched(xp, pitch, yp)
+    assert torch.equal(yp.view(rows, pitch)[:, :cols], ref)
