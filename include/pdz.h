@@ -329,7 +329,8 @@ pdz_status pdz_lanczos_workspace_size(pdz_problem p, const pdz_lanczos_opts* o, 
  * tridiagonal eigensolve (multisection on the leading minors, FP64) all run on
  * the device; the host reads one flag per block of check_every steps.  On
  * vectors of up to 2^22 elements the Ritz pairs of up to 12 steps are solved
- * together after them (the same values; steps past the last are dropped).
+ * together after them, and steps past the last are dropped; steps taken and
+ * every value returned are the same for any check_every and use_graph.
  * v0: device array of D elements in `storage` precision, or NULL for the
  *     seeded start vector; it is normalised internally (not modified).
  * ws: caller-owned device workspace of at least pdz_lanczos_workspace_size

@@ -403,14 +403,11 @@ __global__ __launch_bounds__(kTriBlock) void k_britz_block(const BCtl* ctl, cons
     const int k = st->k + blockIdx.x + 1;
     if (st->done || k > max_iter) return;
     __shared__ TriShared<kBatchMaxIter> S;
-    __shared__ double red[kRed];
     const size_t row = (size_t)p * ld;
     double bk1;
-    if (blockIdx.x + 1 == gridDim.x || k == max_iter) {   // no update after this step has formed beta_{k+1}
-        const double* v = (k & 1) ? norm1 : norm0;
-        double acc = 0.0;
-        for (uint32_t c = ch_begin[p] + threadIdx.x; c < ch_begin[p + 1]; c += blockDim.x) acc += v[c];
-        bk1 = sqrt(bsum(acc, red));
+    if (blockIdx.x + 1 == gridDim.x || k == max_iter) {   // no update after this step has formed beta_{k+1}: its sum
+        static_assert(kTriBlock == kRed, "brange_sum's work group");
+        bk1 = sqrt(brange_sum(((k & 1) ? norm1 : norm0) + ch_begin[p], ch_begin[p + 1] - ch_begin[p]));
         if (threadIdx.x == 0) beta[row + k] = bk1;
     } else {
         bk1 = beta[row + k];

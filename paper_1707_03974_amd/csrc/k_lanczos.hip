@@ -260,6 +260,30 @@ __device__ __forceinline__ double sum_two(const double* p1, int n1, const double
     return block_sum_all<BLOCK>(acc);
 }
 
+// Sum of p[0..n) by a work group of kRedBlock threads, each in place of two of
+// the update's: sum_two<kUpdBlock>'s value bit for bit, in every thread.
+__device__ __forceinline__ double sum_as_update(const double* p, int n) {
+    static_assert(kUpdBlock == 2 * kRedBlock, "two of the update's threads each");
+    __shared__ double ws[kUpdBlock / 64];
+    double lo = 0.0, hi = 0.0;
+    for (int i = threadIdx.x; i < n; i += kUpdBlock) lo += p[i];
+    for (int i = threadIdx.x + kRedBlock; i < n; i += kUpdBlock) hi += p[i];
+#pragma unroll
+    for (int m = 32; m > 0; m >>= 1) {
+        lo += __shfl_xor(lo, m);
+        hi += __shfl_xor(hi, m);
+    }
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) {
+        ws[threadIdx.x >> 6] = lo;
+        ws[(threadIdx.x + kRedBlock) >> 6] = hi;
+    }
+    __syncthreads();
+    double t = ws[0];
+    for (int i = 1; i < kUpdBlock / 64; ++i) t += ws[i];
+    return t;
+}
+
 // KEEP: the new vector is also stored as slot k + 1 of the kept basis (slots
 // of keep_ld elements, keep_cap of them), the copy the refinement combines.
 template <typename T, bool HZ, bool KEEP>
@@ -555,20 +579,17 @@ __global__ __launch_bounds__(kTriBlock) void k_ritz(const double* partial, int n
 
 // Ritz pairs of a block of `steps` steps, work group t the pair of step
 // ctl->k + t (tridiag.h); norms[j]: the n partials of |q|^2 of the vectors of
-// parity j, of which the last step's beta is formed.
+// parity j, of which the last step's beta is formed with the update's sum, so
+// that it does not depend on where a block ends.
 __global__ __launch_bounds__(kTriBlock) void k_ritz_block(const double* norm0, const double* norm1, int n,
                                                           const double* alpha, double* beta, double* theta,
                                                           double* resid, const Ctl* ctl, int max_iter) {
     const int k = ctl->k + blockIdx.x + 1;
     if (ctl->done || k > max_iter) return;
     __shared__ TriShared<kMaxIter> S;
-    __shared__ double red[kRedBlock];
     double bk1;
     if (blockIdx.x + 1 == gridDim.x || k == max_iter) {   // no update after this step has formed beta_{k+1}
-        const double* p = (k & 1) ? norm1 : norm0;
-        double acc = 0.0;
-        for (int i = threadIdx.x; i < n; i += blockDim.x) acc += p[i];
-        bk1 = sqrt(block_sum(acc, red));
+        bk1 = sqrt(sum_as_update((k & 1) ? norm1 : norm0, n));
         if (threadIdx.x == 0) beta[k] = bk1;
     } else {
         bk1 = beta[k];

@@ -79,3 +79,23 @@ def test_invariant_subspace_in_the_middle_of_a_block():
     assert r["converged"] == 1 and r["iters"] == 3 and len(r["thetas"]) == 3
     assert abs(r["E0"]) <= 1e-13 and abs(r["E0_refined"]) <= 1e-13
     assert np.all(np.isfinite(r["alpha"])) and np.all(np.isfinite(r["beta"]))
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32"])
+def test_results_do_not_depend_on_where_blocks_end(storage):
+    """A vector of hundreds of partial sums (853,776 elements): the norm that ends a block or a run and the same
+    norm in the middle of one are summed alike, alone and in a batch."""
+    import paper_1707_03974_amd as pdz
+    torch_cuda()
+    probs = [pdz.Problem.from_workload(synth.workload(n)) for n in ("torus4x3", "ring8")]
+    b = pdz.Batch(probs)
+    full = probs[0].lanczos(storage=storage, max_iter=60, tol=0.0, history=True, coefficients=True)
+    for m in range(1, 37):
+        r = probs[0].lanczos(storage=storage, max_iter=m, tol=0.0, history=True, coefficients=True)
+        for k, n in (("alpha", m), ("beta", m + 1), ("thetas", m)):
+            assert r[k] == full[k][:n], (k, m)
+    for tol in 10.0 ** -np.arange(1.0, 5.0, 0.125):
+        runs = [probs[0].lanczos(storage=storage, tol=tol, check_every=ce, use_graph=ug) for ce, ug in ((1, 0), (40, 1))]
+        res = [b.lanczos(storage=storage, tol=tol, check_every=ce, use_graph=ug)[0] for ce, ug in ((1, 0), (40, 1))]
+        for x, y in ((runs[0], runs[1]), (res[0][0], res[1][0]), (res[0][1], res[1][1])):
+            assert all(x[k] == y[k] for k in ("iters", "E0", "resid_est")), (tol, x, y)
