@@ -131,10 +131,11 @@ __device__ __forceinline__ bf16x8 tanh8(f32x4 a, f32x4 b, f32x4 ba, f32x4 bb) {
 // units of one state; the rows are dealt (tile_unit) so that two tiles leave
 // a lane exactly the operand slot it feeds to the next layer, in the plain
 // feature order: no exchange between lanes, no LDS round trip and no barrier
-// between layers.  The last layer's two rows sit in rows 4s, 4s + 1 of the
-// operand of state tile s, so one accumulator collects all S tiles: with
-// S = 4 lane l holds (o_0, o_1) of state s0 + l in o[0], o[1] (S = 1: lanes
-// 0..15, state s0 + l).
+// between layers.  The last layer's two rows are in every group of four rows of
+// its operand, so each lane group finds the outputs in its own rows and takes
+// those of state tile g: with S = 4 lane l holds (o_0, o_1) of state s0 + l in
+// the first two elements (S = 1: lanes 0..15, state s0 + l).  Each tile has an
+// accumulator of its own: a state whose activations are not numbers stays alone.
 template <bool ACT, int S, typename W>
 __device__ __forceinline__ f32x4 mlp_layers(const W& w, const bf16x8 (&x)[S], const float* b1, const float* b2,
                                             int g, int c, uint64_t s0, uint64_t n, const Act& act,
@@ -163,9 +164,9 @@ __device__ __forceinline__ f32x4 mlp_layers(const W& w, const bf16x8 (&x)[S], co
             }
         }
     }
-    f32x4 o = zero;
-    int mine = c >> 2;
-    asm volatile("" : "+v"(mine));   // the masked rows below are formed when used, not kept over the caller's loop
+    f32x4 o[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s) o[s] = zero;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         if (S > 1) asm volatile("" ::: "memory");   // the next block's weights are not read before this one is done
@@ -196,12 +197,13 @@ __device__ __forceinline__ f32x4 mlp_layers(const W& w, const bf16x8 (&x)[S], co
                     for (int e = 0; e < 8; ++e)
                         row[e] = (uint16_t)((e & 1) ? (hv[e >> 1] >> 16) : (hv[e >> 1] & 0xFFFFu));
             }
-            u32x4 m = __builtin_bit_cast(u32x4, w.l3(q, g, c));
-            if (S > 1 && mine != s) m = u32x4{0u, 0u, 0u, 0u};
-            o = mma(__builtin_bit_cast(bf16x8, m), h2, o);
+            o[s] = mma(w.l3(q, g, c), h2, o[s]);
         }
     }
-    return o;
+    f32x4 own = o[0];
+#pragma unroll
+    for (int s = 1; s < S; ++s) own = g == s ? o[s] : own;
+    return own;
 }
 
 // Features of a state whose up and down strings are packed as up | dn << 16:
@@ -223,7 +225,7 @@ __device__ __forceinline__ void write_out(float* out, uint64_t s, float o0, floa
 // states; with 16 states a wave they would cost half as much as the ALU work).
 // 1.31e8 states (4x4, 7 + 7): 19.2 ms with 16 states a wave, the hidden layer
 // through LDS, scalar rounding to BF16 and the last layer on the vector ALUs;
-// 9.6 ms so (565 TFLOP/s).
+// 9.4 ms so (576 TFLOP/s).
 constexpr int kFwdTiles = 4;             // state tiles of 16 per wave
 constexpr int kFwdStates = 4 * 16 * kFwdTiles;   // states per work group and turn
 template <typename T, bool BASIS>

@@ -89,3 +89,38 @@ def test_loss_at_work_group_edges(n):
     expect, dout = ref.loss_and_dout(out.astype(np.float64), tgt[:, 0].astype(np.float64), tgt[:, 1])
     assert abs(loss.item() - expect) <= 1e-6 * abs(expect)
     assert np.allclose(to_host(d), dout, rtol=1e-5, atol=1e-9)
+
+
+@pytest.mark.parametrize("sites", [(0, 17), (3, 9)])
+def test_a_state_that_is_not_a_number_stays_alone(sites):
+    """Two opposite infinities in a row of W1 cancel to NaN where the two sites agree and saturate where they do
+    not: every state's outputs are those it has on its own (one wave per 16 states, one tile)."""
+    torch = torch_cuda()
+    import paper_1707_03974_amd as pdz
+    from paper_1707_03974_amd import mlp
+    net, _ = _net(14)
+    w = net.w.cpu()
+    w[5 * 32 + sites[0]], w[5 * 32 + sites[1]] = float("inf"), float("-inf")
+    net = mlp.Net(params=w)
+    n = 200_000 + 77
+    up, dn = _states(np.random.default_rng(3), n)
+    occ = _occ(up, dn)
+    out = net.forward(occ)
+    alone = torch.cat([net.forward(occ[k:k + 10_000].contiguous()) for k in range(0, n, 10_000)])
+    bits = np.concatenate([(up[:, None] >> np.arange(16)) & 1, (dn[:, None] >> np.arange(16)) & 1], axis=1)
+    nan = torch.from_numpy(bits[:, sites[0]] == bits[:, sites[1]]).cuda()
+    assert 0.2 < nan.float().mean().item() < 0.8
+    assert torch.equal(torch.isnan(out), nan[:, None].expand(n, 2)) and torch.equal(torch.isnan(alone), torch.isnan(out))
+    assert torch.equal(out[~nan], alone[~nan])
+    # the start vector of a state that is a number: sign * exp(min(o_0, 60))
+    p = pdz.Problem(16, [(0, 1, 1.0)], 1.0, 4, 3)
+    iu, idn = np.meshgrid(np.arange(p.info["D_up"]), np.arange(p.info["D_dn"]), indexing="ij")
+    su = pdz.unrank(16, 4, torch.arange(p.info["D_up"], dtype=torch.int32, device="cuda"))
+    sd = pdz.unrank(16, 3, torch.arange(p.info["D_dn"], dtype=torch.int32, device="cuda"))
+    pairs = torch.stack([su[torch.from_numpy(iu.ravel()).cuda()], sd[torch.from_numpy(idn.ravel()).cuda()]], dim=1)
+    o = torch.cat([net.forward(pairs[k:k + 10_000].contiguous()) for k in range(0, p.D, 10_000)]).double()
+    v = mlp.start_vector(p, net, torch.float64)
+    ok = ~torch.isnan(o[:, 0])
+    expect = torch.exp(o[:, 0].clamp(max=60.0)) * torch.where(o[:, 1] >= 0, 1.0, -1.0)
+    assert 0.2 < ok.double().mean().item() < 0.8
+    assert torch.allclose(v[ok], expect[ok], rtol=1e-13, atol=0.0)
