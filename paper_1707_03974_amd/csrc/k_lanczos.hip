@@ -614,8 +614,15 @@ __global__ __launch_bounds__(kTriBlock) void k_ritz_vector(const double* alpha, 
 }
 
 // Vectors up to which the Ritz pairs run by blocks of steps: up to 11 steps past
-// the last one are then taken for nothing, against one solve (25 us on average
-// over the first 100 steps) saved in every step.
+// the last one are then taken for nothing, against a launch and a solve saved in
+// every step.  The first blocks are shorter (1, 3, 9 steps), so that a run from a
+// vector near the ground state takes few of them.  Whole runs in us before there
+// were blocks (and with the slower H.v of then), with blocks of 12 from the first
+// step, and with the shorter first ones: 4x4 momentum sector 6+6, 4.0e6 elements,
+// FP32, runs of 1 step 789 / 1496 / 405, of 5 steps 2012 / 1511 / 1478, of 28
+// steps 9075 / 4049 / 4067; 5x3 7+3, 2.9e6 elements, FP32, of 1 step 620 / 804 /
+// 361, of 20 steps 2926 / 1421 / 1445; 4x3 6+6, 8.5e5 elements, FP64, of 102 steps
+// 9.4 / 3.8 / 3.8 ms.
 constexpr uint64_t kLagElems = 1ull << 22;
 constexpr int kLagSums = 8192;   // partial sums of alpha the update may have to add
 
@@ -1228,7 +1235,9 @@ struct Run {
             if (st != PDZ_OK) return st;
         }
         const bool lag = !fuse && lag_path(counts);
-        auto enqueue_block = [&]() -> pdz_status {
+        // `period` steps; first: the run's first ones
+        auto enqueue_block = [&](bool first) -> pdz_status {
+            int t0 = 0, len = first ? 1 : kRitzBlock;   // the block of Ritz pairs: its first step and length
             for (int t = 0; t < period; ++t) {
                 pdz_status s2;
                 if (fuse) {
@@ -1236,34 +1245,42 @@ struct Run {
                     s2 = fused_step(buf(a), buf(1 - a), buf(2), counts);
                 } else {
                     const int a = t % 3;
-                    s2 = step_scaled(buf(a), buf((a + 2) % 3), buf((a + 1) % 3), counts, lag ? t % kRitzBlock : -1);
+                    s2 = step_scaled(buf(a), buf((a + 2) % 3), buf((a + 1) % 3), counts, lag ? t - t0 : -1);
                 }
                 if (s2 != PDZ_OK) return s2;
-                if (lag && ((t + 1) % kRitzBlock == 0 || t + 1 == period)) end_block(t % kRitzBlock + 1);
+                if (lag && (t + 1 == t0 + len || t + 1 == period)) {
+                    end_block(t + 1 - t0);
+                    t0 = t + 1;
+                    len = first ? std::min(2 * t0 + 1, kRitzBlock) : kRitzBlock;   // 1, 3, 9, then whole ones
+                }
             }
             return launch_check();
         };
+        st = ok();
         hipGraphExec_t exec = nullptr;
         hipGraph_t graph = nullptr;
-        if (o->use_graph) {
-            PDZ_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-            st = enqueue_block();
-            hipGraph_t g2 = nullptr;
-            hipError_t e = hipStreamEndCapture(s, &g2);
-            if (st != PDZ_OK) {
-                if (g2) (void)hipGraphDestroy(g2);
-                return st;
+        int done_steps = 0;
+        if (lag) {   // the first steps, in blocks of their own; the graph is made while they run
+            st = enqueue_block(true);
+            if (st != PDZ_OK) return st;
+            done_steps = period;
+        }
+        if (o->use_graph && done_steps < o->max_iter) {
+            hipError_t e = hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal);
+            if (e == hipSuccess) {
+                st = enqueue_block(false);
+                e = hipStreamEndCapture(s, &graph);
             }
-            if (e != hipSuccess) return hip_fail(e, "hipStreamEndCapture");
-            graph = g2;
-            e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-            if (e != hipSuccess) {
-                (void)hipGraphDestroy(graph);
-                return hip_fail(e, "hipGraphInstantiate");
+            if (st == PDZ_OK && e == hipSuccess) e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
+            if (st != PDZ_OK || e != hipSuccess) {
+                if (graph) (void)hipGraphDestroy(graph);
+                (void)hipStreamSynchronize(s);   // the first steps use the workspace
+                return st != PDZ_OK ? st : hip_fail(e, "Lanczos graph");
             }
         }
-        st = ok();
-        for (int done_steps = 0; done_steps < o->max_iter; done_steps += period) {
+        if (done_steps > 0) st = read_ctl(h);
+        const bool over = done_steps > 0 && h->done;
+        for (; st == PDZ_OK && !over && done_steps < o->max_iter; done_steps += period) {
             if (exec) {
                 hipError_t e = hipGraphLaunch(exec, s);
                 if (e != hipSuccess) {
@@ -1271,7 +1288,7 @@ struct Run {
                     break;
                 }
             } else {
-                st = enqueue_block();
+                st = enqueue_block(false);
                 if (st != PDZ_OK) break;
             }
             st = read_ctl(h);

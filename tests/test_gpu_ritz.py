@@ -99,3 +99,26 @@ def test_results_do_not_depend_on_where_blocks_end(storage):
         res = [b.lanczos(storage=storage, tol=tol, check_every=ce, use_graph=ug)[0] for ce, ug in ((1, 0), (40, 1))]
         for x, y in ((runs[0], runs[1]), (res[0][0], res[1][0]), (res[0][1], res[1][1])):
             assert all(x[k] == y[k] for k in ("iters", "E0", "resid_est")), (tol, x, y)
+
+
+@pytest.mark.parametrize("check_every,use_graph", [(1, 1), (10, 1), (10, 0), (40, 1)])
+def test_runs_that_end_in_their_first_steps(check_every, use_graph):
+    """From vectors near the ground state a run ends within the first, shorter blocks: same steps and values as
+    the first steps of a run without a tolerance, for which the graph is made as well."""
+    import paper_1707_03974_amd as pdz
+    torch = torch_cuda()
+    g = pdz.Problem.from_workload(synth.workload("ring8"))
+    y = torch.empty(g.D, dtype=torch.float64, device="cuda")
+    g.lanczos(tol=1e-13, ritz=y)
+    noise = torch.from_numpy(synth.random_vector(g.D, 4)).cuda()
+    for mix in (0.0, 1e-6, 1e-3, 1e-1):
+        v0 = y + mix * noise
+        full = g.lanczos(v0=v0, max_iter=60, tol=0.0, history=True, coefficients=True)
+        for tol in (1e-1, 1e-2, 1e-4, 1e-6):
+            r = g.lanczos(v0=v0, max_iter=60, tol=tol, check_every=check_every, use_graph=use_graph, history=True,
+                          coefficients=True)
+            n = r["iters"]
+            assert r["converged"] == 1 and r["thetas"] == full["thetas"][:n] and r["resid_est"] <= tol * abs(r["E0"])
+            assert r["alpha"] == full["alpha"][:n] and r["beta"] == full["beta"][:n + 1]
+            if mix == 0.0:
+                assert n <= 1 + (tol < 1e-5)
