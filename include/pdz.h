@@ -280,8 +280,8 @@ pdz_status pdz_lanczos_default_opts(pdz_lanczos_opts* o);
  * groups of each step.  ms (5 doubles) receives mean milliseconds per step:
  * [0] the down pass (it also carries out the recurrence update when
  * *fused == 1), [1] the up pass, [2] the separate update kernel (0 when
- * fused), [3] the scalar kernels (alpha, beta, tridiagonal solve), [4] the
- * whole step.  ws as for pdz_lanczos with these options (reorth must be 0);
+ * fused), [3] the scalar kernels (alpha, beta, tridiagonal solve; a block's
+ * solves spread over its steps), [4] the whole step.  ws as for pdz_lanczos with these options (reorth must be 0);
  * its contents are overwritten.  Synchronous.  Errors: PDZ_EINVAL. */
 pdz_status pdz_lanczos_kernel_times(pdz_problem p, const pdz_lanczos_opts* o, void* ws, size_t ws_bytes,
                                     int32_t steps, double* ms, int32_t* fused, void* stream);

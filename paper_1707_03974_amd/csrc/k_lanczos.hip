@@ -1098,10 +1098,12 @@ struct Run {
     // seeded start, stream launches with events between the groups.
     // ms[0] down pass (fused with the update on the fused path), ms[1] up
     // pass, ms[2] separate update (0 on the fused path), ms[3] scalar
-    // kernels, ms[4] whole step.
+    // kernels, ms[4] whole step.  Where the run solves its Ritz pairs by blocks
+    // of steps, so does this, and a block's end counts among the scalar kernels.
     pdz_status timed_steps(int steps, double* ms, int* fused_out) {
         const bool fuse = fused_path();
         const SplitCounts counts = split_counts();
+        const bool lag = !fuse && lag_path(counts);
         pdz_status st = start(nullptr, buf(0), fuse ? buf(1) : buf(2), true);
         if (st != PDZ_OK) return st;
         if (fuse) {
@@ -1118,7 +1120,11 @@ struct Run {
                 st = fused_step(buf(a), buf(1 - a), buf(2), counts);
             } else {
                 const int a = t % 3;
-                st = step_scaled(buf(a), buf((a + 2) % 3), buf((a + 1) % 3), counts);
+                st = step_scaled(buf(a), buf((a + 2) % 3), buf((a + 1) % 3), counts, lag ? t % kRitzBlock : -1);
+                if (lag && ((t + 1) % kRitzBlock == 0 || t + 1 == steps)) {
+                    end_block(t % kRitzBlock + 1);
+                    mark(5);
+                }
             }
             if (st != PDZ_OK) break;
             hipError_t he = hipEventSynchronize(e[5]);

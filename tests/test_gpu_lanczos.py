@@ -336,3 +336,25 @@ def test_padded_rows_keep_every_lanczos_path_exact():
     kb = g.lanczos(storage="f32", tol=1e-9, max_iter=400, ritz=yb, keep_basis=1)
     assert ka["E0_refined"] == kb["E0_refined"] and torch.equal(ya, yb), (ka, kb)
     assert abs(ka["E0_refined"] - E) <= 1e-8 * abs(E), (ka, E)
+
+
+@pytest.mark.parametrize("name,storage", [("torus4x3", "f64"), ("torus4x3", "f32"), ("ring8", "f64")])
+def test_the_timed_steps_are_the_steps_of_a_run(name, storage):
+    """The Ritz values the timing leaves in its workspace are those of a run, bit for bit: the same launches."""
+    import ctypes
+    import paper_1707_03974_amd as pdz
+    from paper_1707_03974_amd import _lib
+    torch = torch_cuda()
+    g = pdz.Problem.from_workload(synth.workload(name))
+    steps = 60
+    o = g.lanczos_opts(storage=storage, max_iter=steps + 1, tol=0.0)
+    ws = torch.empty(g.workspace_size(o), dtype=torch.uint8, device="cuda")
+    ms, fused = (ctypes.c_double * 5)(), ctypes.c_int32()
+    _lib.check(_lib.load().pdz_lanczos_kernel_times(g.handle, ctypes.byref(o), ws.data_ptr(), ws.numel(), steps, ms,
+                                                    ctypes.byref(fused), 0))
+    th, n = (ctypes.c_double * steps)(), ctypes.c_int32()
+    _lib.check(_lib.load().pdz_lanczos_history(g.handle, ctypes.byref(o), ws.data_ptr(), ws.numel(), steps, th,
+                                               ctypes.byref(n)))
+    run = g.lanczos(storage=storage, max_iter=steps, tol=0.0, history=True)
+    assert n.value == run["iters"] and list(th[:n.value]) == run["thetas"]
+    assert all(v > 0.0 for v in (ms[0], ms[2], ms[3])) and abs(sum(ms[:4]) - ms[4]) <= 1e-9 * ms[4]
