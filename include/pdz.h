@@ -494,13 +494,15 @@ pdz_status pdz_batch_destroy(pdz_batch b);
  * offsets[n] = length of the packed array. */
 pdz_status pdz_batch_offsets(pdz_batch b, uint64_t* offsets);
 
-/* y_i = H_i x_i for every problem i of the batch, in one launch: work groups
- * walk a list of tiles (problem, group of rows), largest problems first, so
- * the uneven sizes balance across the chip.  x, y: packed device arrays
- * (offsets[n] elements of precision dt), not overlapping.  Each output is
- * summed in the same order as pdz_hv on its problem, so results are bitwise
- * identical to n single calls.  Asynchronous on `stream`; capturable in a
- * HIP graph.  Errors: PDZ_EINVAL. */
+/* y_i = H_i x_i for every problem i of the batch: work groups walk a list of
+ * tiles (problem, group of rows), largest problems first, so the uneven sizes
+ * balance across the chip.  One launch, or two where rows of 33 to 5,022 down
+ * states (a few rows per work group) and others (an element per thread) meet.
+ * x, y: packed device arrays (offsets[n] elements of precision dt), not
+ * overlapping.  Each output is summed in hop-table order, so results are
+ * bitwise identical to n single calls of pdz_hv under plans of that order (all
+ * but the scheduled family, which differs by rounding).  Asynchronous on
+ * `stream`; capturable in a HIP graph.  Errors: PDZ_EINVAL. */
 pdz_status pdz_batch_hv(pdz_batch b, pdz_dtype dt, const void* x, void* y, void* stream);
 
 pdz_status pdz_batch_get_plan(pdz_batch b, pdz_batch_plan* out);

@@ -40,6 +40,7 @@ struct RowsProb {
 };
 
 constexpr int kRowsHops = 8;   // hops whose loads are in flight together
+constexpr uint64_t kRowsMinDn = 33;   // a shorter row leaves half of every wave idle or more
 
 __device__ __forceinline__ float rows_readlane(float v, int l) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));

@@ -1,12 +1,11 @@
 // Batched H.v and Lanczos over many Hubbard clusters of uneven size.
 //
 // The clusters' vectors are packed back to back (each at a 64-element aligned
-// offset).  One launch applies every cluster's H: work groups walk the list of
-// tiles (cluster, group of rows), largest clusters first; a tile is computed
-// whole as in the single-cluster one-pass H.v (hv_rows.h), or, in a batch with
-// rows too long for that, row by row.  Every element is summed by one thread
-// in the same order as the single-cluster H.v, so the results are bitwise
-// identical to pdz_hv on each cluster.
+// offset).  Work groups walk a list of tiles (cluster, group of rows), largest
+// clusters first; the clusters whose rows go with it are computed by tiles of
+// the single-cluster one-pass H.v (hv_rows.h), in one launch, the others element
+// by element in another.  Every element is summed by one thread in the order of
+// the hop tables, diagonal first, whichever form its cluster takes.
 //
 // Batched Lanczos runs the recurrence of k_lanczos.hip for all clusters in
 // lockstep over the packed vectors, unnormalised (v_k = sc_k q_k): per step
@@ -102,8 +101,9 @@ __device__ __forceinline__ double tile_sum(double v) {
 }
 
 // done: per-cluster flags with stride `dstride` ints (NULL: none skipped).
-// dotp: NULL, or one partial sum of x . y per tile.  This form takes any rows
-// that fit the LDS; k_batch_rows below is the fast one.
+// dotp: NULL, or one partial sum of x . y per tile.  One element per thread, so
+// it takes rows of any length that fit the LDS: short ones, flattened over the
+// tile, and those too long for four to lie side by side (rows_form).
 template <typename T, int BLOCK>
 __global__ __launch_bounds__(BLOCK) void k_batch_hv(const BProb* __restrict__ probs, const BTile* __restrict__ tiles,
                                                     uint32_t ntiles, const int* done, int dstride, double* dotp,
@@ -178,9 +178,9 @@ __global__ __launch_bounds__(BLOCK) void k_batch_hv(const BProb* __restrict__ pr
     }
 }
 
-// The same for batches whose rows fit the one-pass tile (four rows side by side
-// in LDS).  32 clusters of the 4x3 and 3x3 tori (8.2e6 elements): 207 us FP64
-// with one element per thread and a device work queue, 108 us so (FP32 145 / 75).
+// The same for clusters in the one-pass tile (four rows side by side in LDS).
+// 32 clusters of the 4x3 and 3x3 tori (8.2e6 elements): 207 us FP64 with one
+// element per thread and a device work queue, 108 us so (FP32 145 / 75).
 template <typename T, int BLOCK>
 __global__ __launch_bounds__(BLOCK, 4) void k_batch_rows(const BProb* __restrict__ probs, const BTile* __restrict__ tiles,
                                                       uint32_t ntiles, const int* done, int dstride, double* dotp,
@@ -569,8 +569,8 @@ struct pdz_batch_s {
     uint32_t* d_chunk_begin = nullptr;   // n + 1
     uint32_t nchunks = 0;
     uint32_t* d_tile_begin = nullptr;    // n first tiles, then n tile counts, for the current plan
+    uint32_t nrows_tiles = 0;            // tiles of k_batch_rows, first in the list; the rest are k_batch_hv's
     uint64_t max_D_dn = 0;
-    bool rows_form = false;              // every tile fits the one-pass form (k_batch_rows)
     pdz_batch_plan plan{0, 0, 0, 0};
     pdz_batch_plan tiles_for{-1, -1, -1, -1};
 };
@@ -598,12 +598,25 @@ bool plan_ok(const pdz_batch_s* b, const pdz_batch_plan& p) {
     return te && bl && wg && od && fits;
 }
 
+// Whether a cluster's tiles take the one-pass form (k_batch_rows): four rows in
+// LDS in FP64, byte offsets of its elements in 32 bits, and rows of at least 33
+// columns.  One product of a batch in us, one-pass form against k_batch_hv
+// (FP64, FP32): 16 x (4x4 8+1, 16 columns) 183 / 82, 123 / 68; 512 x (ring of 8
+// 4+2, 28 columns) 17.6 / 14.2, 13.4 / 12.0; 512 x (ring of 7 3+3, 35 columns)
+// 10.7 / 10.5, 9.0 / 9.2; 256 x (3x3 4+2, 36 columns) 32 / 42, 22 / 28; and with
+// the device work queue k_batch_hv once had, 2 x (5x3 6+6, 5005 columns)
+// 1044 / 1820, 502 / 1420.
+bool rows_form(const pdz_problem q) {
+    return q->dn.D >= kRowsMinDn && q->D <= 0xFFFFFFFFull / 8 &&
+           kMaxCoef * 8 + (q->dn.D + 1) * kBatchRV * 8 <= kBatchLds;
+}
+
 // Rows per tile of a cluster: about tile_elems elements, whole groups of
 // kBatchRV rows in the one-pass form, no more than the LDS holds.
-uint64_t tile_rows(const pdz_batch_s* b, const pdz_problem q, int tile_elems) {
+uint64_t tile_rows(const pdz_problem q, int tile_elems) {
     const uint64_t Dn = q->dn.D;
     uint64_t rows = (uint64_t)tile_elems / Dn;
-    if (b->rows_form) {
+    if (rows_form(q)) {
         rows = rows / kBatchRV * kBatchRV;
         return rows < kBatchRV ? kBatchRV : rows;
     }
@@ -612,26 +625,18 @@ uint64_t tile_rows(const pdz_batch_s* b, const pdz_problem q, int tile_elems) {
     return rows < 1 ? 1 : rows;
 }
 
-// Whether every tile fits the one-pass form: four rows of the widest cluster in
-// FP64, byte offsets of a cluster's elements in 32 bits.
-bool rows_form_fits(const pdz_batch_s* b) {
-    for (const pdz_problem q : b->problems)
-        if (q->D > 0xFFFFFFFFull / 8) return false;
-    return kMaxCoef * 8 + (b->max_D_dn + 1) * kBatchRV * 8 <= kBatchLds;
-}
-
 // Most tiles of any plan (the smallest tiles).
 size_t max_tiles(const pdz_batch_s* b) {
     size_t n = 0;
     for (const pdz_problem q : b->problems) {
-        const uint64_t rows = tile_rows(b, q, 1024);
+        const uint64_t rows = tile_rows(q, 1024);
         n += (size_t)((q->up.D + rows - 1) / rows);
     }
     return n;
 }
 
-// Tiles: rows of each cluster in groups of about tile_elems elements;
-// order 1 = largest clusters first, 2 = cluster order.
+// Tiles: rows of each cluster in groups of about tile_elems elements, the
+// one-pass form's first; order 1 = largest clusters first, 2 = cluster order.
 pdz_status build_tiles(pdz_batch_s* b, const pdz_batch_plan& p) {
     if (b->d_tiles && b->tiles_for.tile_elems == p.tile_elems && b->tiles_for.order == p.order) return ok();
     std::vector<int> idx(b->n);
@@ -640,10 +645,12 @@ pdz_status build_tiles(pdz_batch_s* b, const pdz_batch_plan& p) {
         std::stable_sort(idx.begin(), idx.end(), [&](int a, int c) { return b->problems[a]->D > b->problems[c]->D; });
     std::vector<BTile> tiles;
     std::vector<uint32_t> range(2 * (size_t)b->n);
+    std::stable_partition(idx.begin(), idx.end(), [&](int i) { return rows_form(b->problems[i]); });
+    uint32_t nrows_tiles = 0;
     for (int i : idx) {
         const pdz_problem q = b->problems[i];
         const uint64_t Du = q->up.D;
-        const uint64_t rows = tile_rows(b, q, p.tile_elems);
+        const uint64_t rows = tile_rows(q, p.tile_elems);
         range[i] = (uint32_t)tiles.size();
         for (uint64_t u0 = 0; u0 < Du; u0 += rows) {
             BTile t;
@@ -654,6 +661,7 @@ pdz_status build_tiles(pdz_batch_s* b, const pdz_batch_plan& p) {
             tiles.push_back(t);
         }
         range[b->n + i] = (uint32_t)tiles.size() - range[i];
+        if (rows_form(q)) nrows_tiles = (uint32_t)tiles.size();
     }
     if (b->d_tiles) (void)hipFree(b->d_tiles);
     b->d_tiles = nullptr;
@@ -661,6 +669,7 @@ pdz_status build_tiles(pdz_batch_s* b, const pdz_batch_plan& p) {
     PDZ_HIP(hipMemcpy(b->d_tiles, tiles.data(), tiles.size() * sizeof(BTile), hipMemcpyHostToDevice));
     PDZ_HIP(hipMemcpy(b->d_tile_begin, range.data(), range.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
     b->ntiles = (uint32_t)tiles.size();
+    b->nrows_tiles = nrows_tiles;
     b->tiles_for = p;
     return ok();
 }
@@ -672,26 +681,29 @@ pdz_status batch_hv_launch(pdz_batch_s* b, const pdz_batch_plan& p, const T* x, 
     DeviceCtx* ctx = nullptr;
     pdz_status st = device_ctx(&ctx);
     if (st != PDZ_OK) return st;
-    size_t max_tile = 0;   // elements
+    size_t max_tile[2] = {0, 0};   // elements of a tile's LDS: k_batch_rows, k_batch_hv
     for (const pdz_problem q : b->problems) {
-        const uint64_t rows = std::min<uint64_t>(tile_rows(b, q, p.tile_elems), q->up.D);
-        const size_t n = b->rows_form ? (size_t)(rows + kBatchRV - 1) / kBatchRV * kBatchRV * (q->dn.D + 1)
-                                      : (size_t)rows * q->dn.D;
-        max_tile = std::max(max_tile, n);
+        const uint64_t rows = std::min<uint64_t>(tile_rows(q, p.tile_elems), q->up.D);
+        if (rows_form(q))
+            max_tile[0] = std::max(max_tile[0], (size_t)(rows + kBatchRV - 1) / kBatchRV * kBatchRV * (q->dn.D + 1));
+        else
+            max_tile[1] = std::max(max_tile[1], (size_t)rows * q->dn.D);
     }
-    const size_t lds = (kMaxCoef + max_tile) * sizeof(T);
-    const dim3 grid(std::min<unsigned>((unsigned)(ctx->cu_count * p.wgs_per_cu), b->ntiles)), block((unsigned)p.block);
-    const auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, grid, block, lds, s, b->d_probs, b->d_tiles, b->ntiles, done, dstride, dotp, x, y);
+    const auto launch = [&](auto kernel, int form, uint32_t t0, uint32_t n) {
+        const dim3 grid(std::min<unsigned>((unsigned)(ctx->cu_count * p.wgs_per_cu), n)), block((unsigned)p.block);
+        hipLaunchKernelGGL(kernel, grid, block, (kMaxCoef + max_tile[form]) * sizeof(T), s, b->d_probs, b->d_tiles + t0,
+                           n, done, dstride, dotp ? dotp + t0 : nullptr, x, y);
     };
-    if (b->rows_form) {
-        if (p.block == 1024) launch(k_batch_rows<T, 1024>);
-        else if (p.block == 512) launch(k_batch_rows<T, 512>);
-        else launch(k_batch_rows<T, 256>);
-    } else {
-        if (p.block == 1024) launch(k_batch_hv<T, 1024>);
-        else if (p.block == 512) launch(k_batch_hv<T, 512>);
-        else launch(k_batch_hv<T, 256>);
+    const uint32_t nr = b->nrows_tiles, ng = b->ntiles - nr;
+    if (nr > 0) {
+        if (p.block == 1024) launch(k_batch_rows<T, 1024>, 0, 0, nr);
+        else if (p.block == 512) launch(k_batch_rows<T, 512>, 0, 0, nr);
+        else launch(k_batch_rows<T, 256>, 0, 0, nr);
+    }
+    if (ng > 0) {
+        if (p.block == 1024) launch(k_batch_hv<T, 1024>, 1, nr, ng);
+        else if (p.block == 512) launch(k_batch_hv<T, 512>, 1, nr, ng);
+        else launch(k_batch_hv<T, 256>, 1, nr, ng);
     }
     PDZ_HIP(hipGetLastError());
     return ok();
@@ -1018,7 +1030,6 @@ pdz_status pdz_batch_create(const pdz_problem* problems, int32_t n, pdz_batch* o
     BCK(hipMalloc(&b->d_tile_begin, 2 * (size_t)n * sizeof(uint32_t)));
 #undef BCK
     if (!plan_ok(b, resolve(b))) return cleanup(fail(PDZ_ERANGE, "a cluster row does not fit the batched kernel's LDS"));
-    b->rows_form = rows_form_fits(b);
     pdz_status st = build_tiles(b, resolve(b));
     if (st != PDZ_OK) return cleanup(st);
     *out = b;

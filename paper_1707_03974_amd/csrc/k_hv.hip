@@ -1419,7 +1419,6 @@ bool wide_down(const pdz_problem_s* p, size_t es) { return p->dn.D >= (uint64_t)
 // -> 225 / 116; 705432 x 231 11970 / 7290 -> 2185 / 1110.  Rows of more than
 // 4 MB in all are read past the L2 of every XCD by the up hops.
 constexpr int kRowsPlan = 8;
-constexpr uint64_t kRowsMinDn = 33;
 constexpr uint64_t kRowsFewPieces = 2560;
 bool rows_available(const pdz_problem_s* p, uint64_t pitch) {
     return p->hv_path == 0 && p->dn.D >= kRowsMinDn && p->dn.D < (uint64_t)kWideBlock &&

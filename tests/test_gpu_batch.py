@@ -279,3 +279,46 @@ def test_batch_plan_cache_round_trip(tmp_path):
     assert t2 is None and e2 == e1
     got = b.get_plan()
     assert all(got[k] == e1[k] for k in ("tile_elems", "block", "wgs_per_cu", "order"))
+
+
+# Rows on both sides of each bound of the one-pass tile (33 and 5,022 down states), alone and together.
+FORMS = [
+    (13, [(i, (i + 1) % 13, 1.0) for i in range(13)], 3.0, 3, 1),      # 13 columns
+    (8, [(i, (i + 1) % 8, 1.0) for i in range(8)], 2.0, 4, 2),         # 28
+    (7, [(i, (i + 1) % 7, 1.0) for i in range(7)], 4.0, 3, 3),         # 35
+    (11, [(i, (i + 1) % 11, -0.5) for i in range(11)], 5.0, 5, 4),     # 330
+    (15, [(i, (i + 1) % 15, 1.0) for i in range(15)], 4.0, 2, 6),      # 5,005
+    (15, [(i, (i + 1) % 15, 1.0) for i in range(15)], 4.0, 1, 7),      # 6,435
+]
+
+
+@pytest.mark.parametrize("dtype_name", ["f64", "f32"])
+@pytest.mark.parametrize("pick", [(0, 1), (2, 3, 4), (5,), (4, 0, 3, 5, 1, 2)])
+def test_clusters_of_either_form_equal_single_products_bitwise(dtype_name, pick):
+    torch = torch_cuda()
+    dt = torch.float64 if dtype_name == "f64" else torch.float32
+    probs, b = _make([FORMS[i] for i in pick])
+    xs = [to_dev(synth.random_vector(q.D, 7 + i), dt) for i, q in enumerate(probs)]
+    ref = []
+    for q, x in zip(probs, xs):
+        if q.info["D_dn"] >= 1024:
+            q.set_plan(dtype_name, 2, 0, 0, 0)      # rows this long default to the scheduled order
+        ref.append(q.hv(x))
+    X = b.pack(xs)
+    for te, block, wgs, order in ((0, 0, 0, 0), (1024, 256, 1, 1), (2048, 1024, 2, 2), (8192, 512, 8, 1)):
+        b.set_plan(te, block, wgs, order)
+        Y = b.hv(X)
+        for i, y in enumerate(b.unpack(Y)):
+            assert torch.equal(y, ref[i]), (te, order, i)
+
+
+def test_batched_lanczos_over_clusters_of_both_forms():
+    torch_cuda()
+    probs, b = _make([FORMS[i] for i in (4, 0, 3, 5, 1, 2)])
+    for order in (1, 2):
+        b.set_plan(1024, 0, 0, order)
+        res, st = b.lanczos(max_iter=400, tol=1e-11, seed=2)
+        assert st == 0
+        for i, q in enumerate(probs):
+            e = q.lanczos(max_iter=400, tol=1e-11, seed=2 + i)["E0"]
+            assert abs(res[i]["E0"] - e) <= 1e-9 * abs(e)
