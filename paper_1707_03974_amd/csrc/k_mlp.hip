@@ -279,8 +279,11 @@ __global__ __launch_bounds__(256, BASIS ? 3 : 2) void k_mlp_fwd(const uint16_t* 
 // weights in registers (40 loads of 16 bytes a lane, all in flight at once,
 // instead of staging them through LDS behind a barrier).  A training gradient
 // of 4096 states took 74 us with the kernel above at 16 states a wave, 66 us
-// with this one (nothing else changed).  prm 16-byte aligned.
-constexpr uint64_t kFwdFew = 16384;
+// with this one (nothing else changed).  Up to eight waves a CU, where the two
+// meet (this one / the one above, us, without and with activations): 16,385
+// states 8.2 / 11.3 and 11.8 / 15.4, 32,768 states 11.5 / 11.5 and 16.4 / 16.6,
+// 40,000 states 16.0 / 11.7 and 21.2 / 18.4.  prm 16-byte aligned.
+constexpr uint64_t kFwdFew = 32768;
 __global__ __launch_bounds__(64) void k_mlp_fwd_few(const uint16_t* __restrict__ prm,
                                                     const uint32_t* __restrict__ occ, uint64_t n,
                                                     float* __restrict__ out, Act act, int act_wide) {

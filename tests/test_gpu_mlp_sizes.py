@@ -1,6 +1,6 @@
 """Sizes and alignments at which the network kernels change their split.
 
-Forward: one wave per 16 states up to 16,384 states, 64 states per wave above; ragged tails; parameters
+Forward: one wave per 16 states up to 32,768 states, 64 states per wave above; ragged tails; parameters
 and activations that are not 16-byte aligned.  Backward: chunks of 64 states, one slice per work group,
 256 slices at most.  Loss: one work group up to 8,192 states.  Bounds as in test_gpu_mlp: 1e-2 relative
 for outputs and gradients (BF16 activations), FP32 rounding for the loss.
@@ -124,3 +124,20 @@ def test_a_state_that_is_not_a_number_stays_alone(sites):
     expect = torch.exp(o[:, 0].clamp(max=60.0)) * torch.where(o[:, 1] >= 0, 1.0, -1.0)
     assert 0.2 < ok.double().mean().item() < 0.8
     assert torch.allclose(v[ok], expect[ok], rtol=1e-13, atol=0.0)
+
+
+@pytest.mark.parametrize("n", [32767, 32768, 32769, 33000])
+def test_forward_where_the_kernel_changes(n):
+    """The kernel of long lists and the one of short lists (each list in two halves) give the same bits."""
+    torch = torch_cuda()
+    net, _ = _net(15)
+    occ = _occ(*_states(np.random.default_rng(n), n))
+    act = torch.empty(n * 384, dtype=torch.int16, device="cuda")
+    out = net.forward(occ, act=act)
+    for a, b in ((0, n // 2), (n // 2, n)):
+        m = b - a
+        part_act = torch.empty(m * 384, dtype=torch.int16, device="cuda")
+        assert torch.equal(net.forward(occ[a:b].contiguous(), act=part_act), out[a:b])
+        assert torch.equal(part_act[:m * 128], act[a * 128:b * 128])
+        assert torch.equal(part_act[m * 128:2 * m * 128].view(128, m), act[n * 128:2 * n * 128].view(128, n)[:, a:b])
+        assert torch.equal(part_act[2 * m * 128:], act[(2 * n + a) * 128:(2 * n + b) * 128])
