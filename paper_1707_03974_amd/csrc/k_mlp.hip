@@ -781,11 +781,15 @@ SampWs samp_ws(uint64_t D) {
     return w;
 }
 
-int fwd_grid(uint64_t n) {
+// Work groups of the forward pass: as many as are resident, so that each walks the
+// same number of turns.  Three a CU fit in the basis form (168 registers, 50 KB of
+// LDS), two in the list form (244 registers): with three, list passes of 200,000,
+// 262,144 and 400,000 states took 30.1, 31.3 and 46.5 us, with two 27.9, 28.8, 43.9.
+int fwd_grid(uint64_t n, int per_cu) {
     DeviceCtx* ctx = nullptr;
     const int cu = (device_ctx(&ctx) == PDZ_OK && ctx) ? ctx->cu_count : 256;
     const uint64_t groups = (n + kFwdStates - 1) / kFwdStates;
-    const uint64_t g = (uint64_t)cu * 3;   // three work groups fit a CU (50 KB of LDS, 168 registers)
+    const uint64_t g = (uint64_t)cu * per_cu;
     return (int)(groups < g ? groups : g);
 }
 
@@ -879,7 +883,7 @@ pdz_status pdz_mlp_forward(const uint16_t* params_bf16, const uint32_t* occ, uin
         hipLaunchKernelGGL(k_mlp_fwd_few, dim3((unsigned)((n + 15) / 16)), dim3(64), 0, (hipStream_t)stream,
                            params_bf16, occ, n, out, a, act_wide);
     else
-        hipLaunchKernelGGL((k_mlp_fwd<float, false>), dim3(fwd_grid(n)), dim3(256), 0, (hipStream_t)stream,
+        hipLaunchKernelGGL((k_mlp_fwd<float, false>), dim3(fwd_grid(n, 2)), dim3(256), 0, (hipStream_t)stream,
                            params_bf16, src, n, out, a, act_wide, (float*)nullptr);
     PDZ_HIP(hipGetLastError());
     return ok();
@@ -997,10 +1001,10 @@ pdz_status pdz_start_vector(pdz_problem p, const uint16_t* params_bf16, pdz_dtyp
     const Act none = act_views(nullptr, 0);
     hipStream_t s = (hipStream_t)stream;
     if (dt == PDZ_F64)
-        hipLaunchKernelGGL((k_mlp_fwd<double, true>), dim3(fwd_grid(p->D)), dim3(256), 0, s, params_bf16, src, p->D,
+        hipLaunchKernelGGL((k_mlp_fwd<double, true>), dim3(fwd_grid(p->D, 3)), dim3(256), 0, s, params_bf16, src, p->D,
                            (float*)nullptr, none, 0, static_cast<double*>(v0));
     else
-        hipLaunchKernelGGL((k_mlp_fwd<float, true>), dim3(fwd_grid(p->D)), dim3(256), 0, s, params_bf16, src, p->D,
+        hipLaunchKernelGGL((k_mlp_fwd<float, true>), dim3(fwd_grid(p->D, 3)), dim3(256), 0, s, params_bf16, src, p->D,
                            (float*)nullptr, none, 0, static_cast<float*>(v0));
     PDZ_HIP(hipGetLastError());
     return ok();
