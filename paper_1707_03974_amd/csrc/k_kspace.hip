@@ -70,7 +70,7 @@ struct KSpace {
     uint8_t* d_dcnt = nullptr;      // down moves of (string, q): [momentum][q][rank], pitch Lp, 0 past Ld
     void* d_dtab = nullptr;         // entries: source rank | sign in the top bit (16 bits when every
                                     // momentum has < 2^15 down strings, else 32), slot major per
-                                    // (momentum, q) with pitch Lp
+                                    // (momentum, q) with pitch Lp; none where both precisions take groups
     bool dtab16 = false;
     int uslots = 0;                 // most up moves of one string for one q
     uint64_t* d_upm = nullptr;      // D_up x (N-1) x uslots: source row start | sign << 63 of each up
@@ -83,8 +83,9 @@ struct KSpace {
     // H.v over groups of rows (k_hvk_rows; groups == 0: not used)
     uint32_t groups[2] = {0, 0};        // FP64, FP32
     uint32_t* d_groups[2] = {nullptr, nullptr};   // first row of the group in d_rows << 3 | its rows
-    uint16_t* d_gtab = nullptr;     // d_dtab with kz_pos positions and a zero for every slot past the count
-    uint8_t* d_gmax = nullptr;      // N x N: most down moves of one string of (target momentum, q)
+    uint32_t* d_gmax = nullptr;     // N x N: most down moves of one string of (target momentum, q)
+    uint32_t* d_gbuf = nullptr;     // the allocation of the group lists and d_gmax
+    uint16_t* d_gtab = nullptr;     // the down-move table as k_hvk_rows reads it (kg_entry), laid out as d_dtab
 };
 
 namespace {
@@ -221,12 +222,28 @@ __global__ __launch_bounds__(kKBlock) void k_kdn_states(const KArgs a, uint32_t*
     }
 }
 
+template <typename T>
+constexpr int kKRows = 16 / (int)sizeof(T);   // R
+// Position of element d in Z: one in five left out, so that the E stores of
+// neighbouring threads (64 bytes apart without it) fall into different banks.
+__host__ __device__ constexpr uint32_t kz_pos(uint32_t d) { return d + (d >> 2); }
+__host__ __device__ constexpr uint32_t kz_len(uint32_t Lmax) { return kz_pos(Lmax - 1) + 2; }   // the last one: -0.0
+constexpr uint32_t kKRowsMaxZ = 2048;   // positions: byte offsets of 15 bits
+
+// The down-move table k_hvk_rows reads: the LDS byte offset of the source (16
+// bytes a position) and the sign, below it for an even column, above for an odd
+// one.  Slots past a string's count, and columns past the last, name the
+// position of -0.0.
+__device__ __forceinline__ uint16_t kg_entry(uint32_t column, uint32_t d, uint32_t neg) {
+    return (uint16_t)(kz_pos(d) << 4 | (column & 1u ? neg << 15 : neg));
+}
+
 // Down-move table: for target string d' (momentum kd) and q != 0, every
 // electron p' (ascending) with p' + q empty gives the source string
 // d' - p' + (p' + q) of momentum kd + q; its rank comes from the forward map.
 template <typename TE>
 __global__ __launch_bounds__(kKBlock) void k_kdn_moves(const KArgs a, int slots, uint8_t* dcnt, TE* dtab,
-                                                        uint32_t* err) {
+                                                        uint16_t* gtab, uint32_t* err) {
     constexpr TE neg = (TE)((TE)1 << (8 * sizeof(TE) - 1));
     __shared__ uint8_t skadd[kMaxSites * kMaxSites];
     stage_kadd(skadd, a.kadd, a.N);
@@ -258,7 +275,9 @@ __global__ __launch_bounds__(kKBlock) void k_kdn_moves(const KArgs a, int slots,
                 atomicOr(err, kErrTable);
                 continue;
             }
-            dtab[tb + (uint64_t)s * L + dp] = (TE)(d | (odd_between(phi, p, pp) ? neg : (TE)0));
+            const bool odd = odd_between(phi, p, pp);
+            if (dtab) dtab[tb + (uint64_t)s * L + dp] = (TE)(d | (odd ? neg : (TE)0));
+            if (gtab) gtab[tb + (uint64_t)s * L + dp] = kg_entry((uint32_t)dp, d, odd);
             ++s;
         }
         dcnt[cidx] = (uint8_t)s;
@@ -717,13 +736,6 @@ __global__ __launch_bounds__(kKBlock) void k_hvk(const KArgs a, const T* __restr
 // moves (386 us at 4 waves).  4x4 with diagonals, 8+8, K = 0, against one row
 // per work group: FP32 595 -> 260 us, FP64 980 -> 578 us; 5x3 7+7 226 -> 66 us
 // and 249 -> 88 us.
-template <typename T>
-constexpr int kKRows = 16 / (int)sizeof(T);   // R
-// Position of element d in Z: one in five left out, so that the E stores of
-// neighbouring threads (64 bytes apart without it) fall into different banks.
-__host__ __device__ constexpr uint32_t kz_pos(uint32_t d) { return d + (d >> 2); }
-__host__ __device__ constexpr uint32_t kz_len(uint32_t Lmax) { return kz_pos(Lmax - 1) + 2; }   // the last one: -0.0
-constexpr uint32_t kKRowsMaxZ = 2048;   // positions: byte offsets of 15 bits
 // A group takes longer than a row (its q run one after another, R rows at a
 // time), so it pays where rows fill the chip several times over or are long.
 // 4x4 4+4 (114 columns): 1.8 groups a CU 37.7 us by rows and 36.0 by groups;
@@ -731,24 +743,6 @@ constexpr uint32_t kKRowsMaxZ = 2048;   // positions: byte offsets of 15 bits
 // groups a CU 77 and 43; 5x3 3+7 (429 columns): 0.4 groups a CU 39.1 and 34.5.
 constexpr int kKRowsMin = 4;              // groups per CU
 constexpr uint32_t kKRowsLong = 256;      // or columns
-
-// One block per (target momentum, q).
-__global__ __launch_bounds__(kKBlock) void k_kgtab(const KArgs a, uint16_t* gtab) {
-    const uint16_t* dtab = static_cast<const uint16_t*>(a.dtab);
-    const uint32_t none = kz_len(a.Lmax) - 1;
-    const int k = blockIdx.x / a.N, q = blockIdx.x % a.N;
-    if (q == 0) return;
-    const uint32_t L = a.Lp[k];
-    const uint64_t tb = a.tb_off[k * a.N + q];
-    const uint8_t* cnt = a.dcnt + a.cnt_off[k] + (uint64_t)q * L;
-    for (uint32_t d = threadIdx.x; d < L; d += kKBlock)
-        for (int s = 0; s < a.slots; ++s) {
-            const uint64_t i = tb + (uint64_t)s * L + d;
-            const uint32_t e = dtab[i], real = s < (int)cnt[d] ? 1u : 0u;
-            const uint32_t pos = real ? kz_pos(e & 0x7FFFu) : none, neg = real & (e >> 15);
-            gtab[i] = (uint16_t)(d & 1u ? neg << 15 | pos << 4 : pos << 4 | neg);
-        }
-}
 
 // +-1 by the top bit of v.
 __device__ __forceinline__ float k_pm1(uint32_t v, float) { return __uint_as_float(0x3F800000u | (v & 0x80000000u)); }
@@ -771,7 +765,7 @@ __device__ __forceinline__ void kvec_load_global(const T __attribute__((address_
 template <typename T, int E, int BLOCK>
 __global__ __launch_bounds__(BLOCK, E <= 4 ? 7 : 4) void k_hvk_rows(const KArgs a, const uint32_t* __restrict__ groups,
                                                          uint32_t ngroups, const uint16_t* __restrict__ gtab,
-                                                         const uint8_t* __restrict__ gmax, const T* __restrict__ x,
+                                                         const uint32_t* __restrict__ gmax, const T* __restrict__ x,
                                                          T* __restrict__ y, const int* skip) {
     if (skip && *skip) return;
     constexpr int R = kKRows<T>;
@@ -1117,7 +1111,7 @@ void kspace_free(KSpace* ks) {
     void* ptrs[] = {ks->d_kadd,   ks->d_Ck,      ks->d_Ct,     ks->d_Ld,      ks->d_dn_off, ks->d_tb_off,
                     ks->d_Lp,     ks->d_cnt_off, ks->d_eps,    ks->d_dn_str,  ks->d_eps_dn, ks->d_dcnt,
                     ks->d_dtab,   ks->d_up_str,  ks->d_row_off, ks->d_row_kd, ks->d_eps_up, ks->d_rows,
-                    ks->d_upm,    ks->d_groups[0], ks->d_groups[1], ks->d_gtab,  ks->d_gmax};
+                    ks->d_upm,    ks->d_gbuf,    ks->d_gtab};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
     delete ks;
@@ -1239,16 +1233,34 @@ pdz_status kspace_build(pdz_problem_s* p, int L1, int L2, const double* eps, int
     if ((st = alloc(&ks->d_eps_dn, ks->D_dn)) != PDZ_OK) return st;
     if ((st = alloc(&ks->d_dcnt, ks->cnt_off[N])) != PDZ_OK) return st;
     PDZ_HIP(hipMemset(ks->d_dcnt, 0, ks->cnt_off[N]));   // padding past Ld: no moves
-    if (ks->dtab16) {
-        uint16_t* t = nullptr;
-        if ((st = alloc(&t, ks->entries)) != PDZ_OK) return st;
-        ks->d_dtab = t;
-    } else {
-        uint32_t* t = nullptr;
-        if ((st = alloc(&t, ks->entries)) != PDZ_OK) return st;
-        ks->d_dtab = t;
+    // Groups of rows of one down momentum, where k_hvk_rows takes them (FP64, FP32).
+    const unsigned cu = (unsigned)ctx->cu_count;
+    std::vector<uint64_t> rows_kd(N, 0);   // non-empty rows of each down momentum
+    for (int ku = 0; ku < N; ++ku) {
+        const int kd = kadd(K, kneg(ku));
+        if (ks->Ld[kd] > 0) rows_kd[kd] = C[Cix(N, nu, ku)];
     }
-    PDZ_HIP(hipMemset(ks->d_dtab, 0, ks->entries * (ks->dtab16 ? 2 : 4)));
+    for (int f = 0; f < 2; ++f) {
+        const uint64_t R = f == 0 ? kKRows<double> : kKRows<float>;
+        uint64_t n = 0, nrows = 0;
+        for (int k = 0; k < N; ++k) {
+            n += (rows_kd[k] + R - 1) / R;
+            nrows += rows_kd[k];
+        }
+        if (ks->dtab16 && ks->entries < (1ull << 48) && kz_len(ks->Lmax) <= kKRowsMaxZ && ks->slots > 0 &&
+            ks->uslots > 0 && N > 1 && nrows < (1u << 29) && (n >= (uint64_t)kKRowsMin * cu || ks->Lmax > kKRowsLong))
+            ks->groups[f] = (uint32_t)n;
+    }
+    if (ks->groups[0] || ks->groups[1]) {
+        if ((st = alloc(&ks->d_gtab, ks->entries)) != PDZ_OK) return st;
+        PDZ_HIP(hipMemsetD16(reinterpret_cast<hipDeviceptr_t>(ks->d_gtab), (uint16_t)((kz_len(ks->Lmax) - 1) << 4),
+                             ks->entries));
+    }
+    if (!ks->groups[0] || !ks->groups[1]) {
+        const size_t bytes = std::max<uint64_t>(1, ks->entries) * (ks->dtab16 ? 2 : 4);
+        PDZ_HIP(hipMalloc(&ks->d_dtab, bytes));
+        PDZ_HIP(hipMemset(ks->d_dtab, 0, bytes));
+    }
     if ((st = alloc(&ks->d_upm, ks->D_up * (uint64_t)(N > 1 ? N - 1 : 0) * ks->uslots)) != PDZ_OK) return st;
     if ((st = alloc(&ks->d_up_str, ks->D_up)) != PDZ_OK) return st;
     if ((st = alloc(&ks->d_row_off, ks->D_up)) != PDZ_OK) return st;
@@ -1256,16 +1268,15 @@ pdz_status kspace_build(pdz_problem_s* p, int L1, int L2, const double* eps, int
     if ((st = alloc(&ks->d_eps_up, ks->D_up)) != PDZ_OK) return st;
 
     const KArgs a = kargs(p);
-    const unsigned cu = (unsigned)ctx->cu_count;
     hipLaunchKernelGGL(k_kdn_states, dim3(grid_for(ks->D_dn, cu)), dim3(kKBlock), 0, nullptr, a, ks->d_dn_str,
                        ks->d_eps_dn, err);
     PDZ_HIP(hipGetLastError());
     if (ks->dtab16)
         hipLaunchKernelGGL(k_kdn_moves<uint16_t>, dim3(grid_for(ks->D_dn * N, cu)), dim3(kKBlock), 0, nullptr, a,
-                           ks->slots, ks->d_dcnt, static_cast<uint16_t*>(ks->d_dtab), err);
+                           ks->slots, ks->d_dcnt, static_cast<uint16_t*>(ks->d_dtab), ks->d_gtab, err);
     else
         hipLaunchKernelGGL(k_kdn_moves<uint32_t>, dim3(grid_for(ks->D_dn * N, cu)), dim3(kKBlock), 0, nullptr, a,
-                           ks->slots, ks->d_dcnt, static_cast<uint32_t*>(ks->d_dtab), err);
+                           ks->slots, ks->d_dcnt, static_cast<uint32_t*>(ks->d_dtab), (uint16_t*)nullptr, err);
     PDZ_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_krows, dim3(grid_for(ks->D_up, cu)), dim3(kKBlock), 0, nullptr, a, ctx->binom, ks->d_up_str,
                        ks->d_row_off, ks->d_row_kd, ks->d_eps_up);
@@ -1301,51 +1312,46 @@ pdz_status kspace_build(pdz_problem_s* p, int L1, int L2, const double* eps, int
     for (int k = 0; k < N; ++k) rows.insert(rows.end(), by_kd[k].begin(), by_kd[k].end());
     ks->nrows = rows.size();
     if ((st = upload(&ks->d_rows, rows)) != PDZ_OK) return st;
-    // Groups of rows of one down momentum, where k_hvk_rows takes them.
-    const bool fits = ks->dtab16 && ks->entries < (1ull << 48) && kz_len(ks->Lmax) <= kKRowsMaxZ && ks->slots > 0 && ks->uslots > 0 && N > 1;
-    for (int f = 0; fits && f < 2; ++f) {
-        const uint32_t R = f == 0 ? kKRows<double> : kKRows<float>;
-        std::vector<uint32_t> gr;
-        uint32_t pos = 0;
-        for (int k = 0; k < N; ++k) {
-            for (size_t i = 0; i < by_kd[k].size(); i += R)
-                gr.push_back((uint32_t)(pos + i) << 3 | (uint32_t)std::min<size_t>(R, by_kd[k].size() - i));
-            pos += (uint32_t)by_kd[k].size();
-        }
-        if ((gr.size() < (size_t)kKRowsMin * cu && ks->Lmax <= kKRowsLong) || ks->nrows >= (1u << 29)) continue;
-        if ((st = upload(&ks->d_groups[f], gr)) != PDZ_OK) return st;
-        ks->groups[f] = (uint32_t)gr.size();
-    }
-    if (ks->groups[0] || ks->groups[1]) {
-        std::vector<uint8_t> gm((size_t)N * N, 0);
-        for (int k = 0; k < N; ++k)
-            for (int q = 1; q < N; ++q) {
-                const uint8_t* c = cnt.data() + ks->cnt_off[k] + (uint64_t)q * ks->Lp[k];
-                for (uint32_t d = 0; d < ks->Ld[k]; ++d) gm[(size_t)k * N + q] = std::max(gm[(size_t)k * N + q], c[d]);
-            }
-        if ((st = upload(&ks->d_gmax, gm)) != PDZ_OK) return st;
-        if ((st = alloc(&ks->d_gtab, ks->entries)) != PDZ_OK) return st;
-        hipLaunchKernelGGL(k_kgtab, dim3(N * N), dim3(kKBlock), 0, nullptr, kargs(p), ks->d_gtab);
-        PDZ_HIP(hipGetLastError());
-        PDZ_HIP(hipStreamSynchronize(nullptr));
-    }
     // structural nonzeros: D diagonal entries plus, per row and q, up moves x down moves
     std::vector<uint64_t> mdn((size_t)N * N, 0);   // [momentum][q]: down moves summed over the strings
+    const size_t g0 = (size_t)N * N, g1 = g0 + ks->groups[0];   // d_gbuf: gmax, the FP64 and the FP32 groups
+    std::vector<uint32_t> gbuf(g0, 0);
     for (int k = 0; k < N; ++k)
         for (int q = 1; q < N; ++q) {
             uint64_t sum = 0;
+            uint8_t most = 0;
             const uint8_t* c = cnt.data() + ks->cnt_off[k] + (uint64_t)q * ks->Lp[k];
             for (uint32_t d = 0; d < ks->Ld[k]; ++d) sum += c[d];
+            for (uint32_t d = 0; d < ks->Ld[k]; ++d) most = c[d] > most ? c[d] : most;   // vectorises alone
             mdn[(size_t)k * N + q] = sum;
+            gbuf[(size_t)k * N + q] = most;
         }
+    for (int f = 0; f < 2; ++f) {
+        if (!ks->groups[f]) continue;
+        const uint32_t R = f == 0 ? kKRows<double> : kKRows<float>;
+        uint32_t pos = 0;
+        for (int k = 0; k < N; ++k) {
+            const uint32_t n = (uint32_t)by_kd[k].size();
+            for (uint32_t i = 0; i < n; i += R) gbuf.push_back((pos + i) << 3 | std::min(R, n - i));
+            pos += n;
+        }
+    }
+    if (gbuf.size() != g1 + ks->groups[1]) return fail(PDZ_EDEVICE, "row counts of the momenta do not add up");
+    if (ks->d_gtab) {
+        if ((st = upload(&ks->d_gbuf, gbuf)) != PDZ_OK) return st;
+        ks->d_gmax = ks->d_gbuf;
+        ks->d_groups[0] = ks->d_gbuf + g0;
+        ks->d_groups[1] = ks->d_gbuf + g1;
+    }
     uint64_t nnz = D;
     for (uint64_t r = 0; r < ks->D_up; ++r) {
         const uint32_t phi = ups[r];
         for (int q = 1; q < N; ++q) {
+            const int nq = kneg(q);
             uint64_t mu = 0;
             for (uint32_t b = phi; b; b &= b - 1u) {
                 const int pbit = __builtin_ctz(b);
-                if (!((phi >> kadd(pbit, kneg(q))) & 1u)) ++mu;
+                if (!((phi >> kadd(pbit, nq)) & 1u)) ++mu;
             }
             nnz += mu * mdn[(size_t)rkd[r] * N + q];
             if (ks->Ld[rkd[r]] > 0) ks->staged += mu * ks->Ld[kadd(rkd[r], q)];

@@ -29,3 +29,14 @@ CASES = [
 def test_grouped_rows_match_the_oracle(L1, L2, nu, nd, K, dtype_name):
     bonds = _bonds(torus_nnn(L1, L2, 1.0, -0.3))
     _sampled_rows(L1, L2, _eps(L1, L2, bonds), 5.0, nu, nd, K, 160, 11, dtype_name)
+
+
+# groups for FP64 alone (about 1,510 groups of two rows, 760 of four), for neither precision, for both
+TABLES = [(5, 3, 5, 3, 2), (4, 3, 5, 4, 1), (4, 4, 5, 5, 7)]
+
+
+@pytest.mark.parametrize("L1,L2,nu,nd,K", TABLES, ids=["%dx%d_%d+%d_K%d" % c for c in TABLES])
+def test_each_precision_has_the_table_its_kernel_reads(L1, L2, nu, nd, K):
+    bonds = _bonds(torus_nnn(L1, L2, 1.0, -0.3))
+    for dtype_name in ("f32", "f64", "f32"):
+        _sampled_rows(L1, L2, _eps(L1, L2, bonds), 5.0, nu, nd, K, 160, 12, dtype_name)
