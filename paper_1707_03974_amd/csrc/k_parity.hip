@@ -243,6 +243,24 @@ __global__ __launch_bounds__(kPBlock) void k_ppal(const PArgs a, uint4* info, ui
     }
 }
 
+// Up hops of palindromic row kk = t / stride, slot t % stride (slots past its
+// count: zero, not read).
+__global__ __launch_bounds__(kPBlock) void k_ppup(const PArgs a, const uint32_t* rows_pal, uint64_t n_pal,
+                                                  uint64_t* pup) {
+    const uint64_t n = n_pal * (uint64_t)a.pup_stride;
+    for (uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n; t += (uint64_t)gridDim.x * blockDim.x) {
+        const uint64_t kk = t / a.pup_stride, h = t - kk * a.pup_stride;
+        const uint32_t ru = a.row_rank[rows_pal[kk]];
+        uint64_t v = 0;
+        if (h < a.up_cnt[ru]) {
+            const uint32_t e = a.up_ell[h * a.Dup + ru], ru2 = e & kTargetMask;
+            v = (a.row_off[a.urow[ru2]] & kPupOff) | (a.ucls[ru2] == kClsA ? 0 : kPupImage) |
+                (uint64_t)(e >> kTargetBits) << kPupCoef;
+        }
+        pup[t] = v;
+    }
+}
+
 // Rows of palindromic up strings (few): a work group per kPBlock columns (down
 // representatives) of a row, an element's hops in order, kPHopNB at a time.
 // Few waves, so its time is the chain of dependent loads: entry, operand.  4x4
@@ -884,7 +902,7 @@ void parity_free(ParSpace* q) {
     void* ptrs[] = {q->d_ucls, q->d_uinv, q->d_utree, q->d_urow, q->d_dcls, q->d_dinv, q->d_dtree, q->d_dcol,
                     q->d_dlist, q->d_row_rank, q->d_row_off, q->d_row_pal, q->d_S, q->d_rows_full, q->d_rows_pal,
                     q->d_dcolf, q->d_dlistf, q->d_fmir, q->d_fcnt, q->d_fell, q->d_fell2, q->d_fup,
-                    q->d_pinfo, q->d_pcnt, q->d_pell, q->d_pup};
+                    q->d_pinfo};   // with d_pell, d_pup and d_pcnt behind it
     for (void* v : ptrs)
         if (v) (void)hipFree(v);
     void* gptrs[] = {q->d_col_dn, q->d_goff[0], q->d_goff[1], q->d_gnr[0], q->d_gnr[1], q->d_grp_up[0], q->d_grp_up[1]};
@@ -1322,31 +1340,21 @@ pdz_status parity_build(pdz_problem_s* p, int P) {
         }
     }
     if ((st = dupload(&q->d_rows_pal, rows_pal)) != PDZ_OK) return st;
-    if (q->n_pal > 0) {
-        const int mhd = std::max(p->dn.max_hops, 1), mhu = std::max(p->up.max_hops, 1);
-        std::vector<uint8_t> ucnt_h(Du);
-        std::vector<uint32_t> uell_h((size_t)mhu * Du);
-        PDZ_HIP(hipMemcpy(ucnt_h.data(), p->up.count, Du, hipMemcpyDeviceToHost));
-        if (p->up.max_hops > 0) PDZ_HIP(hipMemcpy(uell_h.data(), p->up.ell, (size_t)mhu * Du * 4, hipMemcpyDeviceToHost));
-        std::vector<uint64_t> pup((size_t)rows_pal.size() * mhu, 0);
-        for (size_t kk = 0; kk < rows_pal.size(); ++kk) {
-            const uint32_t ru = row_rank[rows_pal[kk]];
-            for (int h = 0; h < ucnt_h[ru]; ++h) {
-                const uint32_t e = uell_h[(size_t)h * Du + ru];
-                const uint32_t ru2 = e & kTargetMask;
-                pup[kk * mhu + h] = (row_off[urow[ru2]] & kPupOff) | (ucls[ru2] == kClsA ? 0 : kPupImage) |
-                                    (uint64_t)(e >> kTargetBits) << kPupCoef;
-            }
-        }
-        q->pup_stride = mhu;
-        if ((st = dupload(&q->d_pup, pup)) != PDZ_OK) return st;
-        if ((st = dalloc(&q->d_pinfo, q->Lp)) != PDZ_OK) return st;
-        if ((st = dalloc(&q->d_pcnt, q->Lp)) != PDZ_OK) return st;
-        if ((st = dalloc(&q->d_pell, (uint64_t)mhd * q->Lp)) != PDZ_OK) return st;
-        hipLaunchKernelGGL(k_ppal, dim3(pgrid(q->Lp, cu)), dim3(kPBlock), 0, nullptr, pargs(p), q->d_pinfo, q->d_pcnt,
+    if (q->n_pal > 0) {   // one allocation; the copies below wait for the two kernels
+        const uint64_t mhd = std::max(p->dn.max_hops, 1), mhu = std::max(p->up.max_hops, 1);
+        uint8_t* buf = nullptr;
+        if ((st = dalloc(&buf, 16 * q->Lp + 8 * (mhd * q->Lp + mhu * q->n_pal) + q->Lp)) != PDZ_OK) return st;
+        q->d_pinfo = reinterpret_cast<uint4*>(buf);
+        q->d_pell = reinterpret_cast<uint64_t*>(buf + 16 * q->Lp);
+        q->d_pup = q->d_pell + mhd * q->Lp;
+        q->d_pcnt = reinterpret_cast<uint8_t*>(q->d_pup + mhu * q->n_pal);
+        q->pup_stride = (int)mhu;
+        const PArgs pa = pargs(p);
+        hipLaunchKernelGGL(k_ppal, dim3(pgrid(q->Lp, cu)), dim3(kPBlock), 0, nullptr, pa, q->d_pinfo, q->d_pcnt,
                            q->d_pell);
+        hipLaunchKernelGGL(k_ppup, dim3(pgrid(q->n_pal * mhu, cu)), dim3(kPBlock), 0, nullptr, pa, q->d_rows_pal,
+                           q->n_pal, q->d_pup);
         PDZ_HIP(hipGetLastError());
-        PDZ_HIP(hipStreamSynchronize(nullptr));
     }
     if (!q->force_loop && q->n_full > 0 && p->dn.max_hops > 0) {
         // the scheduled down pass: the column hop table's gather schedule
