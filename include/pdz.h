@@ -502,17 +502,23 @@ pdz_status pdz_batch_offsets(pdz_batch b, uint64_t* offsets);
  * overlapping.  Each output is summed in hop-table order, so results are
  * bitwise identical to n single calls of pdz_hv under plans of that order (all
  * but the scheduled family, which differs by rounding).  Asynchronous on
- * `stream`; capturable in a HIP graph.  Errors: PDZ_EINVAL. */
+ * `stream`; capturable in a HIP graph.  Calls on one batch may overlap on
+ * several streams.  Errors: PDZ_EINVAL. */
 pdz_status pdz_batch_hv(pdz_batch b, pdz_dtype dt, const void* x, void* y, void* stream);
 
 pdz_status pdz_batch_get_plan(pdz_batch b, pdz_batch_plan* out);
-/* Errors: PDZ_EINVAL for a plan outside the ranges above. */
+/* The plan, with the tile list made for it, is the only mutable state of a
+ * batch: do not change it while another thread launches on the batch, and
+ * capture graphs again afterwards (one captured before reads the list that is
+ * freed here).  Waits for the device when the list changes.
+ * Errors: PDZ_EINVAL for a plan outside the ranges above. */
 pdz_status pdz_batch_set_plan(pdz_batch b, const pdz_batch_plan* plan);
 
 /* Autotuner: time every plan of the search space on x, y (packed arrays as
  * in pdz_batch_hv; y is overwritten), `reps` launches each after a warm-up,
- * select the fastest and return it in *best.  trials (may be NULL) receives
- * up to max_trials timings, *n_trials their count.  Synchronous. */
+ * select the fastest as pdz_batch_set_plan does and return it in *best.  trials
+ * (may be NULL) receives up to max_trials timings, *n_trials their count.
+ * Synchronous. */
 pdz_status pdz_batch_tune(pdz_batch b, pdz_dtype dt, const void* x, void* y, int32_t reps, pdz_batch_trial* trials,
                           int32_t max_trials, int32_t* n_trials, pdz_batch_plan* best, void* stream);
 

@@ -663,8 +663,11 @@ pdz_status build_tiles(pdz_batch_s* b, const pdz_batch_plan& p) {
         range[b->n + i] = (uint32_t)tiles.size() - range[i];
         if (rows_form(q)) nrows_tiles = (uint32_t)tiles.size();
     }
-    if (b->d_tiles) (void)hipFree(b->d_tiles);
-    b->d_tiles = nullptr;
+    if (b->d_tiles) {
+        PDZ_HIP(hipDeviceSynchronize());   // products in flight read the list
+        (void)hipFree(b->d_tiles);
+        b->d_tiles = nullptr;
+    }
     PDZ_HIP(hipMalloc(&b->d_tiles, tiles.size() * sizeof(BTile)));
     PDZ_HIP(hipMemcpy(b->d_tiles, tiles.data(), tiles.size() * sizeof(BTile), hipMemcpyHostToDevice));
     PDZ_HIP(hipMemcpy(b->d_tile_begin, range.data(), range.size() * sizeof(uint32_t), hipMemcpyHostToDevice));

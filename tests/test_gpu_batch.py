@@ -322,3 +322,25 @@ def test_batched_lanczos_over_clusters_of_both_forms():
         for i, q in enumerate(probs):
             e = q.lanczos(max_iter=400, tol=1e-11, seed=2 + i)["E0"]
             assert abs(res[i]["E0"] - e) <= 1e-9 * abs(e)
+
+
+def test_products_of_one_batch_overlap_on_two_streams():
+    """Products on two streams at once, and a plan change while some are in flight: every y is the one of a
+    product alone."""
+    torch = torch_cuda()
+    probs, b = _make([FORMS[i] for i in (4, 0, 3, 5, 1, 2)])
+    xs = [b.pack([to_dev(synth.random_vector(q.D, 30 * k + i), torch.float64) for i, q in enumerate(probs)])
+          for k in range(2)]
+    ref = [b.hv(x) for x in xs]
+    ys = [[torch.zeros_like(x) for _ in range(12)] for x in xs]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    for r in range(12):
+        if r % 4 == 3:
+            b.set_plan((1024, 8192, 2048)[r // 4], 256 << (r // 4), 1 + r // 4, 1 + r // 4 % 2)
+        for k in range(2):
+            b.hv(xs[k], ys[k][r], stream=streams[k])
+    torch.cuda.synchronize()
+    for k in range(2):
+        for y in ys[k]:
+            assert torch.equal(y, ref[k])
