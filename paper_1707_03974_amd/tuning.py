@@ -2,12 +2,15 @@
 
 Key of a problem: device architecture, lattice (sites and a hash of the bond list), fillings and
 precision.  U does not change the sparsity pattern, so it is not part of the key.  Key of a batch:
-architecture, the ordered list of its problems' keys (hashed) and precision.  Location:
-$PDZ_TUNE_CACHE, else ~/.cache/pdz/hv_plans.json.
+architecture, the ordered list of its problems' keys (hashed) and precision.  An entry names the
+plan space it was the fastest of; one of another space is tuned again, since a plan kept from it
+would shut out kernels it did not know.  Location: $PDZ_TUNE_CACHE, else ~/.cache/pdz/hv_plans.json.
 """
 import hashlib
 import json
 import os
+
+PLAN_SPACE = 2      # 1 (entries that name none): before the one-pass products over short rows and their batched tiles
 
 
 def cache_path():
@@ -47,6 +50,12 @@ def _load(path):
         return {}
 
 
+def _current(cache, key):
+    """The entry of `key` if it is of the present plan space, else None."""
+    entry = cache.get(key)
+    return entry if entry and entry.get("space") == PLAN_SPACE else None
+
+
 def _store(path, key, entry):
     cache = _load(path)
     cache[key] = entry
@@ -61,13 +70,12 @@ def tuned_plan(problem, dtype_name, reps=5, path=None, retune=False, arch=None):
     """H.v plan from the cache, or tune now (libpdz autotuner) and store it; returns (entry, trials)."""
     path = path or cache_path()
     key = plan_key(problem, dtype_name, arch or _arch())
-    cache = _load(path)
-    if not retune and key in cache:
-        entry = cache[key]
+    entry = _current(_load(path), key)
+    if not retune and entry:
         problem.set_plan(dtype_name, entry["down"], entry["up_cw"], entry.get("up", 0), entry.get("map", 0))
         return entry, None
     best, trials = problem.tune(dtype_name, reps=reps)
-    entry = dict(best, ms=min(t["ms"] for t in trials))
+    entry = dict(best, ms=min(t["ms"] for t in trials), space=PLAN_SPACE)
     _store(path, key, entry)
     return entry, trials
 
@@ -76,12 +84,11 @@ def tuned_batch_plan(batch, dtype_name, reps=5, path=None, retune=False, arch=No
     """Batched H.v plan from the cache, or tune now (libpdz batch autotuner) and store it."""
     path = path or cache_path()
     key = batch_key(batch.problems, dtype_name, arch or _arch())
-    cache = _load(path)
-    if not retune and key in cache:
-        entry = cache[key]
+    entry = _current(_load(path), key)
+    if not retune and entry:
         batch.set_plan(entry["tile_elems"], entry["block"], entry["wgs_per_cu"], entry["order"])
         return entry, None
     best, trials = batch.tune(dtype_name, reps=reps)
-    entry = dict(best, ms=min(t["ms"] for t in trials))
+    entry = dict(best, ms=min(t["ms"] for t in trials), space=PLAN_SPACE)
     _store(path, key, entry)
     return entry, trials

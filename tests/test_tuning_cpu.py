@@ -86,3 +86,19 @@ def test_corrupt_cache_is_ignored(tmp_path):
     g = _ring(8)
     tuning.tuned_plan(g, "f32", path=str(path), arch="gfx950")
     assert g.tuned == 1 and json.loads(path.read_text())
+
+
+def test_plans_of_an_older_plan_space_are_tuned_again(tmp_path):
+    """An entry written before the one-pass products names no plan space: kept, it would pin the two passes."""
+    path = str(tmp_path / "plans.json")
+    g, b = _ring(8), FakeBatch([_ring(8), _ring(10)])
+    old = {tuning.plan_key(g, "f64", "gfx950"): {"down": 2, "up_cw": 128, "up": 1, "map": 3, "ms": 0.02},
+           tuning.batch_key(b.problems, "f64", "gfx950"): {"tile_elems": 4096, "block": 1024, "wgs_per_cu": 4,
+                                                           "order": 1, "ms": 0.2}}
+    with open(path, "w") as f:
+        json.dump(old, f)
+    for _ in range(2):
+        tuning.tuned_plan(g, "f64", path=path, arch="gfx950")
+        tuning.tuned_batch_plan(b, "f64", path=path, arch="gfx950")
+    assert g.tuned == 1 and b.tuned == 1
+    assert g.plans == [("f64", (3, 64, 1, 3))] and b.plans == [(2048, 1024, 4, 1)]
