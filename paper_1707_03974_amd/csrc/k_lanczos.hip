@@ -952,7 +952,8 @@ struct Run {
             if (st != PDZ_OK) return st;
             mark(1);
             mark(2);
-            as.n1 = c.nwhole;
+            as.p2 = partial();
+            as.n2 = c.nwhole;
         } else {
             pdz_status st = launch_hv_any(p, (pdz_dtype)o->storage, q, w, s, done(), kPassDown | kPassUp, nullptr, pitch);
             if (st != PDZ_OK) return st;

@@ -103,3 +103,21 @@ def test_lanczos_on_one_pass_products():
         b = g.lanczos(storage=storage, tol=tol, max_iter=400, ritz=yb, keep_basis=1, use_graph=0)
         assert abs(a["E0_refined"] - E) <= bound * abs(E)
         assert a["E0"] == b["E0"] and torch.equal(ya, yb)     # kept and regenerated vectors, graph and stream
+
+
+@pytest.mark.parametrize("storage", ["f64", "f32"])
+def test_alpha_from_more_partial_sums_than_one_work_group_adds(storage):
+    """92,378 rows give 23,095 partial sums of q . H q: alpha and beta of the first steps against plain dot
+    products of the same vectors (FP64; rounding of 1.6e7 terms in any order, below 1e-12)."""
+    torch = torch_cuda()
+    dt = torch.float64 if storage == "f64" else torch.float32
+    g = _problem((19, _ring(19), 9, 2))
+    v = to_dev(synth.random_vector(g.D, 8), dt)
+    r = g.lanczos(v0=v, storage=storage, max_iter=3, tol=0.0, coefficients=True)
+    q, hq = v.double(), g.hv(v).double()
+    n2 = (q @ q).item()
+    a0 = (q @ hq).item() / n2
+    assert abs(r["alpha"][0] - a0) <= 1e-12 * abs(a0)
+    w = hq - a0 * q
+    b1 = (w.norm() / n2 ** 0.5).item()
+    assert abs(r["beta"][1] - b1) <= (1e-12 if storage == "f64" else 1e-6) * b1
