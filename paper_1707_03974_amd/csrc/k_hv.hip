@@ -1508,6 +1508,7 @@ bool up_pair(const pdz_problem_s* p, size_t es, int cw, int up) {
 // without wide lanes takes batches of 8 hops, a variant without the default
 // width its widest.
 HvPlan plan_fill(const pdz_problem_s* p, pdz_dtype dt, HvPlan pl) {
+    if (!pl.down && !pl.up_cw && !pl.up && !pl.map) return default_plan(p, dt);
     const size_t es = dt == PDZ_F64 ? 8 : 4;
     // a set field of the up pass asks for the two passes
     const HvPlan d = pl.up_cw || pl.up || pl.map ? two_pass_plan(p, dt) : default_plan(p, dt);
