@@ -6,8 +6,8 @@
 //     [full re-orthogonalisation against v_1..v_k, twice];
 //     beta_{k+1} = |w|;  v_{k+1} = w / beta_{k+1}.
 // T_k = tridiag(beta, alpha, beta).  Its lowest eigenvalue theta comes from
-// Sturm-count multisection, its eigenvector s from inverse iteration, and the
-// Ritz pair is accepted when beta_{k+1} |s_k| <= tol |theta|.
+// multisection on the leading minors (tridiag.h), its eigenvector s from inverse
+// iteration, and the Ritz pair is accepted when beta_{k+1} |s_k| <= tol |theta|.
 //
 // Vectors may be stored in FP32 or FP64; every dot product multiplies in FP64
 // and accumulates in FP64.  Reductions use a fixed grid and a fixed tree, so

@@ -225,7 +225,8 @@ __device__ __forceinline__ void write_out(float* out, uint64_t s, float o0, floa
 // states; with 16 states a wave they would cost half as much as the ALU work).
 // 1.31e8 states (4x4, 7 + 7): 19.2 ms with 16 states a wave, the hidden layer
 // through LDS, scalar rounding to BF16 and the last layer on the vector ALUs;
-// 9.4 ms so (576 TFLOP/s).
+// 9.6 ms with the last layer's four tiles in one accumulator behind masked
+// weights, 9.4 ms so (576 TFLOP/s; the accumulators cost ten spilled registers).
 constexpr int kFwdTiles = 4;             // state tiles of 16 per wave
 constexpr int kFwdStates = 4 * 16 * kFwdTiles;   // states per work group and turn
 template <typename T, bool BASIS>

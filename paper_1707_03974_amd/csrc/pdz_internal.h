@@ -75,9 +75,11 @@ struct ParSpace; // inversion-parity tables (k_parity.hip)
 // H.v launch plan for one precision (0 = automatic choice).
 struct HvPlan {
     int down = 0;    // 1: one row per group, hop table loaded up front; 2: one row, table in a loop;
-                     // 3: two rows per group, table in a loop; 8: short rows, the whole product in one pass
+                     // 3, 4: two, three rows per group, table in a loop; 5, 6, 7: one, two, three rows
+                     // through the gather schedule; 8: short rows, the whole product in one pass
     int up_cw = 0;   // up-pass chunk width in columns
-    int up = 0;      // 1: hops of a row loaded in batches of 8; 2: all hops of a row loaded up front
+    int up = 0;      // 1: hops of a row loaded in batches of 8; 2: all hops of a row loaded up front;
+                     // 3: batches of 16; 4: batches of 8 with 16-byte lanes
     int map = 0;     // up-pass tile order: 1 XCD-aware chunk pairs, 2 chunk-major, 3 XCD-aware single chunks
 };
 }  // namespace pdz
