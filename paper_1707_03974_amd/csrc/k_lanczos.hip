@@ -1242,10 +1242,11 @@ struct Run {
             if (st != PDZ_OK) return st;
         }
         const bool lag = !fuse && lag_path(counts);
-        // `period` steps; first: the run's first ones
+        // `period` steps; first: the run's first ones, none past its last
         auto enqueue_block = [&](bool first) -> pdz_status {
+            const int n = first ? std::min(period, o->max_iter) : period;
             int t0 = 0, len = first ? 1 : kRitzBlock;   // the block of Ritz pairs: its first step and length
-            for (int t = 0; t < period; ++t) {
+            for (int t = 0; t < n; ++t) {
                 pdz_status s2;
                 if (fuse) {
                     const int a = t % 2;
@@ -1255,7 +1256,7 @@ struct Run {
                     s2 = step_scaled(buf(a), buf((a + 2) % 3), buf((a + 1) % 3), counts, lag ? t - t0 : -1);
                 }
                 if (s2 != PDZ_OK) return s2;
-                if (lag && (t + 1 == t0 + len || t + 1 == period)) {
+                if (lag && (t + 1 == t0 + len || t + 1 == n)) {
                     end_block(t + 1 - t0);
                     t0 = t + 1;
                     len = first ? std::min(2 * t0 + 1, kRitzBlock) : kRitzBlock;   // 1, 3, 9, then whole ones

@@ -122,3 +122,18 @@ def test_runs_that_end_in_their_first_steps(check_every, use_graph):
             assert r["alpha"] == full["alpha"][:n] and r["beta"] == full["beta"][:n + 1]
             if mix == 0.0:
                 assert n <= 1 + (tol < 1e-5)
+
+
+@pytest.mark.parametrize("max_iter", [1, 2, 3, 4, 5, 13, 14])
+def test_runs_shorter_than_a_check_interval(max_iter):
+    """Fewer steps than the first interval holds: the run ends with them, wherever its blocks would have."""
+    import paper_1707_03974_amd as pdz
+    torch_cuda()
+    g = pdz.Problem.from_workload(synth.workload("ring8"))
+    full = g.lanczos(max_iter=40, tol=0.0, history=True, coefficients=True)
+    for ce, ug in ((1000, 0), (1000, 1), (12, 1), (1, 1)):
+        r = g.lanczos(max_iter=max_iter, tol=0.0, check_every=ce, use_graph=ug, history=True, coefficients=True,
+                      refine=1)
+        assert r["iters"] == max_iter and r["converged"] == 0
+        for k, n in (("thetas", max_iter), ("alpha", max_iter), ("beta", max_iter + 1)):
+            assert r[k] == full[k][:n], (k, ce)
